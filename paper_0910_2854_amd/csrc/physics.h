@@ -73,6 +73,40 @@ __device__ __forceinline__ double rinv64(double rho, float rho32) {
   return r0 * (2.0 - rho * r0);
 }
 
+// max(x, 0) that keeps a NaN (the result of an invalid operation has its sign
+// bit clear): one integer instruction on the sign.  In FP64 only the high word
+// is tested, so a negative x leaves a subnormal >= 0 in place of zero.
+__device__ __forceinline__ float nonneg(float x) { return __int_as_float(max(__float_as_int(x), 0)); }
+__device__ __forceinline__ double nonneg(double x) {
+  const long long b = __double_as_longlong(x);
+  return __longlong_as_double(((long long)max((int)(b >> 32), 0) << 32) | (b & 0xffffffffll));
+}
+
+// max(a, b) of two speeds >= 0; a NaN in either operand wins (FP32: the bit
+// patterns of non-negative numbers are ordered as the numbers, NaNs above all).
+__device__ __forceinline__ float speed_max(float a, float b) {
+  return __int_as_float(max(__float_as_uint(a), __float_as_uint(b)));
+}
+__device__ __forceinline__ double speed_max(double a, double b) { return a > b ? a : b; }
+
+// A cell's centred field and b^2 (in FP64, for the pressure).  The field is
+// fixed during L_d, so the half-step state takes both over from the first
+// evaluation of the cell.
+template <typename T>
+struct FieldQ {
+  T b[3];
+  double b2;
+};
+template <typename T>
+__device__ __forceinline__ FieldQ<T> field_quantities(const T* b) {
+  FieldQ<T> f;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) f.b[k] = b[k];
+  const double bx = (double)b[0], by = (double)b[1], bz = (double)b[2];
+  f.b2 = bx * bx + by * by + bz * bz;
+  return f;
+}
+
 // Quantities of one cell for a sweep along D (Sect. 2.2).  F is the flux of
 // Eq. (17) with x replaced by D, d the freezing speed |v_D| + c_F of Eq. (21).
 // cS and xiE (= -(E + p), the energy entry of Eq. 50) only for HSE.
@@ -88,41 +122,44 @@ struct CellQ {
 // E = rho e + m^2/(2 rho) + b^2/2 and p = (gamma-1) rho e (Sect. 2.1, Eq. 5):
 // the cancellation step, always evaluated in FP64.
 template <typename T>
-__device__ __forceinline__ T pressure(const T* u, const T* b, double gm1, T* b2_out) {
+__device__ __forceinline__ T pressure(const T* u, double b2, double gm1) {
   const double rho = (double)u[RHO];
   const double mx = (double)u[MX], my = (double)u[MY], mz = (double)u[MZ];
-  const double bx = (double)b[0], by = (double)b[1], bz = (double)b[2];
-  const double b2 = bx * bx + by * by + bz * bz;
   const double m2 = mx * mx + my * my + mz * mz;
   const double ri = rinv64(rho, u[RHO]);
-  *b2_out = (T)b2;
   return (T)(gm1 * ((double)u[EN] - 0.5 * m2 * ri - 0.5 * b2));
 }
 
+// Directional fast magnetosonic speed (named after Eq. 21) from q = a^2 +
+// b^2/rho: c_F^2 = q/2 + sqrt((q/2)^2 - a^2 b_d^2/rho).
+template <typename T>
+__device__ __forceinline__ T fast_speed(T q, T a2, T bd, T ri) {
+  const T h = T(0.5) * q;
+  return fsqrt(h + fsqrt(nonneg(h * h - a2 * bd * bd * ri)));
+}
+
 template <typename T, int D, bool HSE>
-__device__ __forceinline__ void cell_quantities(const T* u, const T* b, double gamma, CellQ<T, HSE>& c) {
+__device__ __forceinline__ void cell_quantities(const T* u, const FieldQ<T>& f, double gamma, CellQ<T, HSE>& c) {
 #pragma unroll
   for (int k = 0; k < 5; ++k) c.u[k] = u[k];
   const T ri = rcp(u[RHO]);
   const T v[3] = {u[MX] * ri, u[MY] * ri, u[MZ] * ri};
-  T b2;
-  const T p = pressure<T>(u, b, gamma - 1.0, &b2);
+  const T p = pressure<T>(u, f.b2, gamma - 1.0);
+  const T b2 = (T)f.b2;
   const T ptot = p + T(0.5) * b2;
-  const T bv = b[0] * v[0] + b[1] * v[1] + b[2] * v[2];
-  // Directional fast magnetosonic speed (named after Eq. 21).
   const T a2 = (T)gamma * p * ri;
   const T q = a2 + b2 * ri;
-  const T disc = q * q - T(4) * a2 * b[D] * b[D] * ri;
-  const T cf = fsqrt(T(0.5) * (q + fsqrt(disc < T(0) ? T(0) : disc)));
+  const T bv = f.b[0] * v[0] + f.b[1] * v[1] + f.b[2] * v[2];
+  const T cf = fast_speed(q, a2, f.b[D], ri);
   const T md = u[MX + D];
   c.F[RHO] = md;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    T f = md * v[k] - b[D] * b[k];
-    if (k == D) f += ptot;
-    c.F[MX + k] = f;
+    T x = md * v[k] - f.b[D] * f.b[k];
+    if (k == D) x += ptot;
+    c.F[MX + k] = x;
   }
-  c.F[EN] = (u[EN] + ptot) * v[D] - b[D] * bv;
+  c.F[EN] = (u[EN] + ptot) * v[D] - f.b[D] * bv;
   c.vd = v[D];
   c.cF = cf;
   c.d = fabs(v[D]) + cf;
@@ -136,31 +173,34 @@ __device__ __forceinline__ void cell_quantities(const T* u, const T* b, double g
   }
 }
 
-// Limiters, Eqs. (29)-(30).  van Leer as the harmonic mean 2ab/(a+b) where a
-// and b share a sign (the printed sign prefactor would flip negative pairs).
-template <typename T>
-__device__ __forceinline__ T minmod(T a, T b) {
-  if (a * b <= T(0)) return T(0);
-  return a > T(0) ? (a < b ? a : b) : (a > b ? a : b);
+// Limiters, Eqs. (29)-(30).  minmod as the median of a, b and 0.
+__device__ __forceinline__ float minmod(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
+__device__ __forceinline__ double minmod(double a, double b) {
+  return fmax(fmin(a, b), 0.0) + fmin(fmax(a, b), 0.0);
 }
+// Half the van Leer limiter, the harmonic mean ab/(a+b) where a and b share a
+// sign (the printed sign prefactor would flip negative pairs), else 0.
 template <typename T>
-__device__ __forceinline__ T vanleer(T a, T b) {
+__device__ __forceinline__ T half_vanleer(T a, T b) {
   // the quotient is formed unconditionally and selected: as an arm of the
   // conditional, the FP64 reciprocal's length would keep it a branch
   const T ab = a * b;
-  const T q = T(2) * ab * rcp(a + b);
+  const T q = ab * rcp(a + b);
   return ab > T(0) ? q : T(0);
 }
+// The limited value of a and b, LIM 0 minmod, 1 van Leer, 2 the switch of
+// Sect. 2.2 (minmod where the cell is supersonic, sup = 1; van Leer elsewhere),
+// as the cheapest multiple of it: limit_unit<LIM>() times the result is the
+// limited value.
 template <typename T, int LIM>
-__device__ __forceinline__ T limit(T a, T b) {
-  return LIM == 0 ? minmod(a, b) : vanleer(a, b);
+__device__ __forceinline__ T limit_scaled(T sup, T a, T b) {
+  if (LIM == 0) return minmod(a, b);
+  if (LIM == 1) return half_vanleer(a, b);
+  return sup != T(0) ? T(0.5) * minmod(a, b) : half_vanleer(a, b);
 }
-// Limiter of one cell: LIM 0 minmod, 1 van Leer, 2 the switch of Sect. 2.2
-// (minmod where the cell is supersonic, sup = 1; van Leer elsewhere).
-template <typename T, int LIM>
-__device__ __forceinline__ T limit_cell(T sup, T a, T b) {
-  if (LIM == 2) return sup != T(0) ? minmod(a, b) : vanleer(a, b);
-  return limit<T, LIM>(a, b);
+template <int LIM>
+__device__ constexpr int limit_unit() {
+  return LIM == 0 ? 1 : 2;
 }
 
 // Dissipation Q_j at the interface between cells L and R, so that the
@@ -172,13 +212,13 @@ template <typename T, bool HSE>
 __device__ __forceinline__ void dissipation(const CellQ<T, HSE>& L, const CellQ<T, HSE>& R, T phiL, T phiR,
                                             T* Q) {
   if (!HSE) {
-    const T dmax = L.d > R.d ? L.d : R.d;
+    const T dmax = speed_max(L.d, R.d);
 #pragma unroll
     for (int k = 0; k < 5; ++k) Q[k] = dmax * (R.u[k] - L.u[k]);
   } else {
     const T avL = fabs(L.vd), avR = fabs(R.vd);
-    const T dadv = avL > avR ? avL : avR;
-    const T dac = L.cF > R.cF ? L.cF : R.cF;
+    const T dadv = speed_max(avL, avR);
+    const T dac = speed_max(L.cF, R.cF);
     const T scale = (phiR - phiL) * rcp(L.cS * R.cS);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {

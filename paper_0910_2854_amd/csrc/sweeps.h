@@ -120,9 +120,16 @@ __device__ __forceinline__ double lane_shr(double cur) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+template <typename T>
+__device__ __forceinline__ FieldQ<T> lane_shr(const FieldQ<T>& f);
+
 struct LaneShift {
   template <typename T>
   __device__ __forceinline__ static T prev(const T& cur, const T&, T&) {
+    return lane_shr(cur);
+  }
+  template <typename T>
+  __device__ __forceinline__ static FieldQ<T> prev(const FieldQ<T>& cur, const FieldQ<T>&, FieldQ<T>&) {
     return lane_shr(cur);
   }
   template <typename T, bool HSE>
@@ -146,6 +153,16 @@ struct LaneShift {
     return o;
   }
 };
+
+// (the lane shift of a cell's field)
+template <typename T>
+__device__ __forceinline__ FieldQ<T> lane_shr(const FieldQ<T>& f) {
+  FieldQ<T> o;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) o.b[k] = lane_shr(f.b[k]);
+  o.b2 = lane_shr(f.b2);
+  return o;
+}
 
 template <typename T, int N>
 struct Vec {
@@ -325,13 +342,14 @@ __device__ __forceinline__ T inv_span(T wm, T w0, T wp) {
 // uniform mesh), and the inverse centre spans of c-1 and c-3 for gravity.
 template <typename T>
 struct FluidNU {
-  T kh1, kf3, wl2, wr2, isp1, isp3;
+  T kh1, kf3;  // halved, as FluidConsts::kh2 and kf2
+  T wl2, wr2, isp1, isp3;
 };
 template <typename T>
 __device__ __forceinline__ FluidNU<T> fluid_nu(const T* w, T dt) {
   FluidNU<T> n;
-  n.kh1 = T(0.5) * dt * rcp(w[3]);
-  n.kf3 = dt * rcp(w[1]);
+  n.kh1 = T(0.25) * dt * rcp(w[3]);
+  n.kf3 = T(0.5) * dt * rcp(w[1]);
   n.wl2 = w[2] * rcp(w[1] + w[2]);
   n.wr2 = w[2] * rcp(w[2] + w[3]);
   n.isp1 = inv_span(w[2], w[3], w[4]);
@@ -341,14 +359,15 @@ __device__ __forceinline__ FluidNU<T> fluid_nu(const T* w, T dt) {
 
 template <typename T>
 struct FluidConsts {
-  T k_half, k_full, half_dt, dt, inv2h, halfalpha;
+  T kh2, kf2;  // half of dt / (2h) and of dt / h: the fluxes they multiply are kept doubled
+  T half_dt, dt, inv2h, alpha;
   double gamma;
 };
 
 template <typename T, bool HSE>
 struct FluidHist {
   CellQ<T, HSE> q0, q1;
-  Vec<T, 3> bc;
+  FieldQ<T> f;
   Vec<T, 5> F1, ap, am, Lp, bs, F2, ua, ub;
   T ph1, ph2, ph3, ph4, rp1, rp2, mp1, mp2, sp1;
   __device__ void zero() {
@@ -359,7 +378,8 @@ struct FluidHist {
     }
     q0.vd = q0.cF = q0.d = q0.cS = q0.xiE = q0.sup = T(0);
     q1.vd = q1.cF = q1.d = q1.cS = q1.xiE = q1.sup = T(0);
-    bc.v[0] = bc.v[1] = bc.v[2] = T(0);
+    f.b[0] = f.b[1] = f.b[2] = T(0);
+    f.b2 = 0.0;
     ph1 = ph2 = ph3 = ph4 = rp1 = rp2 = mp1 = mp2 = sp1 = T(0);
   }
 };
@@ -391,20 +411,24 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   for (int i = 0; i < 5; ++i) uc[i] = uc_in[i];
   if (GRAV == 2) gravity_kick<T, D>(uc, gh_c);
   // cell quantities of u at c and c-1
+  const FieldQ<T> f0 = field_quantities<T>(bcc.v);
   CellQ<T, HSE> q0;
-  cell_quantities<T, D, HSE>(uc, bcc.v, k.gamma, q0);
+  cell_quantities<T, D, HSE>(uc, f0, k.gamma, q0);
   const CellQ<T, HSE> q0m = H::prev(q0, hi.q0, ho.q0);
-  const Vec<T, 3> bcm = prev_vec<H>(bcc, hi.bc, ho.bc);
-  // predictor flux at interface c-1/2 (Eq. 24, dissipation scaled by alpha)
+  const FieldQ<T> f0m = H::prev(f0, hi.f, ho.f);
+  // predictor flux at interface c-1/2 (Eq. 24, dissipation scaled by alpha).
+  // All fluxes and flux differences are kept doubled and the step factors
+  // halved: the scalings by 1/2 of Eqs. (24)-(34) are exact, so leaving them
+  // out changes no result and saves 35 products per position.
   T Q[5];
   Vec<T, 5> F1;
   dissipation<T, HSE>(q0m, q0, phm1, phc, Q);
 #pragma unroll
-  for (int i = 0; i < 5; ++i) F1.v[i] = T(0.5) * (q0m.F[i] + q0.F[i]) - k.halfalpha * Q[i];
+  for (int i = 0; i < 5; ++i) F1.v[i] = (q0m.F[i] + q0.F[i]) - k.alpha * Q[i];
   const Vec<T, 5> F1m = prev_vec<H>(F1, hi.F1, ho.F1);
   // predictor half step of cell c-1 (Eq. 41; Eq. 69 on an irregular mesh)
   T up[5];
-  const T khalf = NU ? nu.kh1 : k.k_half;
+  const T khalf = NU ? nu.kh1 : k.kh2;
   if (GRAV == 1) {
     T S[5];
     gravity_source<T, D>(q0m.u[RHO], q0m.u[MX + D], phc - phm2, NU ? nu.isp1 : k.inv2h, S);
@@ -416,7 +440,7 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   }
   // cell quantities of the half-step state of c-1 (field unchanged), and of c-2
   CellQ<T, HSE> q1;
-  cell_quantities<T, D, HSE>(up, bcm.v, k.gamma, q1);
+  cell_quantities<T, D, HSE>(up, f0m, k.gamma, q1);
   const CellQ<T, HSE> q1m = H::prev(q1, hi.q1, ho.q1);
   // relaxed flux differences across interface c-3/2 (between c-2 and c-1)
   T Qc[5];
@@ -425,9 +449,9 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
     const T dF = q1.F[i] - q1m.F[i];
-    ap.v[i] = T(0.5) * (dF + Qc[i]);
-    am.v[i] = T(0.5) * (dF - Qc[i]);
-    bs.v[i] = T(0.5) * (q1m.F[i] + q1.F[i]) - T(0.5) * Qc[i];
+    ap.v[i] = dF + Qc[i];
+    am.v[i] = dF - Qc[i];
+    bs.v[i] = (q1m.F[i] + q1.F[i]) - Qc[i];
   }
   const Vec<T, 5> apm = prev_vec<H>(ap, hi.ap, ho.ap);
   const Vec<T, 5> amm = prev_vec<H>(am, hi.am, ho.am);
@@ -435,25 +459,26 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   // limited second-order flux at interface c-5/2 (Eq. 34); both limiters
   // taken here belong to cell c-2 (its half-step state decides the switch)
   const T sup2 = LIM == 2 ? H::prev(q1.sup, hi.sp1, ho.sp1) : T(0);
-  // (irregular mesh: each difference weighted to put cell c-2's slope on its
-  // interfaces, which absorbs the 1/2)
+  // (the flux is doubled and so are the differences: half their limited value;
+  // irregular mesh: each difference weighted to put cell c-2's slope on its
+  // interfaces, which absorbs that half)
   Vec<T, 5> Lp, F2;
+  constexpr T unit = T(NU ? 1.0 : 0.5) * limit_unit<LIM>();
   if (!NU) {
 #pragma unroll
-    for (int i = 0; i < 5; ++i) Lp.v[i] = limit_cell<T, LIM>(sup2, apm.v[i], ap.v[i]);
+    for (int i = 0; i < 5; ++i) Lp.v[i] = limit_scaled<T, LIM>(sup2, apm.v[i], ap.v[i]);
   } else {
 #pragma unroll
-    for (int i = 0; i < 5; ++i) Lp.v[i] = limit_cell<T, LIM>(sup2, nu.wl2 * apm.v[i], nu.wr2 * ap.v[i]);
+    for (int i = 0; i < 5; ++i) Lp.v[i] = limit_scaled<T, LIM>(sup2, nu.wl2 * apm.v[i], nu.wr2 * ap.v[i]);
   }
   const Vec<T, 5> Lpm = prev_vec<H>(Lp, hi.Lp, ho.Lp);
   if (!NU) {
 #pragma unroll
-    for (int i = 0; i < 5; ++i)
-      F2.v[i] = bsm.v[i] + T(0.5) * (Lpm.v[i] - limit_cell<T, LIM>(sup2, amm.v[i], am.v[i]));
+    for (int i = 0; i < 5; ++i) F2.v[i] = bsm.v[i] + unit * (Lpm.v[i] - limit_scaled<T, LIM>(sup2, amm.v[i], am.v[i]));
   } else {
 #pragma unroll
     for (int i = 0; i < 5; ++i)
-      F2.v[i] = bsm.v[i] + (Lpm.v[i] - limit_cell<T, LIM>(sup2, nu.wl2 * amm.v[i], nu.wr2 * am.v[i]));
+      F2.v[i] = bsm.v[i] + unit * (Lpm.v[i] - limit_scaled<T, LIM>(sup2, nu.wl2 * amm.v[i], nu.wr2 * am.v[i]));
   }
   const Vec<T, 5> F2m = prev_vec<H>(F2, hi.F2, ho.F2);
   // state of cell c-3 before the sweep
@@ -474,7 +499,7 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
     for (int i = 0; i < 5; ++i) u3[i] = um3.v[i];
   }
   // corrector of cell c-3 (Eq. 43)
-  const T kfull = NU ? nu.kf3 : k.k_full;
+  const T kfull = NU ? nu.kf3 : k.kf2;
   if (GRAV == 1) {
     const T rpm2 = H::prev(up[RHO], hi.rp1, ho.rp1);   // rho' of c-2
     const T rpm3 = H::prev(rpm2, hi.rp2, ho.rp2);      // rho' of c-3
@@ -498,12 +523,12 @@ template <typename T>
 __device__ __forceinline__ FluidConsts<T> fluid_consts(const FluidArgs<T>& a, int D) {
   const double dt = a.sc->dt;
   FluidConsts<T> k;
-  k.k_half = (T)a.sc->kh[D];
-  k.k_full = (T)a.sc->kf[D];
+  k.kh2 = T(0.5) * (T)a.sc->kh[D];
+  k.kf2 = T(0.5) * (T)a.sc->kf[D];
   k.half_dt = (T)(0.5 * dt);
   k.dt = (T)dt;
   k.inv2h = (T)a.i2h[D];
-  k.halfalpha = (T)(0.5 * a.alpha);
+  k.alpha = (T)a.alpha;
   k.gamma = a.gamma;
   return k;
 }
@@ -548,7 +573,7 @@ __device__ __forceinline__ bool strided_map(int wave, int nA, int nO, int nseg, 
 // alternative to the lanes policy) they walk along y, so that a wave's load
 // touches 64 rows, one value of each.
 template <typename T, int D, int GRAV, bool HSE, int LIM, bool NU>
-__global__ __launch_bounds__(256) void fluid_strided_kernel(FluidLaunch<T> L) {
+__global__ __launch_bounds__(256, sizeof(T) == 4 && GRAV == 0 && LIM != 2 && !NU ? 4 : 1) void fluid_strided_kernel(FluidLaunch<T> L) {
   constexpr int A = D == 0 ? 1 : 0;
   constexpr int O = D == 0 ? 2 : 3 - D;
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
@@ -662,19 +687,17 @@ __global__ __launch_bounds__(256) void fluid_strided_kernel(FluidLaunch<T> L) {
 // the maximum of the divided speeds is the divided maximum, bitwise.
 template <typename T>
 __device__ __forceinline__ void cell_cfl_speeds(const T* u, const T* b, double gamma, const Geo& g, T* sp, int& bad) {
-  T b2;
-  const T p = pressure<T>(u, b, gamma - 1.0, &b2);
+  const double b2 = field_quantities<T>(b).b2;
+  const T p = pressure<T>(u, b2, gamma - 1.0);
   const T ri = rcp(u[RHO]);
   const T a2 = (T)gamma * p * ri;
-  const T q = a2 + b2 * ri;
+  const T q = a2 + (T)b2 * ri;
   T sum = T(0);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     sp[d] = T(0);
     if (g.n[d] > 1) {
-      const T disc = q * q - T(4) * a2 * b[d] * b[d] * ri;
-      const T cf = fsqrt(T(0.5) * (q + fsqrt(disc < T(0) ? T(0) : disc)));
-      sp[d] = fabs(u[MX + d] * ri) + cf;
+      sp[d] = fabs(u[MX + d] * ri) + fast_speed(q, a2, b[d], ri);
       sum += sp[d];
     }
   }
@@ -998,12 +1021,13 @@ __device__ __forceinline__ T row_position(T w0, T bb, T b4_loaded, T k_half, T k
   const T fp4 = H::prev(fp3, hi.fp4, ho.fp4);
   const T fp5 = H::prev(fp4, hi.fp5, ho.fp5);
   T up, dn;
+  constexpr T unit = T(NU ? 1.0 : 0.5) * limit_unit<LIM>();
   if (!NU) {
-    up = fp4 + T(0.5) * limit<T, LIM>(fp4 - fp5, fp3 - fp4);
-    dn = fp3 - T(0.5) * limit<T, LIM>(fp3 - fp4, fp2 - fp3);
+    up = fp4 + unit * limit_scaled<T, LIM>(T(0), fp4 - fp5, fp3 - fp4);
+    dn = fp3 - unit * limit_scaled<T, LIM>(T(0), fp3 - fp4, fp2 - fp3);
   } else {
-    up = fp4 + limit<T, LIM>(fw.wl4 * (fp4 - fp5), fw.wr4 * (fp3 - fp4));
-    dn = fp3 - limit<T, LIM>(fw.wl3 * (fp3 - fp4), fw.wr3 * (fp2 - fp3));
+    up = fp4 + unit * limit_scaled<T, LIM>(T(0), fw.wl4 * (fp4 - fp5), fw.wr4 * (fp3 - fp4));
+    dn = fp3 - unit * limit_scaled<T, LIM>(T(0), fw.wl3 * (fp3 - fp4), fw.wr3 * (fp2 - fp3));
   }
   const T P2c = V7 > T(0) ? up : dn;                // Phi2 at c-7/2
   if (NEED_BN) {
@@ -1591,8 +1615,9 @@ __device__ __forceinline__ void row_position2(const T (&w0)[2], const T (&bb)[2]
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const T V7 = T(0.5) * (vb3[j] + vb2[j]);
-    const T up = fp4[j] + T(0.5) * limit<T, LIM>(fp4[j] - fp5[j], fp3[j] - fp4[j]);
-    const T dn = fp3[j] - T(0.5) * limit<T, LIM>(fp3[j] - fp4[j], fp2[j] - fp3[j]);
+    constexpr T unit = T(0.5) * limit_unit<LIM>();
+    const T up = fp4[j] + unit * limit_scaled<T, LIM>(T(0), fp4[j] - fp5[j], fp3[j] - fp4[j]);
+    const T dn = fp3[j] - unit * limit_scaled<T, LIM>(T(0), fp3[j] - fp4[j], fp2[j] - fp3[j]);
     P2c[j] = V7 > T(0) ? up : dn;
   }
   if (NEED_BN) {
