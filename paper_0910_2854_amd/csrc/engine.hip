@@ -25,7 +25,7 @@ constexpr long long kAlign = 64;  // box offsets in elements (256 B in FP32)
 
 Tuning default_tuning() {
   Tuning t;
-  t.target[K_FLUID_X] = 768;
+  t.target[K_FLUID_X] = 1536;
   t.target[K_FIELD_X] = 768;
   t.target[K_FLUID_Y] = t.target[K_FLUID_Z] = 64;
   t.target[K_FIELD_Y] = t.target[K_FIELD_Z] = 64;
@@ -593,7 +593,7 @@ static long long kind_waves(const HostBox& b, int kind, int target, int groups, 
         *par = seg;
         return strided_waves(b.n[1], b.n[2], groups) * ceil_div(b.n[0], seg);
       }
-      const int rpw = std::max(1, target / (b.n[0] + 6));
+      const int rpw = std::max(1, target / (b.n[0] + 8));
       *par = rpw;
       return ceil_div((long long)b.n[1] * b.n[2], rpw);
     }
@@ -632,7 +632,7 @@ static long long kind_waves(const HostBox& b, int kind, int target, int groups, 
 // fish_set_shape or the autotuner is used as set.
 static int single_box_target(const HostBox& b, int kind, int target, int groups) {
   int lo = 1;
-  if (kind == K_FLUID_X) lo = groups ? 8 : b.n[0] + 6;
+  if (kind == K_FLUID_X) lo = groups ? 8 : b.n[0] + 8;
   if (kind == K_FIELD_X) lo = b.n[0] + 8;
   if (kind == K_FLUID_Y || kind == K_FLUID_Z || kind == K_FIELD_Y || kind == K_FIELD_Z) lo = 8;
   int par = 1;

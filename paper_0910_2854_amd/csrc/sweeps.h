@@ -123,6 +123,17 @@ __device__ __forceinline__ double lane_shr(double cur) {
 template <typename T>
 __device__ __forceinline__ FieldQ<T> lane_shr(const FieldQ<T>& f);
 
+// lane i takes lane i + 1, lane 63 zero
+__device__ __forceinline__ float lane_shl(float cur) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(cur), 0x130, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_shl(double cur) {
+  const long long cb = __double_as_longlong(cur);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(cb & 0xffffffffll), 0x130, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(cb >> 32), 0x130, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 struct LaneShift {
   template <typename T>
   __device__ __forceinline__ static T prev(const T& cur, const T&, T&) {
@@ -232,7 +243,7 @@ struct RowCursor {
 };
 
 // Branch-free maps for indices the stencils reach from a box row, i in
-// [-8, n + 4): a clamp on outflow axes, at most one period added or removed
+// [-8, n + 8): a clamp on outflow axes, at most one period added or removed
 // on periodic ones (boxes thinner than 8 cells take the general wrap).  bc and
 // n are uniform across the wave, so the choice of path is a scalar branch.
 // The periodic map is the smallest of i, i + n and i - n as unsigned values
@@ -770,12 +781,266 @@ __device__ __forceinline__ void publish_cfl(double cmax, int bad, Scalars* sc, c
   if (bad) atomicOr(&sc->status, 1);
 }
 
-// Lanes policy (D = x): each wave streams rows_per_wave whole x rows.  With
-// CFL the sweep also reduces the CFL speed of the state it writes (the last
-// sub-operator of a double step leaves the next step's time step ready).
+// ------------------------------------------------------------ L_x
+// Lanes policy (D = x).  A lane holds K consecutive cells of an x row, a wave
+// 64 K of a stream of whole rows, each padded by its ghosts.  A value of the
+// neighbouring cell is the lane's own register or, at the lane's edge, the
+// neighbour lane's by one DPP shift (folded into the instruction that uses it
+// where that is possible).  The outer lanes of a window are a halo that the
+// neighbouring windows output.
+//   K = 2: both cells of a lane in one 8-byte (FP64: 16-byte) load and store,
+//   and half the shifts, index arithmetic and halo of K = 1.  256^3: 200 us
+//   (FP64 356), K = 1 233 (384) and K = 2 with single-cell loads 234 (393); with
+//   the next window's loads ahead 261 (409), at 5 waves per SIMD instead of 6.
+//   The waves of a block that work on one box take the windows of their rows in
+//   turn: windows end inside the 128-byte lines of ten arrays, and the wave
+//   that reads the rest of a line should do so while it is still in the L1 or
+//   L2.  With a stretch of rows per wave the lines had left both (24 waves per
+//   CU): the 256^3 FP32 sweep fetched 937 MB of its 537, now 714.
+template <typename T, int K>
+__device__ __forceinline__ void from_left(const T (&x)[K], T (&o)[K]) {
+  o[0] = lane_shr(x[K - 1]);
+#pragma unroll
+  for (int j = 1; j < K; ++j) o[j] = x[j - 1];
+}
+template <typename T, int K>
+__device__ __forceinline__ void from_right(const T (&x)[K], T (&o)[K]) {
+#pragma unroll
+  for (int j = 0; j + 1 < K; ++j) o[j] = x[j + 1];
+  o[K - 1] = lane_shl(x[0]);
+}
+template <typename T, int K>
+__device__ __forceinline__ void from_left(const Vec<T, 5> (&x)[K], Vec<T, 5> (&o)[K]) {
+#pragma unroll
+  for (int i = 0; i < 5; ++i) o[0].v[i] = lane_shr(x[K - 1].v[i]);
+#pragma unroll
+  for (int j = 1; j < K; ++j) o[j] = x[j - 1];
+}
+template <typename T, int K>
+__device__ __forceinline__ void from_right(const Vec<T, 5> (&x)[K], Vec<T, 5> (&o)[K]) {
+#pragma unroll
+  for (int j = 0; j + 1 < K; ++j) o[j] = x[j + 1];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) o[K - 1].v[i] = lane_shl(x[0].v[i]);
+}
+template <typename T, bool HSE, int K>
+__device__ __forceinline__ void from_right(const CellQ<T, HSE> (&x)[K], CellQ<T, HSE> (&o)[K]) {
+#pragma unroll
+  for (int j = 0; j + 1 < K; ++j) o[j] = x[j + 1];
+  const CellQ<T, HSE>& c = x[0];
+  CellQ<T, HSE>& r = o[K - 1];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    r.u[i] = lane_shl(c.u[i]);
+    r.F[i] = i == RHO ? r.F[i] : lane_shl(c.F[i]);
+  }
+  r.F[RHO] = r.u[MX];  // the mass flux along x
+  r.d = lane_shl(c.d);
+  r.sup = T(0);
+  if (HSE) {
+    r.vd = lane_shl(c.vd);
+    r.cF = lane_shl(c.cF);
+    r.cS = lane_shl(c.cS);
+    r.xiE = lane_shl(c.xiE);
+  } else {
+    r.vd = r.cF = r.cS = r.xiE = T(0);
+  }
+}
+
+// Per-cell factors of an irregular mesh from the widths of the cell and its
+// neighbours (as FluidNU, which serves cells of several positions).
+template <typename T>
+struct CellNU {
+  T kh, kf, wl, wr, isp;
+};
+template <typename T>
+__device__ __forceinline__ CellNU<T> cell_nu(T wm, T w0, T wp, T dt) {
+  CellNU<T> n;
+  n.kh = T(0.25) * dt * rcp(w0);
+  n.kf = T(0.5) * dt * rcp(w0);
+  n.wl = w0 * rcp(wm + w0);
+  n.wr = w0 * rcp(w0 + wp);
+  n.isp = inv_span(wm, w0, wp);
+  return n;
+}
+
+// The sweep of a window: un of the lane's cells from their states u, field
+// products f, potential phi and (split gravity) kicks gh; the arithmetic of
+// fluid_position, with every value kept in the lane of its cell.  Interface j
+// is the one right of cell j.
+template <typename T, int GRAV, bool HSE, int LIM, bool NU, int K>
+__device__ __forceinline__ void fluid_window(const T (&u_in)[K][5], const FieldQ<T> (&f)[K], const T (&phi)[K],
+                                             const T (&gh)[K], const CellNU<T> (&nu)[K], const FluidConsts<T>& k,
+                                             T (&un)[K][5]) {
+  constexpr int D = 0;
+  T phl[K], phr[K];
+  from_left(phi, phl);
+  from_right(phi, phr);
+  T u[K][5];
+  CellQ<T, HSE> q[K], qr[K];
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) u[j][i] = u_in[j][i];
+    if (GRAV == 2) gravity_kick<T, D>(u[j], gh[j]);
+    cell_quantities<T, D, HSE>(u[j], f[j], k.gamma, q[j]);
+  }
+  from_right(q, qr);
+  // predictor
+  Vec<T, 5> F[K], Fl[K];
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    T Q[5];
+    dissipation<T, HSE>(q[j], qr[j], phi[j], phr[j], Q);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) F[j].v[i] = (q[j].F[i] + qr[j].F[i]) - k.alpha * Q[i];
+  }
+  from_left(F, Fl);
+  T up[K][5];
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const T khalf = NU ? nu[j].kh : k.kh2;
+    if (GRAV == 1) {
+      T S[5];
+      gravity_source<T, D>(u[j][RHO], u[j][MX + D], phr[j] - phl[j], NU ? nu[j].isp : k.inv2h, S);
+#pragma unroll
+      for (int i = 0; i < 5; ++i) up[j][i] = u[j][i] - khalf * (F[j].v[i] - Fl[j].v[i]) + k.half_dt * S[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 5; ++i) up[j][i] = u[j][i] - khalf * (F[j].v[i] - Fl[j].v[i]);
+    }
+    cell_quantities<T, D, HSE>(up[j], f[j], k.gamma, q[j]);
+  }
+  from_right(q, qr);
+  // corrector
+  Vec<T, 5> ap[K], am[K], bs[K], al[K], Lp[K], Lm[K], Lmr[K];
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    T Q[5];
+    dissipation<T, HSE>(q[j], qr[j], phi[j], phr[j], Q);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      const T dF = qr[j].F[i] - q[j].F[i];
+      ap[j].v[i] = dF + Q[i];
+      am[j].v[i] = dF - Q[i];
+      bs[j].v[i] = (q[j].F[i] + qr[j].F[i]) - Q[i];
+    }
+  }
+  from_left(ap, al);
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+      Lp[j].v[i] = NU ? limit_scaled<T, LIM>(q[j].sup, nu[j].wl * al[j].v[i], nu[j].wr * ap[j].v[i])
+                      : limit_scaled<T, LIM>(q[j].sup, al[j].v[i], ap[j].v[i]);
+  }
+  from_left(am, al);
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+      Lm[j].v[i] = NU ? limit_scaled<T, LIM>(q[j].sup, nu[j].wl * al[j].v[i], nu[j].wr * am[j].v[i])
+                      : limit_scaled<T, LIM>(q[j].sup, al[j].v[i], am[j].v[i]);
+  }
+  from_right(Lm, Lmr);
+  constexpr T unit = T(NU ? 1.0 : 0.5) * limit_unit<LIM>();
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) F[j].v[i] = bs[j].v[i] + unit * (Lp[j].v[i] - Lmr[j].v[i]);
+  }
+  from_left(F, Fl);
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const T kfull = NU ? nu[j].kf : k.kf2;
+    if (GRAV == 1) {
+      T S[5];
+      gravity_source<T, D>(up[j][RHO], up[j][MX + D], phr[j] - phl[j], NU ? nu[j].isp : k.inv2h, S);
+#pragma unroll
+      for (int i = 0; i < 5; ++i) un[j][i] = u[j][i] - kfull * (F[j].v[i] - Fl[j].v[i]) + k.dt * S[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 5; ++i) un[j][i] = u[j][i] - kfull * (F[j].v[i] - Fl[j].v[i]);
+      if (GRAV == 2) gravity_kick<T, D>(un[j], gh[j]);
+    }
+  }
+}
+
+// The rows of a block's waves that work on one box, as one stream of rows
+// padded to L positions, dealt to those waves in turn by windows.
+struct RowStream {
+  int L, first, rows;  // positions per row; first row (y + z ny) and number of rows
+  int turn, waves;     // this wave's turn among the group's waves
+  float invL, inv_n;
+  int n;               // rows per plane (n_y, or the face rows)
+  __device__ void init(int lw, int box_waves, int rows_per_wave, int L_, int n_, int nrows) {
+    const int in_block = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int g0 = max(lw - in_block, 0);
+    const int g1 = min(lw - in_block + (int)(blockDim.x >> 6), box_waves);
+    turn = lw - g0;
+    waves = g1 - g0;
+    first = g0 * rows_per_wave;
+    rows = min(waves * rows_per_wave, nrows - first);
+    L = L_;
+    n = n_;
+    invL = 1.0f / (float)L;
+    inv_n = 1.0f / (float)n;
+  }
+  // a / b for 0 <= a < 2^24 and its remainder, from the rounded reciprocal
+  __device__ static int divide(int a, int b, float inv, int& rem) {
+    int q = (int)((float)a * inv);
+    rem = a - q * b;
+    if (rem < 0) {
+      --q;
+      rem += b;
+    }
+    if (rem >= b) {
+      ++q;
+      rem -= b;
+    }
+    return q;
+  }
+  // position in its row, y and z of stream position pos (0 <= pos < rows L)
+  __device__ void locate(int pos, int& cp, int& y, int& z) const {
+    const int rr = divide(pos, L, invL, cp);
+    const int z0 = first / n;  // uniform
+    z = z0 + divide(first - z0 * n + rr, n, inv_n, y);
+  }
+};
+
+// Load/store of two consecutive elements (ld, st), aligned as one.
+template <typename T>
+struct PairOf {
+  typedef T type __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+};
+template <typename T>
+__device__ __forceinline__ void ld2(const T* p, unsigned off_bytes, T& v0, T& v1) {
+  asm("" : "+v"(off_bytes));
+  const typename PairOf<T>::type v =
+      *(const FISH_GLOBAL typename PairOf<T>::type*)((const FISH_GLOBAL char*)p + off_bytes);
+  v0 = v.x;
+  v1 = v.y;
+}
+template <typename T>
+__device__ __forceinline__ void st2(T* p, unsigned off_bytes, T v0, T v1) {
+  asm("" : "+v"(off_bytes));
+  typename PairOf<T>::type v;
+  v.x = v0;
+  v.y = v1;
+  *(FISH_GLOBAL typename PairOf<T>::type*)((FISH_GLOBAL char*)p + off_bytes) = v;
+}
+
+// With CFL the sweep also reduces the CFL speed of the state it writes (the
+// last sub-operator of a double step leaves the next step's time step ready).
 template <typename T, int GRAV, bool HSE, int LIM, bool CFL, bool NU>
 __global__ __launch_bounds__(256) void fluid_lanes_kernel(FluidLaunch<T> FL) {
-  constexpr int D = 0;
+  constexpr int K = 2;
+  // an output depends on 3 cells to its left and 3 to its right, the last of
+  // which takes its right face from a fourth
+  constexpr int HL = (3 + K - 1) / K, HR = (4 + K - 1) / K;
+  constexpr int OFF = HL * K;               // position of a row's cell 0
+  constexpr int STEP = (64 - HL - HR) * K;  // cells a window outputs
+  constexpr unsigned z4 = sizeof(T);
   __shared__ CflShared sh;
   if (CFL) cfl_shared_init(&sh);
   const BoxDesc* d;
@@ -784,134 +1049,141 @@ __global__ __launch_bounds__(256) void fluid_lanes_kernel(FluidLaunch<T> FL) {
   const FluidArgs<T> a = fluid_view<T, K_FLUID_X>(FL, *d);
   const Geo& g = a.g;
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-  const int L = nx + 6;                     // stream positions per row
-  const long long nrows = (long long)ny * nz;
-  const long long wave = lw;
+  const int nrows = ny * nz;  // < 2^32 bytes of cells
+  const int rpw = a.rows_per_wave;
+  RowStream rs;
+  rs.init(lw, (nrows + rpw - 1) / rpw, rpw, (OFF + nx + 4 + K - 1) / K * K, ny, nrows);
+  const int npos = rs.rows * rs.L;
   const int lane = threadIdx.x & 63;
-  const long long r0 = wave * a.rows_per_wave;
-  if (r0 >= nrows) return;  // whole wave exits together
-  const int rows = (int)min((long long)a.rows_per_wave, nrows - r0);
-  const int npos = rows * L;
-  // lanes 0..HALO-1 recompute the last positions of the previous iteration:
-  // the output of lane i depends on lanes i-6 .. i (the corrector's flux
-  // difference, the limited slopes, the relaxed differences, the predictor
-  // and its fluxes each reach one position back), so lanes 6..63 are exact
-  constexpr int HALO = 6, STEP = 64 - HALO;
-  const int nit = (npos + STEP - 1) / STEP;
-  const FluidConsts<T> k = fluid_consts(a, D);
-  FluidHist<T, HSE> hA, hB;  // unused by the carry-free policy
+  const FluidConsts<T> k = fluid_consts(a, 0);
   T smax[3] = {T(0), T(0), T(0)};  // per axis, the largest |v_d| + c_F,d of the lane's cells
   double cnu = 0.0;  // irregular mesh: the CFL speed over widths, per cell
   int bad = 0;
-  const unsigned st1 = (unsigned)g.st[1], st2 = (unsigned)g.st[2];  // arrays < 2^32 bytes
-  const unsigned up = st2 - (unsigned)(ny - 1) * st1;
-  RowCursor rc;
-  rc.init(lane - HALO, L, (int)r0, rows, ny, st1, st2, up);  // the halo lanes start before the stream (clamped to its start)
-  constexpr unsigned z4 = sizeof(T);
+  const unsigned st1 = (unsigned)g.st[1];  // arrays < 2^32 bytes
+  const unsigned plane_rows = (unsigned)(ny + g.bc[1]);
   // byte offsets of the face above the row's cells along y and z: the next
   // row or plane, or on a periodic axis from the last one back to the first
+  const unsigned stz = (unsigned)g.st[2] * z4;
   const unsigned dy_in = st1 * z4, dy_last = g.bc[1] ? dy_in : (unsigned)(1 - ny) * st1 * z4;
-  const unsigned dz_in = st2 * z4, dz_last = g.bc[2] ? dz_in : (unsigned)(1 - nz) * st2 * z4;
-  unsigned base = 0, dy = 0, dz = 0;  // the row's offset (elements) and face offsets (bytes)
-  T wy = T(1), wz = T(1);             // irregular mesh: widths of the row's cell in y, z
+  const unsigned dz_in = stz, dz_last = g.bc[2] ? dz_in : (unsigned)(1 - nz) * stz;
   struct In {
-    T u[5], u3[5];
-    Vec<T, 3> bc;
-    T phi, gh;
-    T w[5], wy, wz;  // irregular mesh: widths of cells c-4 .. c along x; the row's y, z widths
-    unsigned o3;  // byte offset of the output cell c-3
-    int co;       // output cell index along x
-    bool valid;
+    T u[K][5], bx[K], by[K][2], bz[K][2];
+    T phi[K], gh[K];
+    T w[K], wy, wz;  // irregular mesh: the cells' widths along x; the row's along y and z
+    unsigned o;      // byte offset of the lane's first cell (mapped into the box)
+    int c0;          // its index along x; out of the row: no output
   };
-  // inputs of the lane's next stream position (loads only, one iteration ahead)
-  auto load = [&](int it) {
-    if (rc.moved) {
-      const int y = rc.y, z = rc.z;
-      base = rc.base;
-      dy = y + 1 < ny ? dy_in : dy_last;
-      dz = z + 1 < nz ? dz_in : dz_last;
-      if (NU) {
-        wy = width_at(a.wid[1], y, ny, g.bc[1]);
-        wz = width_at(a.wid[2], z, nz, g.bc[2]);
+  auto load = [&](int win) {
+    In in;
+    const int pos = win * STEP + (lane - HL) * K;
+    int cp, y, z;
+    // positions before the stream or past it are moved onto it; they output nothing
+    rs.locate(min(max(pos, 0), npos - K), cp, y, z);
+    in.c0 = lane >= HL && lane < 64 - HR && pos < npos ? cp - OFF : -K;
+    const unsigned base = ((unsigned)z * plane_rows + (unsigned)y) * st1;
+    const unsigned dy = y + 1 < ny ? dy_in : dy_last, dz = z + 1 < nz ? dz_in : dz_last;
+    unsigned o[K], f[K];  // the cells and their low x faces
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      o[j] = (base + (unsigned)map_cell_near(cp - OFF + j, nx, g.bc[0])) * z4;
+      f[j] = (base + (unsigned)map_face_near(cp - OFF + j, nx, g.bc[0])) * z4;
+    }
+    in.o = o[0];
+    // a pair is split only where the row's ghosts wrap or are copies
+    if (__all(o[1] == o[0] + z4 && f[1] == f[0] + z4)) {
+#pragma unroll
+      for (int i = 0; i < 5; ++i) ld2(a.u[i], o[0], in.u[0][i], in.u[1][i]);
+      ld2(a.b[0], f[0], in.bx[0], in.bx[1]);
+      ld2(a.b[1], o[0], in.by[0][0], in.by[1][0]);
+      ld2(a.b[1], o[0] + dy, in.by[0][1], in.by[1][1]);
+      ld2(a.b[2], o[0], in.bz[0][0], in.bz[1][0]);
+      ld2(a.b[2], o[0] + dz, in.bz[0][1], in.bz[1][1]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) in.u[j][i] = ld(a.u[i], o[j]);
+        in.bx[j] = ld(a.b[0], f[j]);
+        in.by[j][0] = ld(a.b[1], o[j]);
+        in.by[j][1] = ld(a.b[1], o[j] + dy);
+        in.bz[j][0] = ld(a.b[2], o[j]);
+        in.bz[j][1] = ld(a.b[2], o[j] + dz);
       }
     }
-    In in;
-    in.valid = lane >= HALO && it * STEP + lane - HALO < npos;
-    // cell index along x (-3 .. nx+2); lanes past the end of the stream sit
-    // on the wave's last row with cp >= L and are clamped into it, and the
-    // halo lanes of the first iteration onto its start, so that every index
-    // they map stays in the box (they store nothing)
-    const int cpos = min(max(rc.cp, 0), L - 1) - 3;
-    in.co = cpos - 3;
-    const unsigned ms = (base + (unsigned)map_cell_near(cpos, nx, g.bc[0])) * z4;
 #pragma unroll
-    for (int i = 0; i < 5; ++i) in.u[i] = ld(a.u[i], ms);
-    const unsigned f0 = (base + (unsigned)map_face_near(cpos, nx, g.bc[0])) * z4;
-    const unsigned f1 = (base + (unsigned)map_face_near(cpos + 1, nx, g.bc[0])) * z4;
-    in.bc.v[0] = T(0.5) * (ld(a.b[0], f0) + ld(a.b[0], f1));
-    in.bc.v[1] = T(0.5) * (ld(a.b[1], ms) + ld(a.b[1], ms + dy));
-    in.bc.v[2] = T(0.5) * (ld(a.b[2], ms) + ld(a.b[2], ms + dz));
-    in.phi = GRAV ? load_phi(a.phi, (long long)base, 1, cpos, nx, g.bc[0]) : T(0);
+    for (int j = 0; j < K; ++j) {
+      const int c = cp - OFF + j;
+      in.phi[j] = GRAV ? load_phi(a.phi, (long long)base, 1, c, nx, g.bc[0]) : T(0);
+      if (NU) in.w[j] = width_at(a.wid[0], c, nx, g.bc[0]);
+      if (GRAV == 2) {
+        // the kick of the cell this position maps to (a ghost is exactly the
+        // copy of its kicked cell)
+        const int cm = map_cell(c, nx, g.bc[0]);
+        const T isp0 = NU ? inv_span(width_at(a.wid[0], cm - 1, nx, g.bc[0]), width_at(a.wid[0], cm, nx, g.bc[0]),
+                                     width_at(a.wid[0], cm + 1, nx, g.bc[0]))
+                          : k.inv2h;
+        in.gh[j] = k.half_dt * (load_phi(a.phi, (long long)base, 1, cm + 1, nx, g.bc[0]) -
+                                load_phi(a.phi, (long long)base, 1, cm - 1, nx, g.bc[0])) * isp0;
+      } else {
+        in.gh[j] = T(0);
+      }
+    }
     if (NU) {
-#pragma unroll
-      for (int j = 0; j < 5; ++j) in.w[j] = width_at(a.wid[0], cpos - 4 + j, nx, g.bc[0]);
-      in.wy = wy;
-      in.wz = wz;
+      in.wy = width_at(a.wid[1], y, ny, g.bc[1]);
+      in.wz = width_at(a.wid[2], z, nz, g.bc[2]);
     }
-    if (GRAV == 2) {
-      // the kick of the cell this position maps to (a ghost is exactly the
-      // copy of its kicked cell)
-      const int cm = map_cell(cpos, nx, g.bc[0]);
-      const T isp0 = NU ? inv_span(width_at(a.wid[0], cm - 1, nx, g.bc[0]), width_at(a.wid[0], cm, nx, g.bc[0]),
-                                   width_at(a.wid[0], cm + 1, nx, g.bc[0]))
-                        : k.inv2h;
-      in.gh = k.half_dt * (load_phi(a.phi, (long long)base, 1, cm + 1, nx, g.bc[0]) -
-                           load_phi(a.phi, (long long)base, 1, cm - 1, nx, g.bc[0])) * isp0;
-    } else {
-      in.gh = T(0);
-    }
-    in.o3 = (base + (unsigned)map_cell_near(cpos - 3, nx, g.bc[0])) * z4;
-#pragma unroll
-    for (int i = 0; i < 5; ++i) in.u3[i] = ld(a.u[i], in.o3);
-    rc.advance(L, rows, ny, st1, up, STEP);
     return in;
   };
-  auto compute = [&](const In& in, const FluidHist<T, HSE>& hi, FluidHist<T, HSE>& ho) {
-    T un[5];
-    const FluidNU<T> nu = NU ? fluid_nu(in.w, k.dt) : FluidNU<T>{};
-    fluid_position<T, D, GRAV, HSE, LIM, LaneShift, true, NU>(in.u, in.bc, in.phi, in.gh, in.u3, k, nu, hi, ho, un);
-    const bool out = in.valid && in.co >= 0 && in.co < nx;
-    if (out) {
+  auto compute = [&](const In& in) {
+    T bxr[K], un[K][5], bc[K][3];
+    from_right(in.bx, bxr);
+    FieldQ<T> f[K];
 #pragma unroll
-      for (int i = 0; i < 5; ++i) st(a.uo[i], in.o3, un[i]);
+    for (int j = 0; j < K; ++j) {
+      bc[j][0] = T(0.5) * (in.bx[j] + bxr[j]);
+      bc[j][1] = T(0.5) * (in.by[j][0] + in.by[j][1]);
+      bc[j][2] = T(0.5) * (in.bz[j][0] + in.bz[j][1]);
+      f[j] = field_quantities<T>(bc[j]);
+    }
+    CellNU<T> nu[K]{};
+    if (NU) {
+      T wl[K], wr[K];
+      from_left(in.w, wl);
+      from_right(in.w, wr);
+#pragma unroll
+      for (int j = 0; j < K; ++j) nu[j] = cell_nu(wl[j], in.w[j], wr[j], k.dt);
+    }
+    fluid_window<T, GRAV, HSE, LIM, NU, K>(in.u, f, in.phi, in.gh, nu, k, un);
+    // OFF is a multiple of K, so a row's cell 0 is the first of its lane, and
+    // only the last lane of a row can hold a single cell of it
+    const bool out[K] = {(unsigned)in.c0 < (unsigned)nx, in.c0 >= 0 && in.c0 + 1 < nx};
+    if (out[1]) {
+#pragma unroll
+      for (int i = 0; i < 5; ++i) st2(a.uo[i], in.o, un[0][i], un[1][i]);
+    } else if (out[0]) {
+#pragma unroll
+      for (int i = 0; i < 5; ++i) st(a.uo[i], in.o, un[0][i]);
     }
     if (CFL) {
-      // the cell-centred field of the output cell c-3 is the one position
-      // c-3 loaded, three lanes down (the same row for every output lane)
-      T b3[3];
 #pragma unroll
-      for (int j = 0; j < 3; ++j) b3[j] = lane_shr(lane_shr(lane_shr(in.bc.v[j])));
-      int cell_bad = 0;
-      T sp[3];
-      cell_cfl_speeds<T>(un, b3, a.gamma, g, sp, cell_bad);
-      if (out) {
-        if (NU) {
-          cnu = fmax(cnu, cfl_of_cell(sp, (double)in.w[1], (double)in.wy, (double)in.wz, g));
-        } else {
+      for (int j = 0; j < K; ++j) {
+        int cell_bad = 0;
+        T sp[3];
+        cell_cfl_speeds<T>(un[j], bc[j], a.gamma, g, sp, cell_bad);
+        if (out[j]) {
+          if (NU) {
+            cnu = fmax(cnu, cfl_of_cell(sp, (double)in.w[j], (double)in.wy, (double)in.wz, g));
+          } else {
 #pragma unroll
-          for (int dd = 0; dd < 3; ++dd) smax[dd] = fmax(smax[dd], sp[dd]);
+            for (int dd = 0; dd < 3; ++dd) smax[dd] = fmax(smax[dd], sp[dd]);
+          }
+          bad |= cell_bad;
         }
-        bad |= cell_bad;
       }
     }
   };
-  In cur = load(0);
-  for (int it = 0; it < nit; it += 2) {
-    const In nxt = load(it + 1);
-    compute(cur, hA, hB);
-    cur = load(it + 2);
-    compute(nxt, hB, hA);
-  }
+  const int nwin = (npos + STEP - 1) / STEP;
+  for (int win = rs.turn; win < nwin; win += rs.waves) compute(load(win));
   if (CFL) publish_cfl(NU ? cnu : cfl_of(smax, g), bad, const_cast<Scalars*>(a.sc), FL.wl, &sh);
 }
 
