@@ -204,9 +204,8 @@ enum {
  * kinds, each with the plain or the XCD-grouped block order (consecutive
  * blocks of a launch on one XCD, sharing its L2), and with an alternative
  * layout: for the y/z kinds the four waves of a block on four consecutive
- * rows instead of contiguous pencils, for the x field kind two stream
- * positions per lane instead of one, for the check kind the CFL speed of a
- * step's new state reduced by the check kernel after the last x sweep
+ * rows instead of contiguous pencils, for the x field kind none (the value is
+ * accepted and has no effect), for the check kind the CFL speed of a step's new state reduced by the check kernel after the last x sweep
  * instead of inside it (the same value either way).  The x fluid kind has
  * an alternative layout too, the strided policy with the lanes along y and
  * the shape as its segment length; the autotuner does not try it (set it

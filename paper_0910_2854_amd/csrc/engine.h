@@ -63,9 +63,9 @@ struct EngineConfig {
 struct Tuning {
   int target[K_NUM];
   int remap[K_NUM];   // XCD-aware block order per kind (0/1)
-  int groups[K_NUM];  // y/z kinds: waves of a block on consecutive rows; x field kind: two
-                      // stream positions per lane; check kind: the step's CFL reduction in
-                      // the check kernel instead of the last x sweep (0/1)
+  int groups[K_NUM];  // y/z kinds: waves of a block on consecutive rows; check kind: the
+                      // step's CFL reduction in the check kernel instead of the last x
+                      // sweep; x fluid kind: the strided layout (0/1)
 };
 Tuning default_tuning();
 

@@ -26,7 +26,7 @@ constexpr long long kAlign = 64;  // box offsets in elements (256 B in FP32)
 Tuning default_tuning() {
   Tuning t;
   t.target[K_FLUID_X] = 1536;
-  t.target[K_FIELD_X] = 768;
+  t.target[K_FIELD_X] = 384;
   t.target[K_FLUID_Y] = t.target[K_FLUID_Z] = 64;
   t.target[K_FIELD_Y] = t.target[K_FIELD_Z] = 64;
   t.target[K_CHECK] = 16;
@@ -1158,9 +1158,8 @@ int Engine::autotune(int reps, int* chosen) {
     const bool lanes = kind == K_FLUID_X || kind == K_FIELD_X;
     const int* cand = lanes ? lanes_c : seg_c;
     const int ncand = lanes ? (int)(sizeof lanes_c / sizeof(int)) : (int)(sizeof seg_c / sizeof(int));
-    // second knob: the pencil order of the y/z kinds, two positions per lane
-    // for the x field sweep
-    const int nord = (lanes && kind != K_FIELD_X) ? 1 : 2;
+    // second knob: the pencil order of the y/z kinds
+    const int nord = lanes ? 1 : 2;
     const int op = kind >= K_FIELD_X ? 1 : 0;
     const int d = op ? kind - K_FIELD_X : kind - K_FLUID_X;
     float best = 1e30f;

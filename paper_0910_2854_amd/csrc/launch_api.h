@@ -17,7 +17,6 @@ struct SweepSel {
   int gravity = 0;         // 0 none, 1 unsplit, 2 split
   int hse = 0;
   bool nonuniform = false; // per-cell widths (the launch carries them)
-  bool lanes2 = false;     // x field sweep: two stream positions per lane (uniform meshes)
   bool x_strided = false;  // x fluid sweep without the CFL reduction: the strided policy, lanes along y
   hipStream_t stream = nullptr;
 };

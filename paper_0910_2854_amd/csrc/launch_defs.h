@@ -61,10 +61,7 @@ void field_kernel(const SweepSel& s, const FieldLaunch<T>& L) {
   if (L.wl.nwaves == 0) return;
   const dim3 grid(grid_for((long long)L.wl.nwaves * 64));
   if constexpr (D == 0) {
-    if (s.lanes2 && !NU)  // two positions per lane: uniform meshes only
-      hipLaunchKernelGGL((field_lanes2_kernel<T, LIM>), grid, dim3(kBlock), 0, s.stream, L);
-    else
-      hipLaunchKernelGGL((field_lanes_kernel<T, LIM, NU>), grid, dim3(kBlock), 0, s.stream, L);
+    hipLaunchKernelGGL((field_lanes_kernel<T, LIM, NU>), grid, dim3(kBlock), 0, s.stream, L);
   } else {
     hipLaunchKernelGGL((field_strided_kernel<T, D, LIM, NU>), grid, dim3(kBlock), 0, s.stream, L);
   }
@@ -86,7 +83,6 @@ inline SweepSel Engine::sweep_sel() const {
   s.gravity = cfg.gravity;
   s.hse = cfg.hse;
   s.nonuniform = nonuniform;
-  s.lanes2 = tuning.groups[K_FIELD_X] != 0;
   s.x_strided = tuning.groups[K_FLUID_X] != 0;
   s.stream = cfg.stream;
   return s;

@@ -98,18 +98,13 @@ __device__ __forceinline__ void st(T* p, unsigned off_bytes, T v) {
 // earlier, read from the history hin; the history for the next position is
 // written to hout.  The kernels alternate two history sets (hin/hout swap
 // every position), so no register is copied to move the window.
-struct StridedHist {
-  template <typename V>
-  __device__ __forceinline__ static V prev(const V& cur, const V& hin, V& hout) {
-    hout = cur;
-    return hin;
-  }
-};
+template <typename V>
+__device__ __forceinline__ V prev(const V& cur, const V& hin, V& hout) {
+  hout = cur;
+  return hin;
+}
 
-// Lanes policy without a carry: lane i takes lane i-1 by one DPP shift and
-// lane 0 takes zero.  The caller makes the wave's first lanes a halo that
-// recomputes the positions the previous iteration ended on, so nothing has
-// to cross from one iteration to the next and no history is kept.
+// Lane shifts: lane i takes lane i - 1, lane 0 zero (one DPP move a dword).
 __device__ __forceinline__ float lane_shr(float cur) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(cur), 0x138, 0xf, 0xf, true));
 }
@@ -119,9 +114,6 @@ __device__ __forceinline__ double lane_shr(double cur) {
   const int hi = __builtin_amdgcn_mov_dpp((int)(cb >> 32), 0x138, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-
-template <typename T>
-__device__ __forceinline__ FieldQ<T> lane_shr(const FieldQ<T>& f);
 
 // lane i takes lane i + 1, lane 63 zero
 __device__ __forceinline__ float lane_shl(float cur) {
@@ -134,112 +126,9 @@ __device__ __forceinline__ double lane_shl(double cur) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-struct LaneShift {
-  template <typename T>
-  __device__ __forceinline__ static T prev(const T& cur, const T&, T&) {
-    return lane_shr(cur);
-  }
-  template <typename T>
-  __device__ __forceinline__ static FieldQ<T> prev(const FieldQ<T>& cur, const FieldQ<T>&, FieldQ<T>&) {
-    return lane_shr(cur);
-  }
-  template <typename T, bool HSE>
-  __device__ __forceinline__ static CellQ<T, HSE> prev(const CellQ<T, HSE>& cur, const CellQ<T, HSE>&,
-                                                       CellQ<T, HSE>&) {
-    CellQ<T, HSE> o;
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      o.u[k] = lane_shr(cur.u[k]);
-      o.F[k] = lane_shr(cur.F[k]);
-    }
-    o.d = lane_shr(cur.d);
-    if (HSE) {
-      o.vd = lane_shr(cur.vd);
-      o.cF = lane_shr(cur.cF);
-      o.cS = lane_shr(cur.cS);
-      o.xiE = lane_shr(cur.xiE);
-    } else {
-      o.vd = o.cF = o.cS = o.xiE = T(0);
-    }
-    return o;
-  }
-};
-
-// (the lane shift of a cell's field)
-template <typename T>
-__device__ __forceinline__ FieldQ<T> lane_shr(const FieldQ<T>& f) {
-  FieldQ<T> o;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) o.b[k] = lane_shr(f.b[k]);
-  o.b2 = lane_shr(f.b2);
-  return o;
-}
-
 template <typename T, int N>
 struct Vec {
   T v[N];
-};
-template <typename H, typename T, int N>
-__device__ __forceinline__ Vec<T, N> prev_vec(const Vec<T, N>& cur, const Vec<T, N>& hin, Vec<T, N>& hout) {
-  Vec<T, N> o;
-#pragma unroll
-  for (int k = 0; k < N; ++k) o.v[k] = H::prev(cur.v[k], hin.v[k], hout.v[k]);
-  return o;
-}
-
-// ------------------------------------------------------------ lanes cursor
-// Position of one lane in the stream of whole rows a wave walks (lanes
-// policy): row rr of the wave's rows and position cp in [0, L) of that row,
-// with the row's transverse indices (y, z) and its element offset base =
-// y st1 + z st2.  Advancing by one iteration moves `step` positions (64, or
-// 128 with two positions per lane); the row indices and the offset are
-// stepped, never divided or multiplied, and stay on the wave's last row past
-// its end (those lanes' positions are beyond the stream and write nothing).
-// nrow is the number of rows per plane (cells, or face rows of the field
-// sweep).
-struct RowCursor {
-  int cp, rr, y, z;
-  unsigned base;
-  bool moved;
-  // r0 (the wave's first row) is uniform across the wave: one division per
-  // wave, then the lane's own rows are stepped.  up: the element offset from
-  // the last row of a plane to the first row of the next one, st2 - (nrow - 1) st1.
-  __device__ void init(int pos, int L, int r0, int rows, int nrow, unsigned st1, unsigned st2, unsigned up) {
-    const int z0 = r0 / nrow, y0 = r0 - z0 * nrow;
-    cp = pos;
-    rr = 0;
-    y = y0;
-    z = z0;
-    base = (unsigned)y0 * st1 + (unsigned)z0 * st2;
-    moved = true;
-    while (cp >= L && rr < rows - 1) {
-      cp -= L;
-      ++rr;
-      if (++y == nrow) {
-        y = 0;
-        ++z;
-        base += up;
-      } else {
-        base += st1;
-      }
-    }
-  }
-  __device__ void advance(int L, int rows, int nrow, unsigned st1, unsigned up, int step = 64) {
-    cp += step;
-    moved = false;
-    while (cp >= L && rr < rows - 1) {
-      cp -= L;
-      ++rr;
-      if (++y == nrow) {
-        y = 0;
-        ++z;
-        base += up;
-      } else {
-        base += st1;
-      }
-      moved = true;
-    }
-  }
 };
 
 // Branch-free maps for indices the stencils reach from a box row, i in
@@ -406,16 +295,15 @@ struct FluidHist {
 // cell), before its first use; the output cell c-3 after its corrector, by
 // the same factor formed from the history of phi.
 // NU: irregular mesh, with the per-position factors in nu (uniform: k).
-template <typename T, int D, int GRAV, bool HSE, int LIM, typename H, bool RELOAD_U3, bool NU = false>
-__device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& bcc, T phc, T gh_c,
-                                               const T* u3_loaded, const FluidConsts<T>& k, const FluidNU<T>& nu,
+template <typename T, int D, int GRAV, bool HSE, int LIM, bool NU>
+__device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& bcc, T phc, T gh_c, const FluidConsts<T>& k, const FluidNU<T>& nu,
                                                const FluidHist<T, HSE>& hi, FluidHist<T, HSE>& ho, T* un) {
   T phm1 = T(0), phm2 = T(0), phm3 = T(0), phm4 = T(0);
   if (GRAV != 0 || HSE) {
-    phm1 = H::prev(phc, hi.ph1, ho.ph1);
-    phm2 = H::prev(phm1, hi.ph2, ho.ph2);
-    phm3 = H::prev(phm2, hi.ph3, ho.ph3);
-    phm4 = H::prev(phm3, hi.ph4, ho.ph4);
+    phm1 = prev(phc, hi.ph1, ho.ph1);
+    phm2 = prev(phm1, hi.ph2, ho.ph2);
+    phm3 = prev(phm2, hi.ph3, ho.ph3);
+    phm4 = prev(phm3, hi.ph4, ho.ph4);
   }
   T uc[5];
 #pragma unroll
@@ -425,8 +313,8 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   const FieldQ<T> f0 = field_quantities<T>(bcc.v);
   CellQ<T, HSE> q0;
   cell_quantities<T, D, HSE>(uc, f0, k.gamma, q0);
-  const CellQ<T, HSE> q0m = H::prev(q0, hi.q0, ho.q0);
-  const FieldQ<T> f0m = H::prev(f0, hi.f, ho.f);
+  const CellQ<T, HSE> q0m = prev(q0, hi.q0, ho.q0);
+  const FieldQ<T> f0m = prev(f0, hi.f, ho.f);
   // predictor flux at interface c-1/2 (Eq. 24, dissipation scaled by alpha).
   // All fluxes and flux differences are kept doubled and the step factors
   // halved: the scalings by 1/2 of Eqs. (24)-(34) are exact, so leaving them
@@ -436,7 +324,7 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   dissipation<T, HSE>(q0m, q0, phm1, phc, Q);
 #pragma unroll
   for (int i = 0; i < 5; ++i) F1.v[i] = (q0m.F[i] + q0.F[i]) - k.alpha * Q[i];
-  const Vec<T, 5> F1m = prev_vec<H>(F1, hi.F1, ho.F1);
+  const Vec<T, 5> F1m = prev(F1, hi.F1, ho.F1);
   // predictor half step of cell c-1 (Eq. 41; Eq. 69 on an irregular mesh)
   T up[5];
   const T khalf = NU ? nu.kh1 : k.kh2;
@@ -452,7 +340,7 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   // cell quantities of the half-step state of c-1 (field unchanged), and of c-2
   CellQ<T, HSE> q1;
   cell_quantities<T, D, HSE>(up, f0m, k.gamma, q1);
-  const CellQ<T, HSE> q1m = H::prev(q1, hi.q1, ho.q1);
+  const CellQ<T, HSE> q1m = prev(q1, hi.q1, ho.q1);
   // relaxed flux differences across interface c-3/2 (between c-2 and c-1)
   T Qc[5];
   Vec<T, 5> ap, am, bs;
@@ -464,12 +352,12 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
     am.v[i] = dF - Qc[i];
     bs.v[i] = (q1m.F[i] + q1.F[i]) - Qc[i];
   }
-  const Vec<T, 5> apm = prev_vec<H>(ap, hi.ap, ho.ap);
-  const Vec<T, 5> amm = prev_vec<H>(am, hi.am, ho.am);
-  const Vec<T, 5> bsm = prev_vec<H>(bs, hi.bs, ho.bs);
+  const Vec<T, 5> apm = prev(ap, hi.ap, ho.ap);
+  const Vec<T, 5> amm = prev(am, hi.am, ho.am);
+  const Vec<T, 5> bsm = prev(bs, hi.bs, ho.bs);
   // limited second-order flux at interface c-5/2 (Eq. 34); both limiters
   // taken here belong to cell c-2 (its half-step state decides the switch)
-  const T sup2 = LIM == 2 ? H::prev(q1.sup, hi.sp1, ho.sp1) : T(0);
+  const T sup2 = LIM == 2 ? prev(q1.sup, hi.sp1, ho.sp1) : T(0);
   // (the flux is doubled and so are the differences: half their limited value;
   // irregular mesh: each difference weighted to put cell c-2's slope on its
   // interfaces, which absorbs that half)
@@ -482,7 +370,7 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
 #pragma unroll
     for (int i = 0; i < 5; ++i) Lp.v[i] = limit_scaled<T, LIM>(sup2, nu.wl2 * apm.v[i], nu.wr2 * ap.v[i]);
   }
-  const Vec<T, 5> Lpm = prev_vec<H>(Lp, hi.Lp, ho.Lp);
+  const Vec<T, 5> Lpm = prev(Lp, hi.Lp, ho.Lp);
   if (!NU) {
 #pragma unroll
     for (int i = 0; i < 5; ++i) F2.v[i] = bsm.v[i] + unit * (Lpm.v[i] - limit_scaled<T, LIM>(sup2, amm.v[i], am.v[i]));
@@ -491,31 +379,23 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
     for (int i = 0; i < 5; ++i)
       F2.v[i] = bsm.v[i] + unit * (Lpm.v[i] - limit_scaled<T, LIM>(sup2, nu.wl2 * amm.v[i], nu.wr2 * am.v[i]));
   }
-  const Vec<T, 5> F2m = prev_vec<H>(F2, hi.F2, ho.F2);
+  const Vec<T, 5> F2m = prev(F2, hi.F2, ho.F2);
   // state of cell c-3 before the sweep
-  T u3[5];
   // kick of c-3 (split gravity): phi of c-2 and c-4
   const T gh3 = GRAV == 2 ? k.half_dt * (phm2 - phm4) * (NU ? nu.isp3 : k.inv2h) : T(0);
-  if (RELOAD_U3) {
+  Vec<T, 5> um1;
 #pragma unroll
-    for (int i = 0; i < 5; ++i) u3[i] = u3_loaded[i];
-    if (GRAV == 2) gravity_kick<T, D>(u3, gh3);  // bitwise the kick it had on entry
-  } else {
-    Vec<T, 5> um1;
-#pragma unroll
-    for (int i = 0; i < 5; ++i) um1.v[i] = q0m.u[i];
-    const Vec<T, 5> um2 = prev_vec<H>(um1, hi.ua, ho.ua);
-    const Vec<T, 5> um3 = prev_vec<H>(um2, hi.ub, ho.ub);
-#pragma unroll
-    for (int i = 0; i < 5; ++i) u3[i] = um3.v[i];
-  }
+  for (int i = 0; i < 5; ++i) um1.v[i] = q0m.u[i];
+  const Vec<T, 5> um2 = prev(um1, hi.ua, ho.ua);
+  const Vec<T, 5> um3 = prev(um2, hi.ub, ho.ub);
+  const T* u3 = um3.v;
   // corrector of cell c-3 (Eq. 43)
   const T kfull = NU ? nu.kf3 : k.kf2;
   if (GRAV == 1) {
-    const T rpm2 = H::prev(up[RHO], hi.rp1, ho.rp1);   // rho' of c-2
-    const T rpm3 = H::prev(rpm2, hi.rp2, ho.rp2);      // rho' of c-3
-    const T mpm2 = H::prev(up[MX + D], hi.mp1, ho.mp1);
-    const T mpm3 = H::prev(mpm2, hi.mp2, ho.mp2);
+    const T rpm2 = prev(up[RHO], hi.rp1, ho.rp1);   // rho' of c-2
+    const T rpm3 = prev(rpm2, hi.rp2, ho.rp2);      // rho' of c-3
+    const T mpm2 = prev(up[MX + D], hi.mp1, ho.mp1);
+    const T mpm3 = prev(mpm2, hi.mp2, ho.mp2);
     T S[5];
     gravity_source<T, D>(rpm3, mpm3, phm2 - phm4, NU ? nu.isp3 : k.inv2h, S);
 #pragma unroll
@@ -659,8 +539,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && GRAV == 0 && LIM != 2 && !NU
     const int s = s0 - 3 + it;
     T un[5];
     const FluidNU<T> nu = NU ? fluid_nu(in.w, k.dt) : FluidNU<T>{};
-    fluid_position<T, D, GRAV, HSE, LIM, StridedHist, false, NU>(in.u, in.bc, in.phi, in.gh, nullptr, k, nu, hi, ho,
-                                                                  un);
+    fluid_position<T, D, GRAV, HSE, LIM, NU>(in.u, in.bc, in.phi, in.gh, k, nu, hi, ho, un);
     if (it >= 6 && s - 3 < s1 && active) {
       const long long o = (long long)(s - 3) * stD;
 #pragma unroll
@@ -1251,8 +1130,8 @@ __device__ __forceinline__ FieldArgs<T> field_view(const FieldLaunch<T>& L, cons
 
 template <typename T>
 struct RowHist {
-  T w1, w2, b1, b2, b3, b4, f2, p1, vb1, vb2, vb3, fp3, fp4, fp5, P2;
-  __device__ void zero() { w1 = w2 = b1 = b2 = b3 = b4 = f2 = p1 = vb1 = vb2 = vb3 = fp3 = fp4 = fp5 = P2 = T(0); }
+  T w1, w2, b1, b2, b3, b4, f2, p1, vb1, vb2, vb3, fp3, fp4, d34, lim4, P2;
+  __device__ void zero() { w1 = w2 = b1 = b2 = b3 = b4 = f2 = p1 = vb1 = vb2 = vb3 = fp3 = fp4 = d34 = lim4 = P2 = T(0); }
 };
 
 // One position of one face row of b_t along d: Eq. (65) face velocity w0 at
@@ -1260,57 +1139,49 @@ struct RowHist {
 // first-order upwind predictor flux, second-order limited upwind corrector
 // flux (end of Sect. 2.4), Eq. (63).  Gives the edge flux at d-face c-3 (the
 // interface between c-4 and c-3) and, for NEED_BN, the new b_t of cell c-4.
-// Irregular mesh (Sect. 2.5): the weights that put the limited slopes of cells
-// c-4 (upwind side "up") and c-3 ("dn") on the interface between them, as in
-// the fluid corrector; k_half and k_full are then those of cells c-2 and c-4.
+// Irregular mesh (Sect. 2.5): the weights that put the limited slope of cell
+// c-3 on its interfaces, as in the fluid corrector; k_half and k_full are then those of cells c-2 and c-4.
 template <typename T>
 struct FieldW {
-  T wl4, wr4, wl3, wr3;
+  T wl3, wr3;
 };
 
-template <typename T, int LIM, typename H, bool NEED_BN, bool RELOAD_B4, bool NU = false>
-__device__ __forceinline__ T row_position(T w0, T bb, T b4_loaded, T k_half, T k_full, const FieldW<T>& fw,
+template <typename T, int LIM, bool NEED_BN, bool NU>
+__device__ __forceinline__ T row_position(T w0, T bb, T k_half, T k_full, const FieldW<T>& fw,
                                           const RowHist<T>& hi, RowHist<T>& ho, T& bn) {
-  const T w1 = H::prev(w0, hi.w1, ho.w1);
-  const T w2 = H::prev(w1, hi.w2, ho.w2);
+  const T w1 = prev(w0, hi.w1, ho.w1);
+  const T w2 = prev(w1, hi.w2, ho.w2);
   // outer neighbours first: an odd face velocity gives exact negatives here
   // and V = 0 exactly, which the <= 0 branch of Eq. (67) decides
   const T vbc = T(0.25) * ((w2 + w0) + T(2) * w1);   // v-bar of c-1
-  const T b1 = H::prev(bb, hi.b1, ho.b1);                   // b of c-1
+  const T b1 = prev(bb, hi.b1, ho.b1);                   // b of c-1
   const T fc = vbc * b1;                            // f of c-1
-  const T vb1 = H::prev(vbc, hi.vb1, ho.vb1);                // v-bar of c-2
-  const T V = T(0.5) * (vb1 + vbc);                 // interface c-3/2
-  const T f2 = H::prev(fc, hi.f2, ho.f2);                   // f of c-2
+  const T vb1 = prev(vbc, hi.vb1, ho.vb1);                // v-bar of c-2
+  const T V = vb1 + vbc;                            // twice that of interface c-3/2
+  const T f2 = prev(fc, hi.f2, ho.f2);              // f of c-2
   const T P1 = V > T(0) ? f2 : fc;                  // Phi1 at c-3/2
-  const T p1 = H::prev(P1, hi.p1, ho.p1);                   // Phi1 at c-5/2
-  const T b2 = H::prev(b1, hi.b2, ho.b2);                   // b of c-2
+  const T p1 = prev(P1, hi.p1, ho.p1);              // Phi1 at c-5/2
+  const T b2 = prev(b1, hi.b2, ho.b2);              // b of c-2
   const T bp = b2 - k_half * (P1 - p1);             // b' of c-2
   const T fp2 = vb1 * bp;                           // f' of c-2
-  const T vb2 = H::prev(vb1, hi.vb2, ho.vb2);                // v-bar of c-3
-  const T vb3 = H::prev(vb2, hi.vb3, ho.vb3);                // v-bar of c-4
-  const T V7 = T(0.5) * (vb3 + vb2);                // interface c-7/2
-  const T fp3 = H::prev(fp2, hi.fp3, ho.fp3);
-  const T fp4 = H::prev(fp3, hi.fp4, ho.fp4);
-  const T fp5 = H::prev(fp4, hi.fp5, ho.fp5);
-  T up, dn;
+  const T vb2 = prev(vb1, hi.vb2, ho.vb2);          // v-bar of c-3
+  const T vb3 = prev(vb2, hi.vb3, ho.vb3);          // v-bar of c-4
+  const T V7 = vb3 + vb2;                           // twice that of interface c-7/2
+  const T fp3 = prev(fp2, hi.fp3, ho.fp3);
+  const T fp4 = prev(fp3, hi.fp4, ho.fp4);
+  // the limited slope of cell c-3; that of c-4 is the one the last position took
+  const T d23 = fp2 - fp3;
+  const T d34 = prev(d23, hi.d34, ho.d34);
+  const T lim3 = NU ? limit_scaled<T, LIM>(T(0), fw.wl3 * d34, fw.wr3 * d23) : limit_scaled<T, LIM>(T(0), d34, d23);
+  const T lim4 = prev(lim3, hi.lim4, ho.lim4);
   constexpr T unit = T(NU ? 1.0 : 0.5) * limit_unit<LIM>();
-  if (!NU) {
-    up = fp4 + unit * limit_scaled<T, LIM>(T(0), fp4 - fp5, fp3 - fp4);
-    dn = fp3 - unit * limit_scaled<T, LIM>(T(0), fp3 - fp4, fp2 - fp3);
-  } else {
-    up = fp4 + unit * limit_scaled<T, LIM>(T(0), fw.wl4 * (fp4 - fp5), fw.wr4 * (fp3 - fp4));
-    dn = fp3 - unit * limit_scaled<T, LIM>(T(0), fw.wl3 * (fp3 - fp4), fw.wr3 * (fp2 - fp3));
-  }
+  const T up = fp4 + unit * lim4;
+  const T dn = fp3 - unit * lim3;
   const T P2c = V7 > T(0) ? up : dn;                // Phi2 at c-7/2
   if (NEED_BN) {
-    const T P2 = H::prev(P2c, hi.P2, ho.P2);                // Phi2 at c-9/2
-    T b4;
-    if (RELOAD_B4) {
-      b4 = b4_loaded;
-    } else {
-      const T b3 = H::prev(b2, hi.b3, ho.b3);
-      b4 = H::prev(b3, hi.b4, ho.b4);
-    }
+    const T P2 = prev(P2c, hi.P2, ho.P2);                // Phi2 at c-9/2
+    const T b3 = prev(b2, hi.b3, ho.b3);
+    const T b4 = prev(b3, hi.b4, ho.b4);
     bn = b4 - k_full * (P2c - P2);
   }
   return P2c;
@@ -1358,32 +1229,6 @@ __device__ __forceinline__ FieldOffsets field_offsets(const Geo& g, int c1, int 
   return o;
 }
 
-// The same offsets for the x sweep's rows (t1 = y, t2 = z), in bytes, with
-// the cheap maps (the neighbours are within one period); base is the face
-// row's element offset y st1 + z st2, which the lanes cursor keeps.
-// All in unsigned arithmetic: a difference that is negative wraps, and adding
-// it to an offset wraps back (every offset is below 2^32 bytes).
-struct RowOffsets {
-  unsigned base, ownc;             // face row (c1, c2) and its mapped own cell
-  unsigned c1m, c1p, c2m, c2p, f1p, f2p;
-};
-
-template <typename T>
-__device__ __forceinline__ void row_offsets(const Geo& g, int c1, int c2, unsigned base, RowOffsets& r) {
-  constexpr unsigned z = sizeof(T);
-  const unsigned st1 = (unsigned)g.st[1], st2 = (unsigned)g.st[2];
-  const int n1 = g.n[1], n2 = g.n[2], b1 = g.bc[1], b2 = g.bc[2];
-  const int m1 = map_cell_near(c1, n1, b1), m2 = map_cell_near(c2, n2, b2);
-  r.base = base * z;
-  r.ownc = (base + (unsigned)(m1 - c1) * st1 + (unsigned)(m2 - c2) * st2) * z;
-  r.c1m = (unsigned)(map_cell_near(c1 - 1, n1, b1) - m1) * st1 * z;
-  r.c1p = (unsigned)(map_cell_near(c1 + 1, n1, b1) - m1) * st1 * z;
-  r.c2m = (unsigned)(map_cell_near(c2 - 1, n2, b2) - m2) * st2 * z;
-  r.c2p = (unsigned)(map_cell_near(c2 + 1, n2, b2) - m2) * st2 * z;
-  r.f1p = (unsigned)(map_face_near(c1 + 1, n1, b1) - c1) * st1 * z;
-  r.f2p = (unsigned)(map_face_near(c2 + 1, n2, b2) - c2) * st2 * z;
-}
-
 // Byte offsets of everything one position reads, relative to the arrays'
 // base pointers (which carry the d offset when it is wave-uniform).
 struct FieldLane {
@@ -1413,7 +1258,6 @@ template <typename T>
 struct FieldIn {
   T md[5], rho[5];  // cells (c1, c2), (c1-1, c2), (c1+1, c2), (c1, c2-1), (c1, c2+1)
   T b[4];           // b_t1 at t1-faces c1, c1+1; b_t2 at t2-faces c2, c2+1
-  T b4a, b4c;       // b_t1, b_t2 of cell c-4 (lanes policy)
   T bd3;            // b_d at d-face c-3, which the constraint update of this position rewrites
 };
 
@@ -1431,7 +1275,7 @@ __device__ __forceinline__ FieldIn<T> field_load(const T* md, const T* rho, cons
   in.b[1] = ld(bt0, l.fB);
   in.b[2] = ld(bt1, l.fC);
   in.b[3] = ld(bt1, l.fD);
-  in.b4a = in.b4c = in.bd3 = T(0);
+  in.bd3 = T(0);
   return in;
 }
 
@@ -1471,8 +1315,6 @@ __device__ __forceinline__ FieldPosNU<T> field_pos_nu(const T* w, T dt) {
   FieldPosNU<T> f;
   f.kh = T(0.5) * dt * rcp(w[3]);
   f.kf = dt * rcp(w[1]);
-  f.w.wl4 = w[1] * rcp(w[0] + w[1]);
-  f.w.wr4 = w[1] * rcp(w[1] + w[2]);
   f.w.wl3 = w[2] * rcp(w[1] + w[2]);
   f.w.wr3 = w[2] * rcp(w[2] + w[3]);
   return f;
@@ -1488,7 +1330,7 @@ __device__ __forceinline__ T face_interp(T alo, T vlo, T ahi, T vhi) {
 }
 
 // All four face rows at one position.
-template <typename T, int LIM, typename H, bool RELOAD_B4, bool NU = false>
+template <typename T, int LIM, bool NU>
 __device__ __forceinline__ void field_compute(const FieldIn<T>& in, const FieldConsts<T>& k, const FieldRowNU<T>& rn,
                                               const FieldPosNU<T>& pn, const RowHist<T>* hi, RowHist<T>* ho, T& bn1,
                                               T& bn2, T& dbd) {
@@ -1512,10 +1354,10 @@ __device__ __forceinline__ void field_compute(const FieldIn<T>& in, const FieldC
   }
   const T kh = NU ? pn.kh : k.k_half, kf = NU ? pn.kf : k.k_full;
   T dummy;
-  const T eA = row_position<T, LIM, H, true, RELOAD_B4, NU>(wA, in.b[0], in.b4a, kh, kf, pn.w, hi[0], ho[0], bn1);
-  const T eB = row_position<T, LIM, H, false, false, NU>(wB, in.b[1], T(0), kh, kf, pn.w, hi[1], ho[1], dummy);
-  const T eC = row_position<T, LIM, H, true, RELOAD_B4, NU>(wC, in.b[2], in.b4c, kh, kf, pn.w, hi[2], ho[2], bn2);
-  const T eD = row_position<T, LIM, H, false, false, NU>(wD, in.b[3], T(0), kh, kf, pn.w, hi[3], ho[3], dummy);
+  const T eA = row_position<T, LIM, true, NU>(wA, in.b[0], kh, kf, pn.w, hi[0], ho[0], bn1);
+  const T eB = row_position<T, LIM, false, NU>(wB, in.b[1], kh, kf, pn.w, hi[1], ho[1], dummy);
+  const T eC = row_position<T, LIM, true, NU>(wC, in.b[2], kh, kf, pn.w, hi[2], ho[2], bn2);
+  const T eD = row_position<T, LIM, false, NU>(wD, in.b[3], kh, kf, pn.w, hi[3], ho[3], dummy);
   // Eq. (64), physical signs: d/dt b_d = d_t1 Phi^t1 + d_t2 Phi^t2
   dbd = k.dt * ((eB - eA) * (NU ? rn.ih1 : k.ih1) + (eD - eC) * (NU ? rn.ih2 : k.ih2));
 }
@@ -1591,7 +1433,7 @@ __global__ __launch_bounds__(256) void field_strided_kernel(FieldLaunch<T> FL) {
       for (int j = 0; j < 4; ++j) w[j] = width_at(a.wid[D], s - 5 + j, nD, g.bc[D]);
       pn = field_pos_nu(w, k.dt);
     }
-    field_compute<T, LIM, StridedHist, false, NU>(in, k, rn, pn, hi, ho, bn1, bn2, dbd);
+    field_compute<T, LIM, NU>(in, k, rn, pn, hi, ho, bn1, bn2, dbd);
     if (it >= 8 && s - 4 < s1) {
       const long long ob = (long long)(s - 4) * stD;
       if (own1) st(in_sgpr(a.bto[0] + ob), l.fA, bn1);
@@ -1617,398 +1459,217 @@ __global__ __launch_bounds__(256) void field_strided_kernel(FieldLaunch<T> FL) {
   }
 }
 
-// The x field sweep with one face row (y, z) per wave, on a uniform mesh.
-// The row, its base and its neighbour offsets are wave-uniform, so every
-// load and store takes a scalar base and the lane's x offset only, and an
-// iteration that lies inside the row (every cell it reaches in [0, n_x))
-// takes the x index unmapped.  Iteration it covers positions
-// it STEP .. it STEP + STEP - 1 of the row (the last one partly), its first
-// HALO lanes recomputing the positions before them as in the general path.
-template <typename T, int LIM>
-__device__ __forceinline__ void field_lanes_row(const FieldArgs<T>& a, const FieldConsts<T>& k, int y, int zc) {
-  const Geo& g = a.g;
-  const int nx = g.n[0];
-  const bool outx = g.bc[0] == 1;
-  const int L = nx + 8;
-  constexpr int HALO = 8, STEP = 64 - HALO;
-  const int lane = threadIdx.x & 63;
-  constexpr unsigned z = sizeof(T);
-  const unsigned st1 = (unsigned)g.st[1], st2 = (unsigned)g.st[2];
-  RowOffsets ro;
-  row_offsets<T>(g, y, zc, (unsigned)y * st1 + (unsigned)zc * st2, ro);
-  const bool own1 = zc < g.n[2], own2 = y < g.n[1];
-  auto at = [](const T* p, unsigned b) {
-    return in_sgpr((const T*)((const char*)p + (unsigned)__builtin_amdgcn_readfirstlane((int)b)));
-  };
-  auto at_out = [](T* p, unsigned b) {
-    return in_sgpr((T*)((char*)p + (unsigned)__builtin_amdgcn_readfirstlane((int)b)));
-  };
-  const unsigned cn[5] = {ro.ownc, ro.ownc + ro.c1m, ro.ownc + ro.c1p, ro.ownc + ro.c2m, ro.ownc + ro.c2p};
-  const T* md[5];
-  const T* rh[5];
+// ------------------------------------------------------------ B_x
+// Lanes policy (D = x), as L_x: two cells of a face row per lane, windows dealt
+// to the waves of a block, every value in the lane of its cell.  256^3: 160 us
+// FP32, 277 us FP64 at one row per wave (one position per lane, streamed a row
+// per wave: 220 and 385 us).  Bound by its loads, ten of fifteen of which are
+// of the neighbouring rows: with sums in place of the scheme it takes 157 us,
+// with the row's own values in place of the neighbours' 109.
+//
+// One face row of b_t: Eq. (65) face velocity w, Eq. (66) smoothing, Eq. (68)
+// interface velocity, Eq. (67) first-order upwind predictor flux, second-order
+// limited upwind corrector flux (end of Sect. 2.4), Eq. (63); the arithmetic of
+// row_position.  e is the edge flux right of each cell; el and bn (the edge
+// flux left of it, the new b_t) only with NEED_BN.
+template <typename T, int LIM, bool NEED_BN, bool NU, int K>
+__device__ __forceinline__ void face_row(const T (&w)[K], const T (&b)[K], const FieldConsts<T>& k,
+                                         const CellNU<T> (&nu)[K], T (&e)[K], T (&bn)[K]) {
+  T l[K], r[K], vb[K], vbr[K], f[K], fr[K], P[K], fp[K], fpr[K], d[K], lim[K];
+  bool right[K];  // the interface velocity is positive: the left cell is upwind
+  from_left(w, l);
+  from_right(w, r);
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    md[i] = at(a.md, cn[i]);
-    rh[i] = at(a.rho, cn[i]);
+  for (int j = 0; j < K; ++j) {
+    // outer neighbours first: an odd face velocity gives exact negatives here
+    // and an interface velocity of exactly 0, which the <= 0 branch decides
+    vb[j] = T(0.25) * ((l[j] + r[j]) + T(2) * w[j]);
+    f[j] = vb[j] * b[j];
   }
-  const T* bA = at(a.bt[0], ro.base);
-  const T* bB = at(a.bt[0], ro.base + ro.f1p);
-  const T* bC = at(a.bt[1], ro.base);
-  const T* bD = at(a.bt[1], ro.base + ro.f2p);
-  const T* bd = at(a.bd, ro.base);
-  T* o1 = at_out(a.bto[0], ro.base);
-  T* o2 = at_out(a.bto[1], ro.base);
-  T* od = at_out(a.bdo, ro.base);
-  RowHist<T> hA[4], hB[4];  // unused by the carry-free policy
-  struct In {
-    FieldIn<T> f;
-    unsigned oc, o4, of;  // x byte offsets of cells c and c-4 and of d-face c-3
-    int cpos;
-    bool valid;
-  };
-  auto load = [&](int it) {
-    In in;
-    const int p0 = it * STEP - HALO;  // position of lane 0 (uniform)
-    const int p = p0 + lane;
-    in.valid = lane >= HALO && p < L;
-    const int c0 = p0 - 4;            // cell index of lane 0
-    if (c0 >= 4 && c0 + 63 < nx) {    // uniform: the whole iteration inside the row
-      in.cpos = p - 4;
-      in.oc = (unsigned)in.cpos * z;
-      in.o4 = in.oc - 4 * z;
-      in.of = in.oc - 3 * z;
-    } else {
-      // clamped as in the general path: every index stays in the box
-      in.cpos = min(max(p, 0), L - 1) - 4;
-      in.oc = (unsigned)map_cell_near(in.cpos, nx, g.bc[0]) * z;
-      in.o4 = (unsigned)map_cell_near(in.cpos - 4, nx, g.bc[0]) * z;
-      in.of = (unsigned)map_face_near(in.cpos - 3, nx, g.bc[0]) * z;
-    }
+  from_right(vb, vbr);
+  from_right(f, fr);
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      in.f.md[i] = ld(md[i], in.oc);
-      in.f.rho[i] = ld(rh[i], in.oc);
-    }
-    in.f.b[0] = ld(bA, in.oc);
-    in.f.b[1] = ld(bB, in.oc);
-    in.f.b[2] = ld(bC, in.oc);
-    in.f.b[3] = ld(bD, in.oc);
-    in.f.b4a = ld(bA, in.o4);
-    in.f.b4c = ld(bC, in.o4);
-    in.f.bd3 = ld(bd, in.of);
-    return in;
-  };
-  auto compute = [&](const In& in, const RowHist<T>* hi, RowHist<T>* ho) {
-    T bn1, bn2, dbd;
-    field_compute<T, LIM, LaneShift, true, false>(in.f, k, FieldRowNU<T>{}, FieldPosNU<T>{}, hi, ho, bn1, bn2, dbd);
-    const int cb = in.cpos - 4;
-    if (in.valid && cb >= 0 && cb < nx) {
-      if (own1) st(o1, in.o4, bn1);
-      if (own2) st(o2, in.o4, bn2);
-    }
-    const int fd = in.cpos - 3;
-    if (in.valid && own1 && own2 && fd >= 0 && (fd < nx || (outx && fd == nx))) st(od, in.of, in.f.bd3 + dbd);
-  };
-  const int nit = (L + STEP - 1) / STEP;
-  In cur = load(0);
-  for (int it = 0; it < nit; it += 2) {
-    const In nxt = load(it + 1);
-    compute(cur, hA, hB);
-    cur = load(it + 2);
-    compute(nxt, hB, hA);
+  for (int j = 0; j < K; ++j) {
+    right[j] = vb[j] + vbr[j] > T(0);
+    P[j] = right[j] ? f[j] : fr[j];
   }
-}
-
-// Lanes policy (d = x): waves stream whole rows (y, z) of faces, each padded
-// by 4 positions before and 4 after.
-template <typename T, int LIM, bool NU>
-__global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
-  constexpr int D = 0;
-  const BoxDesc* d;
-  int lw;
-  if (!work_item<K_FIELD_X>(FL.wl, d, lw)) return;
-  const FieldArgs<T> a = field_view<T, K_FIELD_X>(FL, *d);
-  const Geo& g = a.g;
-  const int nx = g.n[0];
-  const bool outx = g.bc[0] == 1;
-  const int L = nx + 8;
-  const int ry = g.n[1] + g.bc[1];
-  const int rz = g.n[2] + g.bc[2];
-  const long long nrows = (long long)ry * rz;
-  const long long wave = lw;
-  const int lane = threadIdx.x & 63;
-  const long long r0 = wave * a.rows_per_wave;
-  if (r0 >= nrows) return;  // whole wave exits together
-  if (!NU && a.rows_per_wave == 1) {
-    const int r = __builtin_amdgcn_readfirstlane((int)r0);
-    const int zr = r / ry;
-    field_lanes_row<T, LIM>(a, field_consts<T, D>(a), r - zr * ry, zr);
-    return;
+  from_left(P, l);
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const T bp = b[j] - (NU ? nu[j].kh : k.k_half) * (P[j] - l[j]);
+    fp[j] = vb[j] * bp;
   }
-  const int rows = (int)min((long long)a.rows_per_wave, nrows - r0);
-  const int npos = rows * L;
-  // lanes 0..HALO-1 recompute the last positions of the previous iteration:
-  // the new transverse face of lane i depends on lanes i-8 .. i (the
-  // corrector flux and its neighbour, the limited slopes over three
-  // predictor fluxes, the predictor's upwind fluxes and the smoothed face
-  // velocity each reach back), the edge flux of the normal update on lanes
-  // i-7 .. i, so lanes 8..63 are exact
-  constexpr int HALO = 8, STEP = 64 - HALO;
-  const int nit = (npos + STEP - 1) / STEP;
-  const FieldConsts<T> k = field_consts<T, D>(a);
-  RowHist<T> hA[4], hB[4];  // unused by the carry-free policy
-  const unsigned st1 = (unsigned)g.st[1], st2 = (unsigned)g.st[2];  // arrays < 2^32 bytes
-  const unsigned up = st2 - (unsigned)(ry - 1) * st1;
-  RowCursor rc;
-  rc.init(lane - HALO, L, (int)r0, rows, ry, st1, st2, up);  // the halo lanes start before the stream (clamped to its start)
-  RowOffsets ro;
-  bool own1 = false, own2 = false;
-  FieldRowNU<T> rnr{};  // irregular mesh: the factors of the current row
-  struct In {
-    FieldIn<T> f;
-    FieldRowNU<T> rn;
-    T w[4];              // irregular mesh: widths of cells c-5 .. c-2 along x
-    unsigned b4off, fo;  // byte offsets of cell c-4 and d-face c-3 in the row
-    int cpos;
-    bool valid, own1, own2;
-  };
-  constexpr unsigned z = sizeof(T);
-  auto load = [&](int it) {
-    if (rc.moved) {
-      row_offsets<T>(g, rc.y, rc.z, rc.base, ro);  // y, z face rows
-      own1 = rc.z < g.n[2];
-      own2 = rc.y < g.n[1];
-      if (NU) {
-        const int n1 = g.n[1], n2 = g.n[2], b1 = g.bc[1], b2 = g.bc[2], y = rc.y, zc = rc.z;
-        rnr = field_row_nu(width_at(a.wid[1], y - 1, n1, b1), width_at(a.wid[1], y, n1, b1),
-                           width_at(a.wid[1], y + 1, n1, b1), width_at(a.wid[2], zc - 1, n2, b2),
-                           width_at(a.wid[2], zc, n2, b2), width_at(a.wid[2], zc + 1, n2, b2));
-      }
-    }
-    In in;
-    in.valid = lane >= HALO && it * STEP + lane - HALO < npos;
-    in.cpos = min(max(rc.cp, 0), L - 1) - 4;  // cell index along x (-4 .. nx+3), clamped as in the fluid sweep
-    in.own1 = own1;
-    in.own2 = own2;
-    const unsigned xb = (unsigned)map_cell_near(in.cpos, nx, g.bc[0]) * z;
-    FieldLane l;
-    l.cc = ro.ownc + xb;
-    l.c1m = l.cc + ro.c1m;
-    l.c1p = l.cc + ro.c1p;
-    l.c2m = l.cc + ro.c2m;
-    l.c2p = l.cc + ro.c2p;
-    l.fA = ro.base + xb;
-    l.fB = l.fA + ro.f1p;
-    l.fC = l.fA;
-    l.fD = l.fA + ro.f2p;
-    in.f = field_load<T>(a.md, a.rho, a.bt[0], a.bt[1], l);
-    in.b4off = ro.base + (unsigned)map_cell_near(in.cpos - 4, nx, g.bc[0]) * z;
-    in.f.b4a = ld(a.bt[0], in.b4off);
-    in.f.b4c = ld(a.bt[1], in.b4off);
-    // d-face c-3 (mapped, in range for every lane); b_d there is rewritten by
-    // this position's constraint update, so it is loaded with the inputs
-    in.fo = ro.base + (unsigned)map_face_near(in.cpos - 3, nx, g.bc[0]) * z;
-    in.f.bd3 = ld(a.bd, in.fo);
-    if (NU) {
-      in.rn = rnr;
+  from_right(fp, fpr);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) in.w[j] = width_at(a.wid[0], in.cpos - 5 + j, nx, g.bc[0]);
-    }
-    rc.advance(L, rows, ry, st1, up, STEP);
-    return in;
-  };
-  auto compute = [&](const In& in, const RowHist<T>* hi, RowHist<T>* ho) {
-    T bn1, bn2, dbd;
-    const FieldPosNU<T> pn = NU ? field_pos_nu(in.w, k.dt) : FieldPosNU<T>{};
-    field_compute<T, LIM, LaneShift, true, NU>(in.f, k, in.rn, pn, hi, ho, bn1, bn2, dbd);
-    const int cb = in.cpos - 4;
-    if (in.valid && cb >= 0 && cb < nx) {
-      if (in.own1) st(a.bto[0], in.b4off, bn1);
-      if (in.own2) st(a.bto[1], in.b4off, bn2);
-    }
-    const int fd = in.cpos - 3;
-    if (in.valid && in.own1 && in.own2 && fd >= 0 && (fd < nx || (outx && fd == nx)))
-      st(a.bdo, in.fo, in.f.bd3 + dbd);
-  };
-  In cur = load(0);
-  for (int it = 0; it < nit; it += 2) {
-    const In nxt = load(it + 1);
-    compute(cur, hA, hB);
-    cur = load(it + 2);
-    compute(nxt, hB, hA);
-  }
-}
-
-// ------------------------------------------------------------ B_x, two positions per lane
-// The x field sweep with lane l holding stream positions 2l and 2l+1 of a
-// 128-position window.  The pipeline runs stage by stage over both: the
-// value one position back is the lane's own register for 2l+1 and the
-// neighbour lane's (one DPP shift) for 2l, so each history value costs one
-// shift per two cells.  As in the one-position kernel, the first lanes of a
-// window recompute the positions the previous one ended on (8 positions, 4
-// lanes), so nothing crosses windows.
-template <typename T>
-__device__ __forceinline__ void prev2(const T (&x)[2], T (&p)[2]) {
-  p[1] = x[0];
-  p[0] = lane_shr(x[1]);
-}
-
-// row_position for both positions of the lane.
-template <typename T, int LIM, bool NEED_BN>
-__device__ __forceinline__ void row_position2(const T (&w0)[2], const T (&bb)[2], const T (&b4)[2], T k_half,
-                                              T k_full, T (&bn)[2], T (&P2c)[2]) {
-  T w1[2], w2[2], vbc[2], b1[2], fc[2], vb1[2], V[2], f2[2], P1[2], p1[2], b2[2], bp[2], fp2[2];
-  T vb2[2], vb3[2], fp3[2], fp4[2], fp5[2];
-  prev2(w0, w1);
-  prev2(w1, w2);
+  for (int j = 0; j < K; ++j) d[j] = fpr[j] - fp[j];
+  from_left(d, l);
 #pragma unroll
-  for (int j = 0; j < 2; ++j) vbc[j] = T(0.25) * ((w2[j] + w0[j]) + T(2) * w1[j]);  // v-bar of c-1 (as above)
-  prev2(bb, b1);
+  for (int j = 0; j < K; ++j)
+    lim[j] = NU ? limit_scaled<T, LIM>(T(0), nu[j].wl * l[j], nu[j].wr * d[j])
+                : limit_scaled<T, LIM>(T(0), l[j], d[j]);
+  from_right(lim, r);
+  constexpr T unit = T(NU ? 1.0 : 0.5) * limit_unit<LIM>();
 #pragma unroll
-  for (int j = 0; j < 2; ++j) fc[j] = vbc[j] * b1[j];
-  prev2(vbc, vb1);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) V[j] = T(0.5) * (vb1[j] + vbc[j]);
-  prev2(fc, f2);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) P1[j] = V[j] > T(0) ? f2[j] : fc[j];
-  prev2(P1, p1);
-  prev2(b1, b2);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    bp[j] = b2[j] - k_half * (P1[j] - p1[j]);
-    fp2[j] = vb1[j] * bp[j];
-  }
-  prev2(vb1, vb2);
-  prev2(vb2, vb3);
-  prev2(fp2, fp3);
-  prev2(fp3, fp4);
-  prev2(fp4, fp5);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const T V7 = T(0.5) * (vb3[j] + vb2[j]);
-    constexpr T unit = T(0.5) * limit_unit<LIM>();
-    const T up = fp4[j] + unit * limit_scaled<T, LIM>(T(0), fp4[j] - fp5[j], fp3[j] - fp4[j]);
-    const T dn = fp3[j] - unit * limit_scaled<T, LIM>(T(0), fp3[j] - fp4[j], fp2[j] - fp3[j]);
-    P2c[j] = V7 > T(0) ? up : dn;
+  for (int j = 0; j < K; ++j) {
+    const T up = fp[j] + unit * lim[j];
+    const T dn = fpr[j] - unit * r[j];
+    e[j] = right[j] ? up : dn;
   }
   if (NEED_BN) {
-    T P2[2];
-    prev2(P2c, P2);
+    from_left(e, l);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) bn[j] = b4[j] - k_full * (P2c[j] - P2[j]);
+    for (int j = 0; j < K; ++j) bn[j] = b[j] - (NU ? nu[j].kf : k.k_full) * (e[j] - l[j]);
   }
 }
 
-template <typename T, int LIM>
-__global__ __launch_bounds__(256) void field_lanes2_kernel(FieldLaunch<T> FL) {
-  constexpr int D = 0;
+template <typename T, int LIM, bool NU>
+__global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
+  constexpr int K = 2;
+  // an output depends on 4 cells either side
+  constexpr int H = (4 + K - 1) / K;
+  constexpr int OFF = H * K;               // position of a row's cell 0
+  constexpr int STEP = (64 - 2 * H) * K;   // cells a window outputs
+  constexpr unsigned z4 = sizeof(T);
   const BoxDesc* d;
   int lw;
   if (!work_item<K_FIELD_X>(FL.wl, d, lw)) return;
   const FieldArgs<T> a = field_view<T, K_FIELD_X>(FL, *d);
   const Geo& g = a.g;
-  const int nx = g.n[0];
+  const int nx = g.n[0], n1 = g.n[1], n2 = g.n[2];
   const bool outx = g.bc[0] == 1;
-  const int L = nx + 8;
-  const int ry = g.n[1] + g.bc[1];
-  const int rz = g.n[2] + g.bc[2];
-  const long long nrows = (long long)ry * rz;
+  const int ry = n1 + g.bc[1], rz = n2 + g.bc[2];  // face rows
+  const int nrows = ry * rz;
+  const int rpw = a.rows_per_wave;
+  RowStream rs;
+  rs.init(lw, (nrows + rpw - 1) / rpw, rpw, (nx + 2 * OFF + K - 1) / K * K, ry, nrows);
+  const int npos = rs.rows * rs.L;
   const int lane = threadIdx.x & 63;
-  const long long r0 = (long long)lw * a.rows_per_wave;
-  if (r0 >= nrows) return;  // whole wave exits together
-  const int rows = (int)min((long long)a.rows_per_wave, nrows - r0);
-  const int npos = rows * L;
-  constexpr int HALO = 8, STEP = 128 - HALO;  // positions
-  const int nit = (npos + STEP - 1) / STEP;
-  const FieldConsts<T> k = field_consts<T, D>(a);
-  const unsigned st1 = (unsigned)g.st[1], st2 = (unsigned)g.st[2];  // arrays < 2^32 bytes
-  const unsigned up = st2 - (unsigned)(ry - 1) * st1;
-  RowCursor rc[2];
-  RowOffsets ro[2];
-  bool own1[2] = {false, false}, own2[2] = {false, false};
+  const FieldConsts<T> k = field_consts<T, 0>(a);
+  // byte offsets to the cells and faces beside a row along y and z: inside the
+  // box one row, at its ends the wrap (periodic) or the copy (outflow); all in
+  // unsigned arithmetic, where a negative offset wraps and wraps back
+  const unsigned s1 = (unsigned)g.st[1] * z4, s2 = (unsigned)g.st[2] * z4;
+  const unsigned lo1 = g.bc[1] ? 0u : (unsigned)(n1 - 1) * s1, hi1 = 0u - lo1;
+  const unsigned lo2 = g.bc[2] ? 0u : (unsigned)(n2 - 1) * s2, hi2 = 0u - lo2;
+  for (int win = rs.turn; win * STEP < npos; win += rs.waves) {
+    const int pos = win * STEP + (lane - H) * K;
+    int cp, y, z;
+    // positions before the stream or past it are moved onto it; they output nothing
+    rs.locate(min(max(pos, 0), npos - K), cp, y, z);
+    const int c0 = lane >= H && lane < 64 - H && pos < npos ? cp - OFF : -K;
+    const unsigned row = (unsigned)z * s2 + (unsigned)y * s1;
+    // the row past an outflow axis's last cell has faces only: its cell is the last one
+    const bool end1 = y == n1, end2 = z == n2;
+    const unsigned own = row - (end1 ? s1 : 0u) - (end2 ? s2 : 0u);
+    const unsigned c1m = end1 ? 0u : (y == 0 ? lo1 : 0u - s1);
+    const unsigned c1p = end1 ? 0u : (y == n1 - 1 ? hi1 : s1);
+    const unsigned c2m = end2 ? 0u : (z == 0 ? lo2 : 0u - s2);
+    const unsigned c2p = end2 ? 0u : (z == n2 - 1 ? hi2 : s2);
+    const unsigned f1p = end1 ? 0u : (y == n1 - 1 && !g.bc[1] ? hi1 : s1);
+    const unsigned f2p = end2 ? 0u : (z == n2 - 1 && !g.bc[2] ? hi2 : s2);
+    unsigned x[K], xf[K];  // byte offsets in the row of the cells and of their low x faces
 #pragma unroll
-  for (int j = 0; j < 2; ++j) rc[j].init(2 * lane + j - HALO, L, (int)r0, rows, ry, st1, st2, up);
-  constexpr unsigned z = sizeof(T);
-  struct In {
-    FieldIn<T> f;
-    unsigned b4off, fo;
-    int cpos;
-    bool valid, own1, own2;
-  };
-  auto load1 = [&](int it, int j) {
-    if (rc[j].moved) {
-      row_offsets<T>(g, rc[j].y, rc[j].z, rc[j].base, ro[j]);
-      own1[j] = rc[j].z < g.n[2];
-      own2[j] = rc[j].y < g.n[1];
+    for (int j = 0; j < K; ++j) {
+      x[j] = (unsigned)map_cell_near(cp - OFF + j, nx, g.bc[0]) * z4;
+      xf[j] = (unsigned)map_face_near(cp - OFF + j, nx, g.bc[0]) * z4;
     }
-    In in;
-    in.valid = 2 * lane + j >= HALO && it * STEP + 2 * lane + j - HALO < npos;
-    in.cpos = min(max(rc[j].cp, 0), L - 1) - 4;  // clamped as in the fluid sweep
-    in.own1 = own1[j];
-    in.own2 = own2[j];
-    const unsigned xb = (unsigned)map_cell_near(in.cpos, nx, g.bc[0]) * z;
-    FieldLane l;
-    l.cc = ro[j].ownc + xb;
-    l.c1m = l.cc + ro[j].c1m;
-    l.c1p = l.cc + ro[j].c1p;
-    l.c2m = l.cc + ro[j].c2m;
-    l.c2p = l.cc + ro[j].c2p;
-    l.fA = ro[j].base + xb;
-    l.fB = l.fA + ro[j].f1p;
-    l.fC = l.fA;
-    l.fD = l.fA + ro[j].f2p;
-    in.f = field_load<T>(a.md, a.rho, a.bt[0], a.bt[1], l);
-    in.b4off = ro[j].base + (unsigned)map_cell_near(in.cpos - 4, nx, g.bc[0]) * z;
-    in.f.b4a = ld(a.bt[0], in.b4off);
-    in.f.b4c = ld(a.bt[1], in.b4off);
-    in.fo = ro[j].base + (unsigned)map_face_near(in.cpos - 3, nx, g.bc[0]) * z;
-    in.f.bd3 = ld(a.bd, in.fo);
-    rc[j].advance(L, rows, ry, st1, up, STEP);
-    return in;
-  };
-  auto compute = [&](const In (&in)[2]) {
-    T wA[2], wB[2], wC[2], wD[2], bA[2], bB[2], bC[2], bD[2], b4a[2], b4c[2];
+    const unsigned c[5] = {own, own + c1m, own + c1p, own + c2m, own + c2p};
+    T md[5][K], rho[5][K], b[4][K], bd[K];
+    // a pair is split only where the row's ghosts wrap or are copies
+    if (__all(x[1] == x[0] + z4 && xf[1] == xf[0] + z4)) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+      for (int i = 0; i < 5; ++i) {
+        ld2(a.md, c[i] + x[0], md[i][0], md[i][1]);
+        ld2(a.rho, c[i] + x[0], rho[i][0], rho[i][1]);
+      }
+      ld2(a.bt[0], row + x[0], b[0][0], b[0][1]);
+      ld2(a.bt[0], row + f1p + x[0], b[1][0], b[1][1]);
+      ld2(a.bt[1], row + x[0], b[2][0], b[2][1]);
+      ld2(a.bt[1], row + f2p + x[0], b[3][0], b[3][1]);
+      ld2(a.bd, row + xf[0], bd[0], bd[1]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+          md[i][j] = ld(a.md, c[i] + x[j]);
+          rho[i][j] = ld(a.rho, c[i] + x[j]);
+        }
+        b[0][j] = ld(a.bt[0], row + x[j]);
+        b[1][j] = ld(a.bt[0], row + f1p + x[j]);
+        b[2][j] = ld(a.bt[1], row + x[j]);
+        b[3][j] = ld(a.bt[1], row + f2p + x[j]);
+        bd[j] = ld(a.bd, row + xf[j]);
+      }
+    }
+    FieldRowNU<T> rn{};
+    CellNU<T> nu[K]{};
+    if (NU) {
+      rn = field_row_nu(width_at(a.wid[1], y - 1, n1, g.bc[1]), width_at(a.wid[1], y, n1, g.bc[1]),
+                        width_at(a.wid[1], y + 1, n1, g.bc[1]), width_at(a.wid[2], z - 1, n2, g.bc[2]),
+                        width_at(a.wid[2], z, n2, g.bc[2]), width_at(a.wid[2], z + 1, n2, g.bc[2]));
+      T w[K], wl[K], wr[K];
+#pragma unroll
+      for (int j = 0; j < K; ++j) w[j] = width_at(a.wid[0], cp - OFF + j, nx, g.bc[0]);
+      from_left(w, wl);
+      from_right(w, wr);
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        nu[j] = cell_nu(wl[j], w[j], wr[j], k.dt);
+        nu[j].kh *= T(2);  // the field's fluxes are not kept doubled
+        nu[j].kf *= T(2);
+      }
+    }
+    // v_x of the cell and its four neighbours (Sect. 2.4: the fluid state
+    // current at B_d) and Eq. (65) on the four faces: y faces c1 and c1+1, z
+    // faces c2 and c2+1
+    T w[4][K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
       T v[5];
 #pragma unroll
-      for (int i = 0; i < 5; ++i) v[i] = in[j].f.md[i] * rcp(in[j].f.rho[i]);
-      wA[j] = T(0.5) * (v[1] + v[0]);
-      wB[j] = T(0.5) * (v[0] + v[2]);
-      wC[j] = T(0.5) * (v[3] + v[0]);
-      wD[j] = T(0.5) * (v[0] + v[4]);
-      bA[j] = in[j].f.b[0];
-      bB[j] = in[j].f.b[1];
-      bC[j] = in[j].f.b[2];
-      bD[j] = in[j].f.b[3];
-      b4a[j] = in[j].f.b4a;
-      b4c[j] = in[j].f.b4c;
-    }
-    T bn1[2], bn2[2], eA[2], eB[2], eC[2], eD[2], dummy[2];
-    row_position2<T, LIM, true>(wA, bA, b4a, k.k_half, k.k_full, bn1, eA);
-    row_position2<T, LIM, false>(wB, bB, b4a, k.k_half, k.k_full, dummy, eB);
-    row_position2<T, LIM, true>(wC, bC, b4c, k.k_half, k.k_full, bn2, eC);
-    row_position2<T, LIM, false>(wD, bD, b4c, k.k_half, k.k_full, dummy, eD);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      // Eq. (64), physical signs
-      const T dbd = k.dt * ((eB[j] - eA[j]) * k.ih1 + (eD[j] - eC[j]) * k.ih2);
-      const int cb = in[j].cpos - 4;
-      if (in[j].valid && cb >= 0 && cb < nx) {
-        if (in[j].own1) st(a.bto[0], in[j].b4off, bn1[j]);
-        if (in[j].own2) st(a.bto[1], in[j].b4off, bn2[j]);
+      for (int i = 0; i < 5; ++i) v[i] = md[i][j] * rcp(rho[i][j]);
+      if (!NU) {
+        w[0][j] = T(0.5) * (v[1] + v[0]);
+        w[1][j] = T(0.5) * (v[0] + v[2]);
+        w[2][j] = T(0.5) * (v[3] + v[0]);
+        w[3][j] = T(0.5) * (v[0] + v[4]);
+      } else {
+        w[0][j] = face_interp(rn.a[0][0], v[1], rn.a[0][1], v[0]);
+        w[1][j] = face_interp(rn.a[1][0], v[0], rn.a[1][1], v[2]);
+        w[2][j] = face_interp(rn.a[2][0], v[3], rn.a[2][1], v[0]);
+        w[3][j] = face_interp(rn.a[3][0], v[0], rn.a[3][1], v[4]);
       }
-      const int fd = in[j].cpos - 3;
-      if (in[j].valid && in[j].own1 && in[j].own2 && fd >= 0 && (fd < nx || (outx && fd == nx)))
-        st(a.bdo, in[j].fo, in[j].f.bd3 + dbd);
     }
-  };
-  for (int it = 0; it < nit; ++it) {
-    In in[2];
-    in[0] = load1(it, 0);
-    in[1] = load1(it, 1);
-    compute(in);
+    T e[4][K], bn1[K], bn2[K], none[K];
+    face_row<T, LIM, true, NU>(w[0], b[0], k, nu, e[0], bn1);
+    face_row<T, LIM, false, NU>(w[1], b[1], k, nu, e[1], none);
+    face_row<T, LIM, true, NU>(w[2], b[2], k, nu, e[2], bn2);
+    face_row<T, LIM, false, NU>(w[3], b[3], k, nu, e[3], none);
+    // Eq. (64), physical signs, at the face right of the cell; a cell's own
+    // face is the one left of it
+    T dr[K], dbd[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+      dr[j] = k.dt * ((e[1][j] - e[0][j]) * (NU ? rn.ih1 : k.ih1) + (e[3][j] - e[2][j]) * (NU ? rn.ih2 : k.ih2));
+    from_left(dr, dbd);
+    // cells [0, nx) of b_t, x faces [0, nx) of b_x and on an outflow axis face nx
+    const bool own1 = !end2, own2 = !end1;
+    const bool first = (unsigned)c0 < (unsigned)nx, both = c0 >= 0 && c0 + 1 < nx;
+    if (both) {
+      if (own1) st2(a.bto[0], row + x[0], bn1[0], bn1[1]);
+      if (own2) st2(a.bto[1], row + x[0], bn2[0], bn2[1]);
+    } else if (first) {
+      if (own1) st(a.bto[0], row + x[0], bn1[0]);
+      if (own2) st(a.bto[1], row + x[0], bn2[0]);
+    }
+    if (own1 && own2) {
+      const int nf = nx + (outx ? 1 : 0);
+      if (c0 >= 0 && c0 + 1 < nf)
+        st2(a.bdo, row + xf[0], bd[0] + dbd[0], bd[1] + dbd[1]);
+      else if ((unsigned)c0 < (unsigned)nf)
+        st(a.bdo, row + xf[0], bd[0] + dbd[0]);
+    }
   }
 }
 
