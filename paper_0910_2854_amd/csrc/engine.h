@@ -91,6 +91,8 @@ class Engine {
   // the identity (every ghost is the cell itself, so every flux difference
   // and every potential difference is zero) and is not launched
   bool flat[3] = {false, false, false};
+  bool stream_sweeps = false;  // WorkList::stream of the table's boxes (stream_rule)
+  bool reverse = false;        // WorkList::reverse of the next sweep
   int cur[8]{};
   std::map<long long, long long> free_list;  // offset -> length (elements)
 

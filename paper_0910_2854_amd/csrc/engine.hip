@@ -31,6 +31,10 @@ Tuning default_tuning() {
   t.target[K_FIELD_Y] = t.target[K_FIELD_Z] = 64;
   t.target[K_CHECK] = 16;
   for (int k = 0; k < K_NUM; ++k) t.remap[k] = t.groups[k] = 0;
+  // the y/z field sweeps read four neighbouring rows per row: 256^3 FP32
+  // segments of 64, 145 -> 138 us (B_y) and 142 -> 134 us (B_z); 384^3 588 ->
+  // 554 and 554 -> 520 us; the fluid sweeps read two, L_y 195 -> 206 us
+  t.remap[K_FIELD_Y] = t.remap[K_FIELD_Z] = 1;
   return t;
 }
 
@@ -718,6 +722,10 @@ int Engine::build_lists() {
   if (anynu && (rc = esize == 8 ? upload_widths<double>(slots, wtotal) : upload_widths<float>(slots, wtotal)))
     return rc;
   nonuniform = anynu;
+  long long bytes = 0;
+  for (int s : slots) bytes += 16ll * (long long)esize * boxes[s].nelem;
+  stream_sweeps = nb > 0;
+  for (int s : slots) stream_sweeps = stream_sweeps && stream_rule(bytes, boxes[s].st[1] * (long long)esize);
   for (int a = 0; a < 3; ++a) {
     flat[a] = nb > 0;
     for (int s : slots) flat[a] = flat[a] && boxes[s].n[a] == 1;

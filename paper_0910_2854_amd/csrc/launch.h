@@ -42,6 +42,8 @@ inline WorkList make_wl(const Engine* e, int kind) {
   w.nwaves = e->nwaves[kind];
   w.xcd_remap = e->tuning.remap[kind];
   w.row_groups = e->tuning.groups[kind];
+  w.reverse = e->reverse;
+  w.stream = e->stream_sweeps;
   return w;
 }
 

@@ -17,13 +17,21 @@ void fluid_kernel(const FluidLaunch<T>& L, bool cfl, bool x_strided, hipStream_t
   const dim3 grid(grid_for((long long)L.wl.nwaves * 64));
   if constexpr (D == 0) {
     if (x_strided && !cfl)
-      hipLaunchKernelGGL((fluid_strided_kernel<T, 0, GRAV, HSE, LIM, NU>), grid, dim3(kBlock), 0, stream, L);
+      hipLaunchKernelGGL((fluid_strided_kernel<T, 0, GRAV, HSE, LIM, NU, false>), grid, dim3(kBlock), 0, stream, L);
     else if (cfl)
       hipLaunchKernelGGL((fluid_lanes_kernel<T, GRAV, HSE, LIM, true, NU>), grid, dim3(kBlock), 0, stream, L);
     else
       hipLaunchKernelGGL((fluid_lanes_kernel<T, GRAV, HSE, LIM, false, NU>), grid, dim3(kBlock), 0, stream, L);
   } else {
-    hipLaunchKernelGGL((fluid_strided_kernel<T, D, GRAV, HSE, LIM, NU>), grid, dim3(kBlock), 0, stream, L);
+    // the plain scheme only: the other variants have no registers to spare
+    // (FP64 with the limiter switch would lose half its waves)
+    if constexpr (GRAV == 0 && !NU && LIM != 2) {
+      if (L.wl.stream) {
+        hipLaunchKernelGGL((fluid_strided_kernel<T, D, GRAV, HSE, LIM, NU, true>), grid, dim3(kBlock), 0, stream, L);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((fluid_strided_kernel<T, D, GRAV, HSE, LIM, NU, false>), grid, dim3(kBlock), 0, stream, L);
   }
 }
 
@@ -63,7 +71,10 @@ void field_kernel(const SweepSel& s, const FieldLaunch<T>& L) {
   if constexpr (D == 0) {
     hipLaunchKernelGGL((field_lanes_kernel<T, LIM, NU>), grid, dim3(kBlock), 0, s.stream, L);
   } else {
-    hipLaunchKernelGGL((field_strided_kernel<T, D, LIM, NU>), grid, dim3(kBlock), 0, s.stream, L);
+    if (L.wl.stream)
+      hipLaunchKernelGGL((field_strided_kernel<T, D, LIM, NU, true>), grid, dim3(kBlock), 0, s.stream, L);
+    else
+      hipLaunchKernelGGL((field_strided_kernel<T, D, LIM, NU, false>), grid, dim3(kBlock), 0, s.stream, L);
   }
 }
 
@@ -110,6 +121,7 @@ int Engine::fluid_dispatch() {
     launch_fluid_sweep<T, D>(sweep_sel(), L, D == 0 && last_fluid_cfl);
   }
   for (int k = 0; k < 5; ++k) cur[k] = 1 - cur[k];
+  reverse = !reverse;
   return launch_check();
 }
 
@@ -133,6 +145,7 @@ int Engine::field_sweep() {
     launch_field_sweep<T, D>(sweep_sel(), L);
   }
   for (int f = 5; f < 8; ++f) cur[f] = 1 - cur[f];
+  reverse = !reverse;
   return launch_check();
 }
 

@@ -96,15 +96,19 @@ struct Step {
   const int* list = nullptr;
   long long waves[K_NUM] = {};
   int n[3] = {};
+  bool stream = false, reverse = false;  // WorkList::stream, and WorkList::reverse of the next sweep
   SweepSel sel;
+  const Tuning tuning = default_tuning();
 
   WorkList wl(int kind) const {
     WorkList w;
     w.boxes = table;
     w.wave_box = list;
     w.nwaves = (int)waves[kind];
-    w.xcd_remap = 0;
+    w.xcd_remap = tuning.remap[kind];
     w.row_groups = 0;
+    w.reverse = reverse;
+    w.stream = stream;
     return w;
   }
 
@@ -125,6 +129,7 @@ struct Step {
     L.wl = wl(K_FLUID_X + D);
     L.sc = sc;
     launch_fluid_sweep<T, D>(sel, L, cfl);
+    reverse = !reverse;
     for (int k = 0; k < 5; ++k) cur[k] = 1 - cur[k];
   }
 
@@ -144,6 +149,7 @@ struct Step {
     L.wl = wl(K_FIELD_X + D);
     L.sc = sc;
     launch_field_sweep<T, D>(sel, L);
+    reverse = !reverse;
     for (int f = 5; f < 8; ++f) cur[f] = 1 - cur[f];
   }
 
@@ -156,6 +162,7 @@ struct Step {
     L.wl = wl(K_CHECK);
     L.sc = sc;
     launch_check<T>(L, sel.stream);
+    reverse = !reverse;
   }
 };
 
@@ -321,6 +328,7 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
       st.sel.gravity = p->gravity;
       st.sel.hse = p->hse;
       st.sel.stream = stream;
+      st.stream = stream_rule(16 * ne * (long long)esize, (n[0] + bc[0]) * (long long)esize);
       rc = enqueue(st, dt, report, msg);
     } else {
       Step<float> st;
@@ -340,6 +348,7 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
       st.sel.gravity = p->gravity;
       st.sel.hse = p->hse;
       st.sel.stream = stream;
+      st.stream = stream_rule(16 * ne * (long long)esize, (n[0] + bc[0]) * (long long)esize);
       rc = enqueue(st, dt, report, msg);
     }
   }
