@@ -628,20 +628,78 @@ static long long kind_waves(const HostBox& b, int kind, int target, int groups, 
   }
 }
 
-// A box alone in its engine at a default work shape: halve the shape while
-// the box fills fewer than 2048 waves (8 per CU), down to one row per wave
-// (x kinds), 8-cell segments (y/z kinds) or 64 cells per wave (check).  The
-// default suits a 256^3 box; a small box alone would leave most of the chip
-// idle.  A batch fills the chip with its many boxes, and a shape set by
-// fish_set_shape or the autotuner is used as set.
-static int single_box_target(const HostBox& b, int kind, int target, int groups) {
-  int lo = 1;
-  if (kind == K_FLUID_X) lo = groups ? 8 : b.n[0] + 8;
-  if (kind == K_FIELD_X) lo = b.n[0] + 8;
-  if (kind == K_FLUID_Y || kind == K_FLUID_Z || kind == K_FIELD_Y || kind == K_FIELD_Z) lo = 8;
+// The work shape of a kind at its default, for the boxes of a table.  A launch
+// of many waves takes the default as it is; a launch that leaves SIMDs idle is
+// cut finer.
+//   x kinds: halved while the boxes have fewer than 4096 waves, down to a row
+// per wave (128^3 FP32 L_x: 35.2 us at 5 rows per wave, 32.7 at 2).
+//   y/z kinds: a wave walks its segment and `halo` more positions, and a
+// position takes it as long alone on its SIMD as `alone` waves that share one
+// (latency against issue; more where the boxes come from HBM).  With fewer than
+// 4096 waves at the default, the segment is the one whose rounds of resident
+// waves take the shortest time.  Measured, L_z, at 64 halved to 2048 waves but
+// no shorter than 8, and so: 32^3 FP32 18.0 -> 12.8 us (8 -> 2 cells), 64^3 FP32
+// 20.0 -> 16.7 (8 -> 4), FP64 24.1 -> 21.2.  Boxes of several sizes are taken
+// together, by the longest walk or the sum of the work.
+static int planned_target(const std::vector<const HostBox*>& boxes, int kind, int target, int groups, size_t esize) {
+  if (kind == K_CHECK) {
+    long long w = 0;
+    int par = 1;
+    for (;;) {
+      w = 0;
+      for (const HostBox* b : boxes) w += kind_waves(*b, kind, target, groups, &par);
+      if (w >= 2048 || target < 2) return target;
+      target /= 2;
+    }
+  }
+  if (kind == K_FIELD_X || (kind == K_FLUID_X && !groups)) {
+    int lo = 0, par = 1;
+    for (const HostBox* b : boxes) lo = std::max(lo, b->n[0] + 8);
+    for (;;) {
+      long long w = 0;
+      for (const HostBox* b : boxes) w += kind_waves(*b, kind, target, groups, &par);
+      if (w >= 4096 || target / 2 < lo) return target;
+      target /= 2;
+    }
+  }
+  const int D = kind == K_FLUID_X ? 0 : kind <= K_FLUID_Z ? kind - K_FLUID_X : kind - K_FIELD_X;
+  const int halo = kind <= K_FLUID_Z ? 6 : 8;
+  long long bytes = 0, waves = 0;
   int par = 1;
-  while (target / 2 >= lo && kind_waves(b, kind, target, groups, &par) < 2048) target /= 2;
-  return target;
+  for (const HostBox* b : boxes) {
+    bytes += 16ll * (long long)esize * b->nelem;
+    waves += kind_waves(*b, kind, target, groups, &par);
+  }
+  if (waves >= 4096) return target;
+  constexpr double kSimds = 1024.0;
+  const double occupancy = esize == 8 ? 2.0 : 4.0;
+  const double alone = (esize == 8 ? 1.15 : 1.75) * (bytes > (256ll << 20) ? 1.45 : 1.0);
+  int best = target;
+  double best_t = 0.0;
+  for (int seg = target; seg >= 1; --seg) {
+    double work = 0.0;
+    long long w = 0;
+    int longest = 0;
+    for (const HostBox* b : boxes) {
+      const long long bw = kind_waves(*b, kind, seg, groups, &par);
+      const int even = (b->n[D] + (b->n[D] + par - 1) / par - 1) / ((b->n[D] + par - 1) / par);
+      w += bw;
+      work += (double)bw * (even + halo);
+      longest = std::max(longest, even);
+    }
+    double t;
+    if (boxes.size() == 1) {
+      const double n = std::ceil((double)w / kSimds), full = std::floor(n / occupancy), rest = n - full * occupancy;
+      t = (longest + halo) * (full * std::max(alone, occupancy) + (rest > 0.0 ? std::max(alone, rest) : 0.0));
+    } else {
+      t = std::max((longest + halo) * alone, work / kSimds);
+    }
+    if (seg == target || t < best_t) {
+      best_t = t;
+      best = seg;
+    }
+  }
+  return best;
 }
 
 // Segments per pencil of a y/z kind, ceil(n_d / segment length); 0 for the
@@ -653,17 +711,28 @@ static int kind_segments(const HostBox& b, int kind, int par) {
   return 0;
 }
 
-void plan_single_box(const int n[3], const int bc[3], int par[K_NUM], int nseg[K_NUM], long long waves[K_NUM]) {
+// Segments of equal length (to a cell) instead of full ones and a remainder.
+static int even_segments(const HostBox& b, int kind, int par) {
+  const int k = kind_segments(b, kind, par);
+  return k > 0 ? (b.n[kind <= K_FLUID_Z ? kind - K_FLUID_X : kind - K_FIELD_X] + k - 1) / k : par;
+}
+
+void plan_single_box(const int n[3], const int bc[3], size_t esize, long long max_waves, int par[K_NUM],
+                     int nseg[K_NUM], long long waves[K_NUM]) {
   HostBox b;
   for (int a = 0; a < 3; ++a) {
     b.n[a] = n[a];
     b.bc[a] = bc[a];
     b.o[a] = bc[a] == 1 ? 1 : 0;
   }
+  b.nelem = (long long)(n[0] + b.o[0]) * (n[1] + b.o[1]) * (n[2] + b.o[2]);
   const Tuning t = default_tuning();
   for (int k = 0; k < K_NUM; ++k) {
-    const int target = single_box_target(b, k, t.target[k], t.groups[k]);
+    const int target = planned_target({&b}, k, t.target[k], t.groups[k], esize);
     waves[k] = kind_waves(b, k, target, t.groups[k], &par[k]);
+    // several short rows per wave where single ones are too many for the caller
+    if (k == K_FIELD_X && waves[k] > max_waves) waves[k] = kind_waves(b, k, 2 * target, t.groups[k], &par[k]);
+    if (k != K_FLUID_X) par[k] = even_segments(b, k, par[k]);
     nseg[k] = kind_segments(b, k, par[k]);
   }
 }
@@ -685,6 +754,19 @@ int Engine::build_lists() {
       boxes[s].woff[a] = anynu ? wtotal[a] : 0;
       if (anynu) wtotal[a] += boxes[s].n[a];
     }
+  // a shape left at its default is planned for the boxes; one set by
+  // fish_set_shape or the autotuner is used as set
+  int target[K_NUM];
+  bool planned[K_NUM];
+  {
+    const Tuning defaults = default_tuning();
+    std::vector<const HostBox*> all;
+    for (int s : slots) all.push_back(&boxes[s]);
+    for (int k = 0; k < K_NUM; ++k) {
+      planned[k] = nb > 0 && tuning.target[k] == defaults.target[k];
+      target[k] = planned[k] ? planned_target(all, k, tuning.target[k], tuning.groups[k], esize) : tuning.target[k];
+    }
+  }
   for (int t = 0; t < nb; ++t) {
     const HostBox& b = boxes[slots[t]];
     BoxDesc& d = desc[t];
@@ -703,12 +785,10 @@ int Engine::build_lists() {
     }
     d.slot = slots[t];
     for (int a = 0; a < 3; ++a) d.woff[a] = b.woff[a];
-    const Tuning defaults = default_tuning();
     for (int k = 0; k < K_NUM; ++k) {
       int par = 1;
-      int target = tuning.target[k];
-      if (nb == 1 && target == defaults.target[k]) target = single_box_target(b, k, target, tuning.groups[k]);
-      const long long w = kind_waves(b, k, target, tuning.groups[k], &par);
+      const long long w = kind_waves(b, k, target[k], tuning.groups[k], &par);
+      if (planned[k] && k != K_FLUID_X) par = even_segments(b, k, par);
       if ((long long)list[k].size() + w >= (1ll << 31) / 64)
         return fail(5, "work list exceeds the launch size");
       d.wave0[k] = (int)list[k].size();

@@ -256,7 +256,7 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
   }
   BoxDesc d{};
   long long waves[K_NUM];
-  plan_single_box(n, bc, d.par, d.nseg, waves);
+  plan_single_box(n, bc, esize, FISH_NOALLOC_MAX_WAVES, d.par, d.nseg, waves);
   long long most = 0;
   for (int k = 0; k < K_NUM; ++k) most = waves[k] > most ? waves[k] : most;
   if (most > FISH_NOALLOC_MAX_WAVES) {
