@@ -1362,37 +1362,46 @@ __device__ __forceinline__ T face_interp(T alo, T vlo, T ahi, T vhi) {
   return p + q;
 }
 
+// v_d of the five cells around the thread's pencil (Sect. 2.4: the fluid state
+// current at B_d) and Eq. (65) on its four t-faces.
+template <typename T, bool NU>
+__device__ __forceinline__ void field_velocities(const FieldIn<T>& in, const FieldRowNU<T>& rn, T* w) {
+  T v[5];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) v[i] = in.md[i] * rcp(in.rho[i]);
+  if (!NU) {
+    w[0] = T(0.5) * (v[1] + v[0]);
+    w[1] = T(0.5) * (v[0] + v[2]);
+    w[2] = T(0.5) * (v[3] + v[0]);
+    w[3] = T(0.5) * (v[0] + v[4]);
+  } else {
+    w[0] = face_interp(rn.a[0][0], v[1], rn.a[0][1], v[0]);
+    w[1] = face_interp(rn.a[1][0], v[0], rn.a[1][1], v[2]);
+    w[2] = face_interp(rn.a[2][0], v[3], rn.a[2][1], v[0]);
+    w[3] = face_interp(rn.a[3][0], v[0], rn.a[3][1], v[4]);
+  }
+}
+// Eq. (64), physical signs: d/dt b_d = d_t1 Phi^t1 + d_t2 Phi^t2, from the edge
+// fluxes of the four faces
+template <typename T, bool NU>
+__device__ __forceinline__ T field_change(T eA, T eB, T eC, T eD, const FieldConsts<T>& k, const FieldRowNU<T>& rn) {
+  return k.dt * ((eB - eA) * (NU ? rn.ih1 : k.ih1) + (eD - eC) * (NU ? rn.ih2 : k.ih2));
+}
+
 // All four face rows at one position.
 template <typename T, int LIM, bool NU>
 __device__ __forceinline__ void field_compute(const FieldIn<T>& in, const FieldConsts<T>& k, const FieldRowNU<T>& rn,
                                               const FieldPosNU<T>& pn, const RowHist<T>* hi, RowHist<T>* ho, T& bn1,
                                               T& bn2, T& dbd) {
-  // v_d of the five cells around the thread's pencil (Sect. 2.4: the fluid
-  // state current at B_d)
-  T v[5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i) v[i] = in.md[i] * rcp(in.rho[i]);
-  // Eq. (65) on the four t-faces
-  T wA, wB, wC, wD;
-  if (!NU) {
-    wA = T(0.5) * (v[1] + v[0]);
-    wB = T(0.5) * (v[0] + v[2]);
-    wC = T(0.5) * (v[3] + v[0]);
-    wD = T(0.5) * (v[0] + v[4]);
-  } else {
-    wA = face_interp(rn.a[0][0], v[1], rn.a[0][1], v[0]);
-    wB = face_interp(rn.a[1][0], v[0], rn.a[1][1], v[2]);
-    wC = face_interp(rn.a[2][0], v[3], rn.a[2][1], v[0]);
-    wD = face_interp(rn.a[3][0], v[0], rn.a[3][1], v[4]);
-  }
+  T w[4];
+  field_velocities<T, NU>(in, rn, w);
   const T kh = NU ? pn.kh : k.k_half, kf = NU ? pn.kf : k.k_full;
   T dummy;
-  const T eA = row_position<T, LIM, true, NU>(wA, in.b[0], kh, kf, pn.w, hi[0], ho[0], bn1);
-  const T eB = row_position<T, LIM, false, NU>(wB, in.b[1], kh, kf, pn.w, hi[1], ho[1], dummy);
-  const T eC = row_position<T, LIM, true, NU>(wC, in.b[2], kh, kf, pn.w, hi[2], ho[2], bn2);
-  const T eD = row_position<T, LIM, false, NU>(wD, in.b[3], kh, kf, pn.w, hi[3], ho[3], dummy);
-  // Eq. (64), physical signs: d/dt b_d = d_t1 Phi^t1 + d_t2 Phi^t2
-  dbd = k.dt * ((eB - eA) * (NU ? rn.ih1 : k.ih1) + (eD - eC) * (NU ? rn.ih2 : k.ih2));
+  const T eA = row_position<T, LIM, true, NU>(w[0], in.b[0], kh, kf, pn.w, hi[0], ho[0], bn1);
+  const T eB = row_position<T, LIM, false, NU>(w[1], in.b[1], kh, kf, pn.w, hi[1], ho[1], dummy);
+  const T eC = row_position<T, LIM, true, NU>(w[2], in.b[2], kh, kf, pn.w, hi[2], ho[2], bn2);
+  const T eD = row_position<T, LIM, false, NU>(w[3], in.b[3], kh, kf, pn.w, hi[3], ho[3], dummy);
+  dbd = field_change<T, NU>(eA, eB, eC, eD, k, rn);
 }
 
 // Strided policy (d = y or z).
@@ -1445,6 +1454,22 @@ __global__ __launch_bounds__(256) void field_strided_kernel(FieldLaunch<T> FL) {
     const int n1 = g.n[T1], n2 = g.n[T2], b1 = g.bc[T1], b2 = g.bc[T2];
     rn = field_row_nu(width_at(w1, c1 - 1, n1, b1), width_at(w1, c1, n1, b1), width_at(w1, c1 + 1, n1, b1),
                       width_at(w2, c2 - 1, n2, b2), width_at(w2, c2, n2, b2), width_at(w2, c2 + 1, n2, b2));
+  }
+  if (nD == 1) {
+    // every ghost along d is the cell itself: the smoothing, the predictor and
+    // the limited slopes leave v b of the cell as the edge flux, exactly, and
+    // b_t as it was; a walk of nine positions otherwise (512^2 FP32: 21 us)
+    const FieldIn<T> in = field_load<T>(a.md, a.rho, a.bt[0], a.bt[1], l);
+    T w[4];
+    field_velocities<T, NU>(in, rn, w);
+    const T dbd = field_change<T, NU>(w[0] * in.b[0], w[1] * in.b[1], w[2] * in.b[2], w[3] * in.b[3], k, rn);
+    if (own1) st(a.bto[0], l.fA, in.b[0]);
+    if (own2) st(a.bto[1], l.fA, in.b[2]);
+    if (ownd) {
+      st(a.bdo, l.fA, ld(a.bd, l.fA) + dbd);
+      if (outD) st(a.bdo + stD, l.fA, ld(a.bd + stD, l.fA) + dbd);
+    }
+    return;
   }
   auto load = [&](int it) {
     const int s = s0 - 4 + it;  // uniform
@@ -1654,38 +1679,30 @@ __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
         nu[j].kf *= T(2);
       }
     }
-    // v_x of the cell and its four neighbours (Sect. 2.4: the fluid state
-    // current at B_d) and Eq. (65) on the four faces: y faces c1 and c1+1, z
-    // faces c2 and c2+1
-    T w[4][K];
+    T w[4][K];  // v_x on the y faces c1 and c1+1 and the z faces c2 and c2+1
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      T v[5];
+      FieldIn<T> in;
+      T wj[4];
 #pragma unroll
-      for (int i = 0; i < 5; ++i) v[i] = md[i][j] * rcp(rho[i][j]);
-      if (!NU) {
-        w[0][j] = T(0.5) * (v[1] + v[0]);
-        w[1][j] = T(0.5) * (v[0] + v[2]);
-        w[2][j] = T(0.5) * (v[3] + v[0]);
-        w[3][j] = T(0.5) * (v[0] + v[4]);
-      } else {
-        w[0][j] = face_interp(rn.a[0][0], v[1], rn.a[0][1], v[0]);
-        w[1][j] = face_interp(rn.a[1][0], v[0], rn.a[1][1], v[2]);
-        w[2][j] = face_interp(rn.a[2][0], v[3], rn.a[2][1], v[0]);
-        w[3][j] = face_interp(rn.a[3][0], v[0], rn.a[3][1], v[4]);
+      for (int i = 0; i < 5; ++i) {
+        in.md[i] = md[i][j];
+        in.rho[i] = rho[i][j];
       }
+      field_velocities<T, NU>(in, rn, wj);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w[q][j] = wj[q];
     }
     T e[4][K], bn1[K], bn2[K], none[K];
     face_row<T, LIM, true, NU>(w[0], b[0], k, nu, e[0], bn1);
     face_row<T, LIM, false, NU>(w[1], b[1], k, nu, e[1], none);
     face_row<T, LIM, true, NU>(w[2], b[2], k, nu, e[2], bn2);
     face_row<T, LIM, false, NU>(w[3], b[3], k, nu, e[3], none);
-    // Eq. (64), physical signs, at the face right of the cell; a cell's own
-    // face is the one left of it
+    // the change of b_x at the face right of the cell; a cell's own face is the
+    // one left of it
     T dr[K], dbd[K];
 #pragma unroll
-    for (int j = 0; j < K; ++j)
-      dr[j] = k.dt * ((e[1][j] - e[0][j]) * (NU ? rn.ih1 : k.ih1) + (e[3][j] - e[2][j]) * (NU ? rn.ih2 : k.ih2));
+    for (int j = 0; j < K; ++j) dr[j] = field_change<T, NU>(e[0][j], e[1][j], e[2][j], e[3][j], k, rn);
     from_left(dr, dbd);
     // cells [0, nx) of b_t, x faces [0, nx) of b_x and on an outflow axis face nx
     const bool own1 = !end2, own2 = !end1;
