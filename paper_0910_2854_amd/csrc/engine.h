@@ -144,6 +144,7 @@ class Engine {
   hipEvent_t stage_ev[2] = {nullptr, nullptr};
   void* stage[2] = {nullptr, nullptr};
   size_t stage_bytes = 0;
+  int stage_turn = 0;  // the staging buffer the next piece takes
 
   // measurement hook
   int timing_mask = 0;

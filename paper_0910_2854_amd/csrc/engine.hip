@@ -13,6 +13,7 @@
 #include <cmath>
 #include <cstring>
 #include <functional>
+#include <system_error>
 #include <thread>
 
 namespace fish {
@@ -338,17 +339,27 @@ int Engine::park(int slot) {
 // one is copied.  The compute stream waits for an upload through an event;
 // a download waits for the compute stream the same way.
 
-// Run f(a, b) over [0, n) split across up to 16 threads.
-static void parallel_for(long long n, const std::function<void(long long, long long)>& f) {
+// Run f(a, b) over [0, n) split across up to 16 threads, one per MB of host
+// data: starting a thread costs as much as converting a few hundred kB (48
+// boxes of 16^3-64^3, an array at a time over 16 threads each: 115 ms).
+static void parallel_for(long long n, size_t host_bytes, const std::function<void(long long, long long)>& f) {
   const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-  const long long nt = std::min<long long>(std::min<long long>(hw, 16), n);
+  const long long nt =
+      std::min<long long>({(long long)hw, 16, n, std::max<long long>(1, (long long)(host_bytes >> 20))});
   if (nt <= 1 || n < 8) {
     f(0, n);
     return;
   }
   std::vector<std::thread> th;
-  th.reserve((size_t)nt);
-  for (long long t = 0; t < nt; ++t) th.emplace_back(f, n * t / nt, n * (t + 1) / nt);
+  th.reserve((size_t)nt - 1);
+  long long t = 1;
+  try {
+    for (; t < nt; ++t) th.emplace_back(f, n * t / nt, n * (t + 1) / nt);
+  } catch (const std::system_error&) {
+    // no more threads to be had: the rest runs here
+  }
+  f(0, n / nt);
+  if (t < nt) f(n * t / nt, n);
   for (auto& x : th) x.join();
 }
 
@@ -378,59 +389,86 @@ static ArrayShape array_shape(const HostBox& c, int a) {
   return s;
 }
 
-// Device planes [k0, k1) of array a from the interface array src into dst
-// (zero outside the stored region).
+// A piece of a transfer: device planes [k0, k1) of array a, in staging memory
+// at dev, and the interface array it belongs to.
 template <typename T>
-static void pack_planes(const HostBox& c, int a, const double* src, T* dst, int k0, int k1) {
-  const ArrayShape s = array_shape(c, a);
-  const long long rows = (long long)(k1 - k0) * s.ext[1];
-  parallel_for(rows, [&](long long r0, long long r1) {
-    for (long long r = r0; r < r1; ++r) {
-      const int k = k0 + (int)(r / s.ext[1]);
-      const int j = (int)(r % s.ext[1]);
-      T* d = dst + (long long)(k - k0) * s.st2 + (long long)j * s.st1;
-      if (k >= s.keep[2] || j >= s.keep[1]) {
-        for (int i = 0; i < s.ext[0]; ++i) d[i] = T(0);
-        continue;
-      }
-      const double* q = src + (size_t)s.m[0] * ((size_t)j + (size_t)s.m[1] * k);
-      for (int i = 0; i < s.keep[0]; ++i) d[i] = (T)q[i];
-      for (int i = s.keep[0]; i < s.ext[0]; ++i) d[i] = T(0);
-    }
-  });
+struct Piece {
+  int a, k0, k1;
+  T* dev;
+  double* host;  // packed pieces only read it
+};
+
+// Row j of plane k (device layout) from the interface array (zero outside the
+// stored region).
+template <typename T>
+static void pack_row(const HostBox& c, const ArrayShape& s, const Piece<T>& q, int k, int j) {
+  T* d = q.dev + (long long)(k - q.k0) * c.st[2] + (long long)j * c.st[1];
+  if (k >= s.keep[2] || j >= s.keep[1]) {
+    for (int i = 0; i < s.ext[0]; ++i) d[i] = T(0);
+    return;
+  }
+  const double* h = q.host + (size_t)s.m[0] * ((size_t)j + (size_t)s.m[1] * k);
+  for (int i = 0; i < s.keep[0]; ++i) d[i] = (T)h[i];
+  for (int i = s.keep[0]; i < s.ext[0]; ++i) d[i] = T(0);
 }
 
-// Interface planes of array a whose device plane lies in [k0, k1), from the
-// device planes in src.  On a periodic axis face n is written equal to face 0.
+// Row j of plane k (interface layout) from the device planes.  On a periodic
+// axis face n is written equal to face 0.
 template <typename T>
-static void unpack_planes(const HostBox& c, int a, const T* src, double* dst, int k0, int k1) {
-  const ArrayShape s = array_shape(c, a);
-  const int ax = (a >= 5 && a <= 7) ? a - 5 : -1;
-  // interface planes to fill: k in [k0, k1) within m[2], plus plane n of a
-  // periodic z-face array when device plane 0 is in the chunk
-  std::vector<std::pair<int, int>> planes;  // (interface k, device k)
-  for (int k = k0; k < k1 && k < s.m[2]; ++k) planes.push_back({k, k});
-  if (ax == 2 && c.bc[2] == 0 && k0 == 0) planes.push_back({c.n[2], 0});
-  if (ax == 2 && c.bc[2] == 0) {
-    // interface plane n maps to device plane 0, never to device plane n
-    planes.erase(std::remove_if(planes.begin(), planes.end(),
-                                [&](const std::pair<int, int>& p) { return p.first == c.n[2] && p.second != 0; }),
-                 planes.end());
+static void unpack_row(const HostBox& c, const ArrayShape& s, const Piece<T>& q, int k, int j) {
+  const int ax = (q.a >= 5 && q.a <= 7) ? q.a - 5 : -1;
+  double* d = q.host + (size_t)s.m[0] * ((size_t)j + (size_t)s.m[1] * k);
+  if (ax == 2 && c.bc[2] == 0 && k == c.n[2]) k = 0;
+  if (ax == 1 && c.bc[1] == 0 && j == c.n[1]) j = 0;
+  const T* h = q.dev + (long long)(k - q.k0) * c.st[2] + (long long)j * c.st[1];
+  if (ax == 0 && c.bc[0] == 0) {
+    for (int i = 0; i < c.n[0]; ++i) d[i] = (double)h[i];
+    d[c.n[0]] = (double)h[0];
+  } else {
+    for (int i = 0; i < s.m[0]; ++i) d[i] = (double)h[i];
   }
-  const long long rows = (long long)planes.size() * s.m[1];
-  parallel_for(rows, [&](long long r0, long long r1) {
+}
+
+// All rows of some pieces, packed or unpacked, spread over threads together.
+template <typename T, bool PACK>
+static void convert(const HostBox& c, const std::vector<Piece<T>>& pieces) {
+  struct Rows {
+    ArrayShape s;
+    long long first;  // row number of the piece's first row
+    int k0, per_plane;
+    bool wrap;  // unpacking the z faces of a periodic axis: plane n, from device plane 0
+  };
+  std::vector<Rows> rows;
+  long long total = 0;
+  size_t bytes = 0;
+  for (const auto& q : pieces) {
+    Rows r;
+    r.s = array_shape(c, q.a);
+    r.first = total;
+    r.k0 = q.k0;
+    r.per_plane = PACK ? r.s.ext[1] : r.s.m[1];
+    const bool periodic_z = !PACK && q.a == 7 && c.bc[2] == 0;
+    r.wrap = periodic_z && q.k0 == 0;
+    const int limit = PACK ? q.k1 : std::min(q.k1, periodic_z ? c.n[2] : r.s.m[2]);
+    const long long planes = std::max(0, limit - q.k0) + (r.wrap ? 1 : 0);
+    total += planes * r.per_plane;
+    bytes += (size_t)planes * r.per_plane * r.s.m[0] * sizeof(double);
+    rows.push_back(r);
+  }
+  parallel_for(total, bytes, [&](long long r0, long long r1) {
+    size_t i = rows.size() - 1;
+    while (rows[i].first > r0) --i;
     for (long long r = r0; r < r1; ++r) {
-      const auto& pk = planes[(size_t)(r / s.m[1])];
-      int j = (int)(r % s.m[1]);
-      double* d = dst + (size_t)s.m[0] * ((size_t)j + (size_t)s.m[1] * pk.first);
-      if (ax == 1 && c.bc[1] == 0 && j == c.n[1]) j = 0;  // face n is face 0
-      const T* q = src + (long long)(pk.second - k0) * s.st2 + (long long)j * s.st1;
-      if (ax == 0 && c.bc[0] == 0) {
-        for (int i = 0; i < c.n[0]; ++i) d[i] = (double)q[i];
-        d[c.n[0]] = (double)q[0];
-      } else {
-        for (int i = 0; i < s.m[0]; ++i) d[i] = (double)q[i];
-      }
+      while (i + 1 < rows.size() && r >= rows[i + 1].first) ++i;
+      const Rows& w = rows[i];
+      const long long local = r - w.first;
+      const int j = (int)(local % w.per_plane);
+      int k = w.k0 + (int)(local / w.per_plane);
+      if (w.wrap) k = k == 0 ? c.n[2] : k - 1;  // plane n first, then 0, 1, ...
+      if (PACK)
+        pack_row(c, w.s, pieces[i], k, j);
+      else
+        unpack_row(c, w.s, pieces[i], k, j);
     }
   });
 }
@@ -463,19 +501,38 @@ int Engine::upload_t(int slot, const double* cell5, const double* bx, const doub
     HIP_TRY(hipEventRecord(compute_ev, cfg.stream));
     HIP_TRY(hipStreamWaitEvent(copy_stream, compute_ev, 0));
   }
-  int idx = 0;
-  for (int a = 0; a < 9; ++a) {
-    if (a == 8 && !cfg.gravity) break;
-    const double* src = a < 5 ? cell5 + a * nc : a == 5 ? bx : a == 6 ? by : a == 7 ? bz : phi_in;
-    T* dev = (a < 8 ? (T*)pool[cur[a]][a].ptr : (T*)phi.ptr) + c.off;
-    for (int k0 = 0; k0 < nz; k0 += ppc) {
-      const int k1 = std::min(nz, k0 + ppc);
-      HIP_TRY(hipEventSynchronize(stage_ev[idx]));  // the buffer's previous copy is done
-      pack_planes<T>(c, a, src, (T*)stage[idx], k0, k1);
-      HIP_TRY(hipMemcpyAsync(dev + (long long)k0 * c.st[2], stage[idx], (size_t)(k1 - k0) * plane,
-                             hipMemcpyHostToDevice, copy_stream));
-      HIP_TRY(hipEventRecord(stage_ev[idx], copy_stream));
-      idx ^= 1;
+  const size_t array = (size_t)nz * plane;
+  const int narrays = cfg.gravity ? 9 : 8;
+  auto host = [&](int a) {
+    const double* h = a < 5 ? cell5 + a * nc : a == 5 ? bx : a == 6 ? by : a == 7 ? bz : phi_in;
+    return const_cast<double*>(h);
+  };
+  auto device = [&](int a) { return (a < 8 ? (T*)pool[cur[a]][a].ptr : (T*)phi.ptr) + c.off; };
+  // a box that fits a staging buffer goes as one piece of work; the two
+  // buffers alternate between boxes
+  if (narrays * array <= stage_bytes) {
+    const int idx = stage_turn;
+    stage_turn ^= 1;
+    HIP_TRY(hipEventSynchronize(stage_ev[idx]));  // the buffer's previous copy is done
+    std::vector<Piece<T>> pieces;
+    for (int a = 0; a < narrays; ++a)
+      pieces.push_back({a, 0, nz, (T*)((char*)stage[idx] + a * array), host(a)});
+    convert<T, true>(c, pieces);
+    for (const auto& q : pieces)
+      HIP_TRY(hipMemcpyAsync(device(q.a), q.dev, array, hipMemcpyHostToDevice, copy_stream));
+    HIP_TRY(hipEventRecord(stage_ev[idx], copy_stream));
+  } else {
+    for (int a = 0; a < narrays; ++a) {
+      for (int k0 = 0; k0 < nz; k0 += ppc) {
+        const int idx = stage_turn;
+        stage_turn ^= 1;
+        const int k1 = std::min(nz, k0 + ppc);
+        HIP_TRY(hipEventSynchronize(stage_ev[idx]));  // the buffer's previous copy is done
+        convert<T, true>(c, {{a, k0, k1, (T*)stage[idx], host(a)}});
+        HIP_TRY(hipMemcpyAsync(device(a) + (long long)k0 * c.st[2], stage[idx], (size_t)(k1 - k0) * plane,
+                               hipMemcpyHostToDevice, copy_stream));
+        HIP_TRY(hipEventRecord(stage_ev[idx], copy_stream));
+      }
     }
   }
   HIP_TRY(hipEventRecord(copy_ev, copy_stream));
@@ -520,38 +577,53 @@ int Engine::download_t(int slot, double* cell5, double* bx, double* by, double* 
     HIP_TRY(hipEventRecord(compute_ev, cfg.stream));
     HIP_TRY(hipStreamWaitEvent(copy_stream, compute_ev, 0));
   }
+  const size_t array = (size_t)nz * plane;
+  auto host = [&](int a) { return a < 5 ? (cell5 ? cell5 + a * nc : nullptr) : a == 5 ? bx : a == 6 ? by : bz; };
+  auto device = [&](int a) { return (const T*)pool[cur[a]][a].ptr + c.off; };
+  // (a staging buffer still being uploaded from is written behind that upload:
+  // both run on the copy stream)
+  if (8 * array <= stage_bytes) {
+    std::vector<Piece<T>> pieces;
+    for (int a = 0; a < 8; ++a)
+      if (host(a)) pieces.push_back({a, 0, nz, (T*)((char*)stage[stage_turn] + a * array), host(a)});
+    if (pieces.empty()) return 0;
+    for (const auto& q : pieces)
+      HIP_TRY(hipMemcpyAsync(q.dev, device(q.a), array, hipMemcpyDeviceToHost, copy_stream));
+    HIP_TRY(hipEventRecord(stage_ev[stage_turn], copy_stream));
+    HIP_TRY(hipEventSynchronize(stage_ev[stage_turn]));
+    convert<T, false>(c, pieces);
+    return 0;
+  }
   // chunks in order; chunk i is unpacked while chunk i+1 is copied
   struct Pending {
-    int a, k0, k1, idx;
-    double* dst;
+    Piece<T> q;
+    int idx;
   };
   std::vector<Pending> pend;
-  int idx = 0;
-  auto drain = [&](const Pending& q) -> int {
-    HIP_TRY(hipEventSynchronize(stage_ev[q.idx]));
-    unpack_planes<T>(c, q.a, (const T*)stage[q.idx], q.dst, q.k0, q.k1);
+  auto drain = [&](const Pending& p) -> int {
+    HIP_TRY(hipEventSynchronize(stage_ev[p.idx]));
+    convert<T, false>(c, {p.q});
     return 0;
   };
   for (int a = 0; a < 8; ++a) {
-    double* dst = a < 5 ? (cell5 ? cell5 + a * nc : nullptr) : a == 5 ? bx : a == 6 ? by : bz;
-    if (!dst) continue;
-    const T* dev = (const T*)pool[cur[a]][a].ptr + c.off;
+    if (!host(a)) continue;
     for (int k0 = 0; k0 < nz; k0 += ppc) {
+      const int idx = stage_turn;
+      stage_turn ^= 1;
       const int k1 = std::min(nz, k0 + ppc);
       // the buffer is free once its previous chunk has been unpacked
-      if (!pend.empty() && pend.front().idx == idx) {
+      if (pend.size() == 2) {
         if ((rc = drain(pend.front()))) return rc;
         pend.erase(pend.begin());
       }
-      HIP_TRY(hipMemcpyAsync(stage[idx], dev + (long long)k0 * c.st[2], (size_t)(k1 - k0) * plane,
+      HIP_TRY(hipMemcpyAsync(stage[idx], device(a) + (long long)k0 * c.st[2], (size_t)(k1 - k0) * plane,
                              hipMemcpyDeviceToHost, copy_stream));
       HIP_TRY(hipEventRecord(stage_ev[idx], copy_stream));
-      pend.push_back({a, k0, k1, idx, dst});
-      idx ^= 1;
+      pend.push_back({{a, k0, k1, (T*)stage[idx], host(a)}, idx});
     }
   }
-  for (const auto& q : pend)
-    if ((rc = drain(q))) return rc;
+  for (const auto& p : pend)
+    if ((rc = drain(p))) return rc;
   return 0;
 }
 
