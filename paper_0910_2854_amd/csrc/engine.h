@@ -93,6 +93,7 @@ class Engine {
   bool flat[3] = {false, false, false};
   bool stream_sweeps = false;  // WorkList::stream of the table's boxes (stream_rule)
   bool reverse = false;        // WorkList::reverse of the next sweep
+  bool lanes[K_NUM]{};         // WorkList::lanes of the table's lists
   int cur[8]{};
   std::map<long long, long long> free_list;  // offset -> length (elements)
 

@@ -44,6 +44,7 @@ inline WorkList make_wl(const Engine* e, int kind) {
   w.row_groups = e->tuning.groups[kind];
   w.reverse = e->reverse;
   w.stream = e->stream_sweeps;
+  w.lanes = e->lanes[kind];
   return w;
 }
 

@@ -42,9 +42,9 @@ void launch_begin_step(const BoxDesc* boxes, int nb, Scalars* sc, double dt, hip
 
 // The work shape of a box alone in its table at the default tuning (as the
 // engine plans it): per kind the parameter of BoxDesc::par, the segments per
-// pencil of BoxDesc::nseg and the waves of its work list.
+// pencil of BoxDesc::nseg, the waves of its work list and WorkList::lanes.
 // With more than max_waves waves the x field sweep is cut coarser.
 void plan_single_box(const int n[3], const int bc[3], size_t esize, long long max_waves, int par[K_NUM],
-                     int nseg[K_NUM], long long waves[K_NUM]);
+                     int nseg[K_NUM], long long waves[K_NUM], bool lanes[K_NUM]);
 
 }  // namespace fish

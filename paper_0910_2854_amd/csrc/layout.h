@@ -63,6 +63,7 @@ struct WorkList {
   int reverse;          // 1: the blocks run from the last to the first (see list_block)
   int stream;           // 1: what a sweep reads or writes once passes the caches by (see ld_once)
   int row_groups;       // y/z kinds: 1 = a block's waves on consecutive rows (see strided_map)
+  int lanes;            // y/z kinds: 1 = the lanes policy (par: rows per wave)
 };
 
 }  // namespace fish

@@ -95,6 +95,7 @@ struct Step {
   Scalars* sc = nullptr;
   const int* list = nullptr;
   long long waves[K_NUM] = {};
+  bool lanes[K_NUM] = {};
   int n[3] = {};
   bool stream = false, reverse = false;  // WorkList::stream, and WorkList::reverse of the next sweep
   SweepSel sel;
@@ -109,6 +110,7 @@ struct Step {
     w.row_groups = 0;
     w.reverse = reverse;
     w.stream = stream;
+    w.lanes = lanes[kind];
     return w;
   }
 
@@ -256,7 +258,8 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
   }
   BoxDesc d{};
   long long waves[K_NUM];
-  plan_single_box(n, bc, esize, FISH_NOALLOC_MAX_WAVES, d.par, d.nseg, waves);
+  bool lanes[K_NUM];
+  plan_single_box(n, bc, esize, FISH_NOALLOC_MAX_WAVES, d.par, d.nseg, waves, lanes);
   long long most = 0;
   for (int k = 0; k < K_NUM; ++k) most = waves[k] > most ? waves[k] : most;
   if (most > FISH_NOALLOC_MAX_WAVES) {
@@ -322,7 +325,10 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
       st.table = table;
       st.sc = sc;
       st.list = list;
-      for (int k = 0; k < K_NUM; ++k) st.waves[k] = waves[k];
+      for (int k = 0; k < K_NUM; ++k) {
+        st.waves[k] = waves[k];
+        st.lanes[k] = lanes[k];
+      }
       for (int a = 0; a < 3; ++a) st.n[a] = n[a];
       st.sel.limiter = p->limiter;
       st.sel.gravity = p->gravity;
@@ -342,7 +348,10 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
       st.table = table;
       st.sc = sc;
       st.list = list;
-      for (int k = 0; k < K_NUM; ++k) st.waves[k] = waves[k];
+      for (int k = 0; k < K_NUM; ++k) {
+        st.waves[k] = waves[k];
+        st.lanes[k] = lanes[k];
+      }
       for (int a = 0; a < 3; ++a) st.n[a] = n[a];
       st.sel.limiter = p->limiter;
       st.sel.gravity = p->gravity;

@@ -722,8 +722,8 @@ __device__ __forceinline__ void from_right(const Vec<T, 5> (&x)[K], Vec<T, 5> (&
 #pragma unroll
   for (int i = 0; i < 5; ++i) o[K - 1].v[i] = lane_shl(x[0].v[i]);
 }
-template <typename T, bool HSE, int K>
-__device__ __forceinline__ void from_right(const CellQ<T, HSE> (&x)[K], CellQ<T, HSE> (&o)[K]) {
+template <int D, typename T, bool HSE, int K>
+__device__ __forceinline__ void cells_from_right(const CellQ<T, HSE> (&x)[K], CellQ<T, HSE> (&o)[K]) {
 #pragma unroll
   for (int j = 0; j + 1 < K; ++j) o[j] = x[j + 1];
   const CellQ<T, HSE>& c = x[0];
@@ -733,7 +733,7 @@ __device__ __forceinline__ void from_right(const CellQ<T, HSE> (&x)[K], CellQ<T,
     r.u[i] = lane_shl(c.u[i]);
     r.F[i] = i == RHO ? r.F[i] : lane_shl(c.F[i]);
   }
-  r.F[RHO] = r.u[MX];  // the mass flux along x
+  r.F[RHO] = r.u[MX + D];  // the mass flux
   r.d = lane_shl(c.d);
   r.sup = T(0);
   if (HSE) {
@@ -767,11 +767,10 @@ __device__ __forceinline__ CellNU<T> cell_nu(T wm, T w0, T wp, T dt) {
 // products f, potential phi and (split gravity) kicks gh; the arithmetic of
 // fluid_position, with every value kept in the lane of its cell.  Interface j
 // is the one right of cell j.
-template <typename T, int GRAV, bool HSE, int LIM, bool NU, int K>
+template <typename T, int D, int GRAV, bool HSE, int LIM, bool NU, int K>
 __device__ __forceinline__ void fluid_window(const T (&u_in)[K][5], const FieldQ<T> (&f)[K], const T (&phi)[K],
                                              const T (&gh)[K], const CellNU<T> (&nu)[K], const FluidConsts<T>& k,
                                              T (&un)[K][5]) {
-  constexpr int D = 0;
   T phl[K], phr[K];
   from_left(phi, phl);
   from_right(phi, phr);
@@ -784,7 +783,7 @@ __device__ __forceinline__ void fluid_window(const T (&u_in)[K][5], const FieldQ
     if (GRAV == 2) gravity_kick<T, D>(u[j], gh[j]);
     cell_quantities<T, D, HSE>(u[j], f[j], k.gamma, q[j]);
   }
-  from_right(q, qr);
+  cells_from_right<D>(q, qr);
   // predictor
   Vec<T, 5> F[K], Fl[K];
 #pragma unroll
@@ -810,7 +809,7 @@ __device__ __forceinline__ void fluid_window(const T (&u_in)[K][5], const FieldQ
     }
     cell_quantities<T, D, HSE>(up[j], f[j], k.gamma, q[j]);
   }
-  from_right(q, qr);
+  cells_from_right<D>(q, qr);
   // corrector
   Vec<T, 5> ap[K], am[K], bs[K], al[K], Lp[K], Lm[K], Lmr[K];
 #pragma unroll
@@ -939,8 +938,11 @@ __device__ __forceinline__ void st2_once(T* p, unsigned off_bytes, T v0, T v1) {
 
 // With CFL the sweep also reduces the CFL speed of the state it writes (the
 // last sub-operator of a double step leaves the next step's time step ready).
-template <typename T, int GRAV, bool HSE, int LIM, bool CFL, bool NU>
+template <typename T, int D, int GRAV, bool HSE, int LIM, bool CFL, bool NU>
 __global__ __launch_bounds__(256) void fluid_lanes_kernel(FluidLaunch<T> FL) {
+  static_assert(D == 0 || !CFL, "the last sweep of a step is along x");
+  constexpr int A = D == 0 ? 1 : 0, O = D == 0 ? 2 : 3 - D;  // rows: A fast
+  constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
   constexpr int K = 2;
   // an output depends on 3 cells to its left and 3 to its right, the last of
   // which takes its right face from a fourth
@@ -952,104 +954,105 @@ __global__ __launch_bounds__(256) void fluid_lanes_kernel(FluidLaunch<T> FL) {
   if (CFL) cfl_shared_init(&sh);
   const BoxDesc* d;
   int lw;
-  if (!work_item<K_FLUID_X>(FL.wl, d, lw)) return;
-  const FluidArgs<T> a = fluid_view<T, K_FLUID_X>(FL, *d);
+  if (!work_item<K_FLUID_X + D>(FL.wl, d, lw)) return;
+  const FluidArgs<T> a = fluid_view<T, K_FLUID_X + D>(FL, *d);
   const Geo& g = a.g;
-  const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-  const int nrows = ny * nz;  // < 2^32 bytes of cells
+  const int n = g.n[D], bcD = g.bc[D];
+  const int nrows = g.n[A] * g.n[O];  // < 2^32 bytes of cells
   const int rpw = a.rows_per_wave;
   RowStream rs;
-  rs.init(lw, (nrows + rpw - 1) / rpw, rpw, (OFF + nx + 4 + K - 1) / K * K, ny, nrows);
+  rs.init(lw, (nrows + rpw - 1) / rpw, rpw, (OFF + n + 4 + K - 1) / K * K, g.n[A], nrows);
   const int npos = rs.rows * rs.L;
   const int lane = threadIdx.x & 63;
-  const FluidConsts<T> k = fluid_consts(a, 0);
+  const FluidConsts<T> k = fluid_consts(a, D);
   T smax[3] = {T(0), T(0), T(0)};  // per axis, the largest |v_d| + c_F,d of the lane's cells
   double cnu = 0.0;  // irregular mesh: the CFL speed over widths, per cell
   int bad = 0;
-  const unsigned st1 = (unsigned)g.st[1];  // arrays < 2^32 bytes
-  const unsigned plane_rows = (unsigned)(ny + g.bc[1]);
-  // byte offsets of the face above the row's cells along y and z: the next
-  // row or plane, or on a periodic axis from the last one back to the first
-  const unsigned stz = (unsigned)g.st[2] * z4;
-  const unsigned dy_in = st1 * z4, dy_last = g.bc[1] ? dy_in : (unsigned)(1 - ny) * st1 * z4;
-  const unsigned dz_in = stz, dz_last = g.bc[2] ? dz_in : (unsigned)(1 - nz) * stz;
+  // byte offsets (arrays < 2^32 bytes): along the row, between rows, and to the
+  // face above the row's cells along T1 and T2 (the next row, or on a periodic
+  // axis from the last one back to the first)
+  const unsigned sD = (unsigned)g.st[D] * z4, sA = (unsigned)g.st[A] * z4, sO = (unsigned)g.st[O] * z4;
+  const unsigned up1 = (unsigned)g.st[T1] * z4, last1 = g.bc[T1] ? up1 : (unsigned)(1 - g.n[T1]) * up1;
+  const unsigned up2 = (unsigned)g.st[T2] * z4, last2 = g.bc[T2] ? up2 : (unsigned)(1 - g.n[T2]) * up2;
   struct In {
-    T u[K][5], bx[K], by[K][2], bz[K][2];
+    T u[K][5], bD[K], b1[K][2], b2[K][2];
     T phi[K], gh[K];
-    T w[K], wy, wz;  // irregular mesh: the cells' widths along x; the row's along y and z
-    unsigned o;      // byte offset of the lane's first cell (mapped into the box)
-    int c0;          // its index along x; out of the row: no output
+    T w[K], wt[2];   // irregular mesh: the cells' widths along D; the row's along T1 and T2
+    unsigned o[K];   // byte offsets of the cells (mapped into the box)
+    int c0;          // index of the first along D; out of the row: no output
   };
   auto load = [&](int win) {
     In in;
     const int pos = win * STEP + (lane - HL) * K;
-    int cp, y, z;
+    int cp, ra, ro;
     // positions before the stream or past it are moved onto it; they output nothing
-    rs.locate(min(max(pos, 0), npos - K), cp, y, z);
+    rs.locate(min(max(pos, 0), npos - K), cp, ra, ro);
     in.c0 = lane >= HL && lane < 64 - HR && pos < npos ? cp - OFF : -K;
-    const unsigned base = ((unsigned)z * plane_rows + (unsigned)y) * st1;
-    const unsigned dy = y + 1 < ny ? dy_in : dy_last, dz = z + 1 < nz ? dz_in : dz_last;
-    unsigned o[K], f[K];  // the cells and their low x faces
+    const unsigned base = (unsigned)ra * sA + (unsigned)ro * sO;
+    const int c1 = T1 == A ? ra : ro, c2 = T2 == A ? ra : ro;
+    const unsigned d1 = c1 + 1 < g.n[T1] ? up1 : last1, d2 = c2 + 1 < g.n[T2] ? up2 : last2;
+    unsigned f[K];  // the cells' low faces along D
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      o[j] = (base + (unsigned)map_cell_near(cp - OFF + j, nx, g.bc[0])) * z4;
-      f[j] = (base + (unsigned)map_face_near(cp - OFF + j, nx, g.bc[0])) * z4;
+      in.o[j] = base + (unsigned)map_cell_near(cp - OFF + j, n, bcD) * sD;
+      f[j] = base + (unsigned)map_face_near(cp - OFF + j, n, bcD) * sD;
     }
-    in.o = o[0];
-    // a pair is split only where the row's ghosts wrap or are copies
-    if (__all(o[1] == o[0] + z4 && f[1] == f[0] + z4)) {
+    const unsigned* o = in.o;
+    // along x a pair is split only where the row's ghosts wrap or are copies
+    if (D == 0 && __all(o[1] == o[0] + z4 && f[1] == f[0] + z4)) {
 #pragma unroll
       for (int i = 0; i < 5; ++i) ld2(a.u[i], o[0], in.u[0][i], in.u[1][i]);
-      ld2(a.b[0], f[0], in.bx[0], in.bx[1]);
-      ld2(a.b[1], o[0], in.by[0][0], in.by[1][0]);
-      ld2(a.b[1], o[0] + dy, in.by[0][1], in.by[1][1]);
-      ld2(a.b[2], o[0], in.bz[0][0], in.bz[1][0]);
-      ld2(a.b[2], o[0] + dz, in.bz[0][1], in.bz[1][1]);
+      ld2(a.b[D], f[0], in.bD[0], in.bD[1]);
+      ld2(a.b[T1], o[0], in.b1[0][0], in.b1[1][0]);
+      ld2(a.b[T1], o[0] + d1, in.b1[0][1], in.b1[1][1]);
+      ld2(a.b[T2], o[0], in.b2[0][0], in.b2[1][0]);
+      ld2(a.b[T2], o[0] + d2, in.b2[0][1], in.b2[1][1]);
     } else {
 #pragma unroll
       for (int j = 0; j < K; ++j) {
 #pragma unroll
         for (int i = 0; i < 5; ++i) in.u[j][i] = ld(a.u[i], o[j]);
-        in.bx[j] = ld(a.b[0], f[j]);
-        in.by[j][0] = ld(a.b[1], o[j]);
-        in.by[j][1] = ld(a.b[1], o[j] + dy);
-        in.bz[j][0] = ld(a.b[2], o[j]);
-        in.bz[j][1] = ld(a.b[2], o[j] + dz);
+        in.bD[j] = ld(a.b[D], f[j]);
+        in.b1[j][0] = ld(a.b[T1], o[j]);
+        in.b1[j][1] = ld(a.b[T1], o[j] + d1);
+        in.b2[j][0] = ld(a.b[T2], o[j]);
+        in.b2[j][1] = ld(a.b[T2], o[j] + d2);
       }
     }
 #pragma unroll
     for (int j = 0; j < K; ++j) {
       const int c = cp - OFF + j;
-      in.phi[j] = GRAV ? load_phi(a.phi, (long long)base, 1, c, nx, g.bc[0]) : T(0);
-      if (NU) in.w[j] = width_at(a.wid[0], c, nx, g.bc[0]);
+      const long long row = base / z4, st = g.st[D];
+      in.phi[j] = GRAV ? load_phi(a.phi, row, st, c, n, bcD) : T(0);
+      if (NU) in.w[j] = width_at(a.wid[D], c, n, bcD);
       if (GRAV == 2) {
         // the kick of the cell this position maps to (a ghost is exactly the
         // copy of its kicked cell)
-        const int cm = map_cell(c, nx, g.bc[0]);
-        const T isp0 = NU ? inv_span(width_at(a.wid[0], cm - 1, nx, g.bc[0]), width_at(a.wid[0], cm, nx, g.bc[0]),
-                                     width_at(a.wid[0], cm + 1, nx, g.bc[0]))
+        const int cm = map_cell(c, n, bcD);
+        const T isp0 = NU ? inv_span(width_at(a.wid[D], cm - 1, n, bcD), width_at(a.wid[D], cm, n, bcD),
+                                     width_at(a.wid[D], cm + 1, n, bcD))
                           : k.inv2h;
-        in.gh[j] = k.half_dt * (load_phi(a.phi, (long long)base, 1, cm + 1, nx, g.bc[0]) -
-                                load_phi(a.phi, (long long)base, 1, cm - 1, nx, g.bc[0])) * isp0;
+        in.gh[j] = k.half_dt * (load_phi(a.phi, row, st, cm + 1, n, bcD) - load_phi(a.phi, row, st, cm - 1, n, bcD)) *
+                   isp0;
       } else {
         in.gh[j] = T(0);
       }
     }
-    if (NU) {
-      in.wy = width_at(a.wid[1], y, ny, g.bc[1]);
-      in.wz = width_at(a.wid[2], z, nz, g.bc[2]);
+    if (NU && CFL) {
+      in.wt[0] = width_at(a.wid[T1], c1, g.n[T1], g.bc[T1]);
+      in.wt[1] = width_at(a.wid[T2], c2, g.n[T2], g.bc[T2]);
     }
     return in;
   };
   auto compute = [&](const In& in) {
-    T bxr[K], un[K][5], bc[K][3];
-    from_right(in.bx, bxr);
+    T bDr[K], un[K][5], bc[K][3];
+    from_right(in.bD, bDr);
     FieldQ<T> f[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      bc[j][0] = T(0.5) * (in.bx[j] + bxr[j]);
-      bc[j][1] = T(0.5) * (in.by[j][0] + in.by[j][1]);
-      bc[j][2] = T(0.5) * (in.bz[j][0] + in.bz[j][1]);
+      bc[j][D] = T(0.5) * (in.bD[j] + bDr[j]);
+      bc[j][T1] = T(0.5) * (in.b1[j][0] + in.b1[j][1]);
+      bc[j][T2] = T(0.5) * (in.b2[j][0] + in.b2[j][1]);
       f[j] = field_quantities<T>(bc[j]);
     }
     CellNU<T> nu[K]{};
@@ -1060,21 +1063,25 @@ __global__ __launch_bounds__(256) void fluid_lanes_kernel(FluidLaunch<T> FL) {
 #pragma unroll
       for (int j = 0; j < K; ++j) nu[j] = cell_nu(wl[j], in.w[j], wr[j], k.dt);
     }
-    fluid_window<T, GRAV, HSE, LIM, NU, K>(in.u, f, in.phi, in.gh, nu, k, un);
+    fluid_window<T, D, GRAV, HSE, LIM, NU, K>(in.u, f, in.phi, in.gh, nu, k, un);
     // OFF is a multiple of K, so a row's cell 0 is the first of its lane, and
     // only the last lane of a row can hold a single cell of it
-    const bool out[K] = {(unsigned)in.c0 < (unsigned)nx, in.c0 >= 0 && in.c0 + 1 < nx};
+    const bool out[K] = {(unsigned)in.c0 < (unsigned)n, in.c0 >= 0 && in.c0 + 1 < n};
     if (out[1]) {
-      if (FL.wl.stream) {
 #pragma unroll
-        for (int i = 0; i < 5; ++i) st2_once(a.uo[i], in.o, un[0][i], un[1][i]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 5; ++i) st2(a.uo[i], in.o, un[0][i], un[1][i]);
+      for (int i = 0; i < 5; ++i) {
+        if (D != 0) {
+          st(a.uo[i], in.o[0], un[0][i]);
+          st(a.uo[i], in.o[1], un[1][i]);
+        } else if (FL.wl.stream) {
+          st2_once(a.uo[i], in.o[0], un[0][i], un[1][i]);
+        } else {
+          st2(a.uo[i], in.o[0], un[0][i], un[1][i]);
+        }
       }
     } else if (out[0]) {
 #pragma unroll
-      for (int i = 0; i < 5; ++i) st(a.uo[i], in.o, un[0][i]);
+      for (int i = 0; i < 5; ++i) st(a.uo[i], in.o[0], un[0][i]);
     }
     if (CFL) {
 #pragma unroll
@@ -1084,7 +1091,7 @@ __global__ __launch_bounds__(256) void fluid_lanes_kernel(FluidLaunch<T> FL) {
         cell_cfl_speeds<T>(un[j], bc[j], a.gamma, g, sp, cell_bad);
         if (out[j]) {
           if (NU) {
-            cnu = fmax(cnu, cfl_of_cell(sp, (double)in.w[j], (double)in.wy, (double)in.wz, g));
+            cnu = fmax(cnu, cfl_of_cell(sp, (double)in.w[j], (double)in.wt[0], (double)in.wt[1], g));
           } else {
 #pragma unroll
             for (int dd = 0; dd < 3; ++dd) smax[dd] = fmax(smax[dd], sp[dd]);
@@ -1581,9 +1588,11 @@ __device__ __forceinline__ void face_row(const T (&w)[K], const T (&b)[K], const
   }
 }
 
-template <typename T, int LIM, bool NU>
+template <typename T, int D, int LIM, bool NU>
 __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
   constexpr int K = 2;
+  constexpr int A = D == 0 ? 1 : 0;  // rows: A fast
+  constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
   // an output depends on 4 cells either side
   constexpr int H = (4 + K - 1) / K;
   constexpr int OFF = H * K;               // position of a row's cell 0
@@ -1591,30 +1600,30 @@ __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
   constexpr unsigned z4 = sizeof(T);
   const BoxDesc* d;
   int lw;
-  if (!work_item<K_FIELD_X>(FL.wl, d, lw)) return;
-  const FieldArgs<T> a = field_view<T, K_FIELD_X>(FL, *d);
+  if (!work_item<K_FIELD_X + D>(FL.wl, d, lw)) return;
+  const FieldArgs<T> a = field_view<T, K_FIELD_X + D>(FL, *d);
   const Geo& g = a.g;
-  const int nx = g.n[0], n1 = g.n[1], n2 = g.n[2];
-  const bool outx = g.bc[0] == 1;
-  const int ry = n1 + g.bc[1], rz = n2 + g.bc[2];  // face rows
-  const int nrows = ry * rz;
+  const int n = g.n[D], bcD = g.bc[D], n1 = g.n[T1], n2 = g.n[T2];
+  const int r1 = n1 + g.bc[T1], r2 = n2 + g.bc[T2];  // face rows
+  const int nrows = r1 * r2;
   const int rpw = a.rows_per_wave;
   RowStream rs;
-  rs.init(lw, (nrows + rpw - 1) / rpw, rpw, (nx + 2 * OFF + K - 1) / K * K, ry, nrows);
+  rs.init(lw, (nrows + rpw - 1) / rpw, rpw, (n + 2 * OFF + K - 1) / K * K, T1 == A ? r1 : r2, nrows);
   const int npos = rs.rows * rs.L;
   const int lane = threadIdx.x & 63;
-  const FieldConsts<T> k = field_consts<T, 0>(a);
-  // byte offsets to the cells and faces beside a row along y and z: inside the
-  // box one row, at its ends the wrap (periodic) or the copy (outflow); all in
-  // unsigned arithmetic, where a negative offset wraps and wraps back
-  const unsigned s1 = (unsigned)g.st[1] * z4, s2 = (unsigned)g.st[2] * z4;
-  const unsigned lo1 = g.bc[1] ? 0u : (unsigned)(n1 - 1) * s1, hi1 = 0u - lo1;
-  const unsigned lo2 = g.bc[2] ? 0u : (unsigned)(n2 - 1) * s2, hi2 = 0u - lo2;
+  const FieldConsts<T> k = field_consts<T, D>(a);
+  // byte offsets to the cells and faces beside a row along T1 and T2: inside
+  // the box one row, at its ends the wrap (periodic) or the copy (outflow); all
+  // in unsigned arithmetic, where a negative offset wraps and wraps back
+  const unsigned sD = (unsigned)g.st[D] * z4, s1 = (unsigned)g.st[T1] * z4, s2 = (unsigned)g.st[T2] * z4;
+  const unsigned lo1 = g.bc[T1] ? 0u : (unsigned)(n1 - 1) * s1, hi1 = 0u - lo1;
+  const unsigned lo2 = g.bc[T2] ? 0u : (unsigned)(n2 - 1) * s2, hi2 = 0u - lo2;
   for (int win = rs.turn; win * STEP < npos; win += rs.waves) {
     const int pos = win * STEP + (lane - H) * K;
-    int cp, y, z;
+    int cp, ra, ro;
     // positions before the stream or past it are moved onto it; they output nothing
-    rs.locate(min(max(pos, 0), npos - K), cp, y, z);
+    rs.locate(min(max(pos, 0), npos - K), cp, ra, ro);
+    const int y = T1 == A ? ra : ro, z = T1 == A ? ro : ra;  // the row's indices along T1 and T2
     const int c0 = lane >= H && lane < 64 - H && pos < npos ? cp - OFF : -K;
     const unsigned row = (unsigned)z * s2 + (unsigned)y * s1;
     // the row past an outflow axis's last cell has faces only: its cell is the last one
@@ -1624,18 +1633,18 @@ __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
     const unsigned c1p = end1 ? 0u : (y == n1 - 1 ? hi1 : s1);
     const unsigned c2m = end2 ? 0u : (z == 0 ? lo2 : 0u - s2);
     const unsigned c2p = end2 ? 0u : (z == n2 - 1 ? hi2 : s2);
-    const unsigned f1p = end1 ? 0u : (y == n1 - 1 && !g.bc[1] ? hi1 : s1);
-    const unsigned f2p = end2 ? 0u : (z == n2 - 1 && !g.bc[2] ? hi2 : s2);
-    unsigned x[K], xf[K];  // byte offsets in the row of the cells and of their low x faces
+    const unsigned f1p = end1 ? 0u : (y == n1 - 1 && !g.bc[T1] ? hi1 : s1);
+    const unsigned f2p = end2 ? 0u : (z == n2 - 1 && !g.bc[T2] ? hi2 : s2);
+    unsigned x[K], xf[K];  // byte offsets in the row of the cells and of their low faces along D
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      x[j] = (unsigned)map_cell_near(cp - OFF + j, nx, g.bc[0]) * z4;
-      xf[j] = (unsigned)map_face_near(cp - OFF + j, nx, g.bc[0]) * z4;
+      x[j] = (unsigned)map_cell_near(cp - OFF + j, n, bcD) * sD;
+      xf[j] = (unsigned)map_face_near(cp - OFF + j, n, bcD) * sD;
     }
     const unsigned c[5] = {own, own + c1m, own + c1p, own + c2m, own + c2p};
     T md[5][K], rho[5][K], b[4][K], bd[K];
-    // a pair is split only where the row's ghosts wrap or are copies
-    if (__all(x[1] == x[0] + z4 && xf[1] == xf[0] + z4)) {
+    // along x a pair is split only where the row's ghosts wrap or are copies
+    if (D == 0 && __all(x[1] == x[0] + z4 && xf[1] == xf[0] + z4)) {
 #pragma unroll
       for (int i = 0; i < 5; ++i) {
         ld2(a.md, c[i] + x[0], md[i][0], md[i][1]);
@@ -1664,12 +1673,12 @@ __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
     FieldRowNU<T> rn{};
     CellNU<T> nu[K]{};
     if (NU) {
-      rn = field_row_nu(width_at(a.wid[1], y - 1, n1, g.bc[1]), width_at(a.wid[1], y, n1, g.bc[1]),
-                        width_at(a.wid[1], y + 1, n1, g.bc[1]), width_at(a.wid[2], z - 1, n2, g.bc[2]),
-                        width_at(a.wid[2], z, n2, g.bc[2]), width_at(a.wid[2], z + 1, n2, g.bc[2]));
+      rn = field_row_nu(width_at(a.wid[T1], y - 1, n1, g.bc[T1]), width_at(a.wid[T1], y, n1, g.bc[T1]),
+                        width_at(a.wid[T1], y + 1, n1, g.bc[T1]), width_at(a.wid[T2], z - 1, n2, g.bc[T2]),
+                        width_at(a.wid[T2], z, n2, g.bc[T2]), width_at(a.wid[T2], z + 1, n2, g.bc[T2]));
       T w[K], wl[K], wr[K];
 #pragma unroll
-      for (int j = 0; j < K; ++j) w[j] = width_at(a.wid[0], cp - OFF + j, nx, g.bc[0]);
+      for (int j = 0; j < K; ++j) w[j] = width_at(a.wid[D], cp - OFF + j, n, bcD);
       from_left(w, wl);
       from_right(w, wr);
 #pragma unroll
@@ -1679,7 +1688,7 @@ __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
         nu[j].kf *= T(2);
       }
     }
-    T w[4][K];  // v_x on the y faces c1 and c1+1 and the z faces c2 and c2+1
+    T w[4][K];  // v_D on the t1-faces c1 and c1+1 and the t2-faces c2 and c2+1
 #pragma unroll
     for (int j = 0; j < K; ++j) {
       FieldIn<T> in;
@@ -1698,31 +1707,35 @@ __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
     face_row<T, LIM, false, NU>(w[1], b[1], k, nu, e[1], none);
     face_row<T, LIM, true, NU>(w[2], b[2], k, nu, e[2], bn2);
     face_row<T, LIM, false, NU>(w[3], b[3], k, nu, e[3], none);
-    // the change of b_x at the face right of the cell; a cell's own face is the
+    // the change of b_D at the face right of the cell; a cell's own face is the
     // one left of it
     T dr[K], dbd[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) dr[j] = field_change<T, NU>(e[0][j], e[1][j], e[2][j], e[3][j], k, rn);
     from_left(dr, dbd);
-    // cells [0, nx) of b_t, x faces [0, nx) of b_x and on an outflow axis face nx
+    // cells [0, n) of b_t, faces [0, n) of b_D and on an outflow axis face n
     const bool own1 = !end2, own2 = !end1;
-    const bool first = (unsigned)c0 < (unsigned)nx, both = c0 >= 0 && c0 + 1 < nx;
-    if (both && FL.wl.stream) {
-      if (own1) st2_once(a.bto[0], row + x[0], bn1[0], bn1[1]);
-      if (own2) st2_once(a.bto[1], row + x[0], bn2[0], bn2[1]);
-    } else if (both) {
-      if (own1) st2(a.bto[0], row + x[0], bn1[0], bn1[1]);
-      if (own2) st2(a.bto[1], row + x[0], bn2[0], bn2[1]);
-    } else if (first) {
+    auto put = [&](T* p, unsigned o0, unsigned o1, T v0, T v1) {
+      if (D != 0) {
+        st(p, o0, v0);
+        st(p, o1, v1);
+      } else if (FL.wl.stream) {
+        st2_once(p, o0, v0, v1);
+      } else {
+        st2(p, o0, v0, v1);
+      }
+    };
+    if (c0 >= 0 && c0 + 1 < n) {
+      if (own1) put(a.bto[0], row + x[0], row + x[1], bn1[0], bn1[1]);
+      if (own2) put(a.bto[1], row + x[0], row + x[1], bn2[0], bn2[1]);
+    } else if ((unsigned)c0 < (unsigned)n) {
       if (own1) st(a.bto[0], row + x[0], bn1[0]);
       if (own2) st(a.bto[1], row + x[0], bn2[0]);
     }
     if (own1 && own2) {
-      const int nf = nx + (outx ? 1 : 0);
-      if (c0 >= 0 && c0 + 1 < nf && FL.wl.stream)
-        st2_once(a.bdo, row + xf[0], bd[0] + dbd[0], bd[1] + dbd[1]);
-      else if (c0 >= 0 && c0 + 1 < nf)
-        st2(a.bdo, row + xf[0], bd[0] + dbd[0], bd[1] + dbd[1]);
+      const int nf = n + (bcD ? 1 : 0);
+      if (c0 >= 0 && c0 + 1 < nf)
+        put(a.bdo, row + xf[0], row + xf[1], bd[0] + dbd[0], bd[1] + dbd[1]);
       else if ((unsigned)c0 < (unsigned)nf)
         st(a.bdo, row + xf[0], bd[0] + dbd[0]);
     }
