@@ -15,9 +15,15 @@ template <typename T, int D, int GRAV, bool HSE, int LIM, bool NU>
 void fluid_kernel(const FluidLaunch<T>& L, bool cfl, bool x_strided, hipStream_t stream) {
   if (L.wl.nwaves == 0) return;
   const dim3 grid(grid_for((long long)L.wl.nwaves * 64));
+  // FP64 with gravity, HSE, an irregular mesh or the limiter switch: loading a
+  // position ahead takes the registers of a second wave per SIMD.  A launch
+  // with no second wave (1024 SIMDs) has them to spare (100x90x110 with the
+  // switch: step 399 -> 374 us), except with gravity, whose kernels would go
+  // through the accumulation registers (120^3 with gravity and HSE, split: 702 -> 750).
+  constexpr bool kHeavy = sizeof(T) == 8 && (GRAV != 0 || HSE || NU || LIM == 2);
   if constexpr (D == 0) {
     if (x_strided && !cfl)
-      hipLaunchKernelGGL((fluid_strided_kernel<T, 0, GRAV, HSE, LIM, NU, false>), grid, dim3(kBlock), 0, stream, L);
+      hipLaunchKernelGGL((fluid_strided_kernel<T, 0, GRAV, HSE, LIM, NU, false, !kHeavy>), grid, dim3(kBlock), 0, stream, L);
     else if (cfl)
       hipLaunchKernelGGL((fluid_lanes_kernel<T, 0, GRAV, HSE, LIM, true, NU>), grid, dim3(kBlock), 0, stream, L);
     else
@@ -31,11 +37,17 @@ void fluid_kernel(const FluidLaunch<T>& L, bool cfl, bool x_strided, hipStream_t
     // (FP64 with the limiter switch would lose half its waves)
     if constexpr (GRAV == 0 && !NU && LIM != 2) {
       if (L.wl.stream) {
-        hipLaunchKernelGGL((fluid_strided_kernel<T, D, GRAV, HSE, LIM, NU, true>), grid, dim3(kBlock), 0, stream, L);
+        hipLaunchKernelGGL((fluid_strided_kernel<T, D, GRAV, HSE, LIM, NU, true, true>), grid, dim3(kBlock), 0, stream, L);
         return;
       }
     }
-    hipLaunchKernelGGL((fluid_strided_kernel<T, D, GRAV, HSE, LIM, NU, false>), grid, dim3(kBlock), 0, stream, L);
+    constexpr bool kSpare = GRAV == 0 && !HSE;
+    if (!kHeavy || (kSpare && L.wl.nwaves <= 1024))
+      hipLaunchKernelGGL((fluid_strided_kernel<T, D, GRAV, HSE, LIM, NU, false, !kHeavy || kSpare>), grid,
+                         dim3(kBlock), 0, stream, L);
+    else
+      hipLaunchKernelGGL((fluid_strided_kernel<T, D, GRAV, HSE, LIM, NU, false, !kHeavy>), grid, dim3(kBlock), 0,
+                         stream, L);
   }
 }
 

@@ -483,7 +483,7 @@ __device__ __forceinline__ bool strided_map(int wave, int nA, int nO, int nseg, 
 // walk along x (each load of a wave is 64 consecutive values); for D = x (an
 // alternative to the lanes policy) they walk along y, so that a wave's load
 // touches 64 rows, one value of each.
-template <typename T, int D, int GRAV, bool HSE, int LIM, bool NU, bool ONCE>
+template <typename T, int D, int GRAV, bool HSE, int LIM, bool NU, bool ONCE, bool AHEAD>
 __global__ __launch_bounds__(256, sizeof(T) == 4 && GRAV == 0 && LIM != 2 && !NU ? 4 : 1) void fluid_strided_kernel(FluidLaunch<T> L) {
   constexpr int A = D == 0 ? 1 : 0;
   constexpr int O = D == 0 ? 2 : 3 - D;
@@ -569,9 +569,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && GRAV == 0 && LIM != 2 && !NU
   // positions s0-3 .. s1+2, padded to an even count (the pad writes nothing;
   // the prefetch reads at most two positions past the end, mapped in range)
   const int npos = (s1 - s0) + 6;
-  if (sizeof(T) == 8 && (GRAV != 0 || HSE || NU || LIM == 2)) {
-    // FP64 with gravity, HSE, an irregular mesh or the limiter switch: no
-    // lookahead; its registers would halve the waves per SIMD (to one)
+  if (!AHEAD) {
     for (int it = 0; it < npos; it += 2) {
       compute(it, load(it), hA, hB);
       compute(it + 1, load(it + 1), hB, hA);
