@@ -18,8 +18,8 @@ void fluid_kernel(const FluidLaunch<T>& L, bool cfl, bool x_strided, hipStream_t
   // FP64 with gravity, HSE, an irregular mesh or the limiter switch: loading a
   // position ahead takes the registers of a second wave per SIMD.  A launch
   // with no second wave (1024 SIMDs) has them to spare (100x90x110 with the
-  // switch: step 399 -> 374 us), except with gravity, whose kernels would go
-  // through the accumulation registers (120^3 with gravity and HSE, split: 702 -> 750).
+  // switch: step 399 -> 374 us); gravity gains nothing (120^3, HSE, split
+  // gravity: 704 either way).
   constexpr bool kHeavy = sizeof(T) == 8 && (GRAV != 0 || HSE || NU || LIM == 2);
   if constexpr (D == 0) {
     if (x_strided && !cfl)

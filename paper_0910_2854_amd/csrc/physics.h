@@ -219,13 +219,13 @@ __device__ __forceinline__ void dissipation(const CellQ<T, HSE>& L, const CellQ<
     const T avL = fabs(L.vd), avR = fabs(R.vd);
     const T dadv = speed_max(avL, avR);
     const T dac = speed_max(L.cF, R.cF);
-    const T scale = (phiR - phiL) * rcp(L.cS * R.cS);
+    const T scale = T(0.5) * ((phiR - phiL) * rcp(L.cS * R.cS));  // (exact: the mean of xi taken here)
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
       const T du = R.u[k] - L.u[k];
       const T xiL = (k == EN) ? L.xiE : -L.u[k];
       const T xiR = (k == EN) ? R.xiE : -R.u[k];
-      const T g = T(0.5) * (xiL + xiR) * scale;
+      const T g = (xiL + xiR) * scale;
       const T delta = minmod(du - g, du);
       Q[k] = dadv * du + dac * delta;
     }
