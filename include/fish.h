@@ -265,9 +265,8 @@ int fish_selftest_math(int device, int n, const double* x, double* rcp_out, doub
  * ignored; p->stream is the stream the work is enqueued on (NULL = default).
  * Asynchronous.  Irregular meshes are not available here.
  *
- * Scratch: the step's box table, step scalars and work lists live in one
- * static device array of FISH_NOALLOC_SCRATCH_BYTES on each GPU the call
- * runs on, held until the process ends and found at the first call on that
+ * Scratch: the step's box table and step scalars live in one static device
+ * array of FISH_NOALLOC_SCRATCH_BYTES on each GPU the call runs on, held until the process ends and found at the first call on that
  * GPU.  Every call on a GPU uses the same array, and each call rewrites what
  * it reads: calls in stream order are independent, calls that overlap on one
  * GPU (two host threads, two streams) race and give wrong results.  A box
@@ -282,7 +281,7 @@ int fish_selftest_math(int device, int n, const double* x, double* rcp_out, doub
  * non-finite value, before or after the step) is reported in the report,
  * not by the return value.  The caller's current device is restored. */
 #define FISH_NOALLOC_MAX_WAVES (1 << 20)
-#define FISH_NOALLOC_SCRATCH_BYTES (2048 + 4 * FISH_NOALLOC_MAX_WAVES)
+#define FISH_NOALLOC_SCRATCH_BYTES 2048
 
 typedef struct fish_step_report {
   double dt;       /* the step size of every sub-operator (0 for a state refused before the step) */

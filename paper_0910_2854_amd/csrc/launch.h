@@ -9,8 +9,6 @@
 
 namespace fish {
 
-constexpr int kBlock = 256;
-
 inline unsigned grid_for(long long threads) { return (unsigned)((threads + kBlock - 1) / kBlock); }
 
 #define HIP_TRY(expr)                                                                   \
@@ -39,6 +37,8 @@ inline WorkList make_wl(const Engine* e, int kind) {
   WorkList w;
   w.boxes = static_cast<const BoxDesc*>(e->table.ptr);
   w.wave_box = static_cast<const int*>(e->lists[kind].ptr);
+  w.one = e->table_slots.size() == 1;
+  w.slot = w.one ? e->table_slots[0] : 0;
   w.nwaves = e->nwaves[kind];
   w.xcd_remap = e->tuning.remap[kind];
   w.row_groups = e->tuning.groups[kind];

@@ -55,9 +55,16 @@ inline bool stream_rule(long long bytes, long long row_bytes) {
   return row_bytes % 128 == 0 && bytes > (384ll << 20);
 }
 
+// Threads and waves of a block of every launch over a work list: constants,
+// since the block and grid size of a running kernel are loads of its own.
+constexpr int kBlock = 256;
+constexpr int kBlockWaves = kBlock / 64;
+
 struct WorkList {
   const BoxDesc* boxes;
-  const int* wave_box;  // table index of the box of every wave
+  const int* wave_box;  // table index of the box of every wave (not read with one)
+  int one;              // 1: the table is one box, with its Scalars at slot (see work_item)
+  int slot;
   int nwaves;
   int xcd_remap;        // 1: consecutive blocks of the list run on one XCD (see list_block)
   int reverse;          // 1: the blocks run from the last to the first (see list_block)

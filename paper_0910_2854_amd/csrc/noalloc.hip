@@ -1,7 +1,7 @@
 // noalloc.hip -- the double step of Eqs. (12)-(13) on a box whose state the
 // caller holds in device memory, with no context and no device allocation:
-// the box table, the step scalars and the work lists live in one static
-// device array per GPU (`scratch`), and the sweeps ping-pong between the
+// the box table and the step scalars live in one static device array per GPU
+// (`scratch`), and the sweeps ping-pong between the
 // caller's state and work arrays.  The kernels are the engine's (launch_api.h).
 #include <hip/hip_runtime.h>
 
@@ -18,14 +18,12 @@
 namespace fish {
 namespace {
 
-// scratch: [0, 1 KiB) the box's BoxDesc, [1 KiB, 2 KiB) its Scalars, then the
-// work list shared by every kind (all zeros: every wave belongs to box 0).
+// scratch: [0, 1 KiB) the box's BoxDesc, [1 KiB, 2 KiB) its Scalars.
 constexpr size_t kTableOff = 0;
 constexpr size_t kScalOff = 1024;
-constexpr size_t kListOff = 2048;
-constexpr size_t kScratchBytes = kListOff + sizeof(int) * (size_t)FISH_NOALLOC_MAX_WAVES;
+constexpr size_t kScratchBytes = 2048;
 static_assert(sizeof(BoxDesc) <= kScalOff - kTableOff, "BoxDesc outgrows its scratch slot");
-static_assert(sizeof(Scalars) <= kListOff - kScalOff, "Scalars outgrow their scratch slot");
+static_assert(sizeof(Scalars) <= kScratchBytes - kScalOff, "Scalars outgrow their scratch slot");
 static_assert(kScratchBytes == FISH_NOALLOC_SCRATCH_BYTES, "scratch size differs from the header's");
 
 // One copy per GPU the library runs on, held until the process ends.  Host
@@ -54,21 +52,19 @@ int scratch_on(int device, void** out, std::string* msg) {
   return FISH_OK;
 }
 
-// The box's table entry and step scalars, and zeros over the first nzero
-// entries of the work list (the previous call may have used fewer).
-__global__ __launch_bounds__(256) void noalloc_setup_kernel(BoxDesc desc, BoxDesc* table, Scalars* sc, int* list,
-                                                            int nzero) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) {
-    *table = desc;
-    Scalars s;
-    s.dt = s.t = s.t_end = 0.0;
-    s.cmax_bits = 0ull;
-    s.status = s.has_end = s.taken = s.pad = 0;
-    for (int d = 0; d < 3; ++d) s.kh[d] = s.kf[d] = 0.0;
-    *sc = s;
-  }
-  for (int w = i; w < nzero; w += gridDim.x * blockDim.x) list[w] = 0;
+// The box's table entry and step scalars, at the start of a step of size dt; with
+// dt = 0 launch_begin_step starts the step when the CFL speed is known.
+__global__ void noalloc_setup_kernel(BoxDesc desc, BoxDesc* table, Scalars* sc, double dt) {
+  if (threadIdx.x != 0) return;
+  *table = desc;
+  Scalars s;
+  s.t_end = 0.0;
+  s.cmax_bits = 0ull;
+  s.status = s.has_end = s.pad = 0;
+  set_step(&s, desc.g, dt);
+  s.t = 2.0 * dt;
+  s.taken = dt > 0.0;
+  *sc = s;
 }
 
 // The step size taken, the CFL step of the new state (Eq. 14; the CFL speed
@@ -93,7 +89,6 @@ struct Step {
   double gamma = 0.0, alpha = 0.0;
   const BoxDesc* table = nullptr;
   Scalars* sc = nullptr;
-  const int* list = nullptr;
   long long waves[K_NUM] = {};
   bool lanes[K_NUM] = {};
   int n[3] = {};
@@ -104,7 +99,9 @@ struct Step {
   WorkList wl(int kind) const {
     WorkList w;
     w.boxes = table;
-    w.wave_box = list;
+    w.wave_box = nullptr;
+    w.one = 1;
+    w.slot = 0;
     w.nwaves = (int)waves[kind];
     w.xcd_remap = tuning.remap[kind];
     w.row_groups = 0;
@@ -178,8 +175,8 @@ struct Step {
     }                                                                                  \
   } while (0)
 
-// The launches of one double step: the step size (given, or the CFL step of
-// the state: its CFL speed reduced by the check kernel, then dt = k / C, with
+// The launches of one double step: the step size (given to the setup kernel, or
+// the CFL step of the state: its CFL speed reduced by the check kernel, then dt = k / C, with
 // the maximum cleared for the last sweep), the twelve sub-operators in
 // symmetric order with the CFL speed of the new state reduced by the last
 // one, and the report.
@@ -188,9 +185,9 @@ int enqueue(Step<T>& s, double dt, fish_step_report* report, std::string* msg) {
   if (dt == 0.0) {
     s.check();
     LAUNCHED();
+    launch_begin_step(s.table, 1, s.sc, dt, s.sel.stream);
+    LAUNCHED();
   }
-  launch_begin_step(s.table, 1, s.sc, dt, s.sel.stream);
-  LAUNCHED();
   s.template fluid<0>(false);
   LAUNCHED();
   s.template field<0>();
@@ -263,7 +260,7 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
   long long most = 0;
   for (int k = 0; k < K_NUM; ++k) most = waves[k] > most ? waves[k] : most;
   if (most > FISH_NOALLOC_MAX_WAVES) {
-    *msg = "the box needs " + std::to_string(most) + " wavefronts in one launch; the scratch holds " +
+    *msg = "the box needs " + std::to_string(most) + " wavefronts in one launch; the most is " +
            std::to_string(FISH_NOALLOC_MAX_WAVES);
     return FISH_ERR_UNSUPPORTED;
   }
@@ -305,10 +302,7 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
     const hipStream_t stream = static_cast<hipStream_t>(p->stream);
     BoxDesc* table = reinterpret_cast<BoxDesc*>(s8 + kTableOff);
     Scalars* sc = reinterpret_cast<Scalars*>(s8 + kScalOff);
-    int* list = reinterpret_cast<int*>(s8 + kListOff);
-    const int nzero = (int)most;
-    const unsigned blocks = (unsigned)std::max<long long>(1, std::min<long long>(1024, (most + 255) / 256));
-    hipLaunchKernelGGL(noalloc_setup_kernel, dim3(blocks), dim3(256), 0, stream, d, table, sc, list, nzero);
+    hipLaunchKernelGGL(noalloc_setup_kernel, dim3(1), dim3(64), 0, stream, d, table, sc, dt);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
       *msg = std::string("kernel launch: ") + hipGetErrorString(e);
@@ -324,7 +318,6 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
       st.alpha = p->predictor_alpha;
       st.table = table;
       st.sc = sc;
-      st.list = list;
       for (int k = 0; k < K_NUM; ++k) {
         st.waves[k] = waves[k];
         st.lanes[k] = lanes[k];
@@ -347,7 +340,6 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
       st.alpha = p->predictor_alpha;
       st.table = table;
       st.sc = sc;
-      st.list = list;
       for (int k = 0; k < K_NUM; ++k) {
         st.waves[k] = waves[k];
         st.lanes[k] = lanes[k];

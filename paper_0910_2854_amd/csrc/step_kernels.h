@@ -8,18 +8,6 @@
 
 namespace fish {
 
-// The step size of every sub-operator and the factors the sweeps take from
-// it, dt / (2 h_d) and dt / h_d per axis (evaluated once per step, not in
-// every wave of every sweep).
-__device__ __forceinline__ void set_step(Scalars* s, const Geo& g, double dt) {
-  s->dt = dt;
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    s->kh[d] = dt / (2.0 * g.h[d]);
-    s->kf[d] = dt / g.h[d];
-  }
-}
-
 // Per-box step scalars; one thread per box of the table.
 __global__ void reset_cmax_kernel(const BoxDesc* boxes, int nb, Scalars* sc) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;

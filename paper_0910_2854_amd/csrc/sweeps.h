@@ -46,22 +46,52 @@ namespace fish {
 // before it left in the 256 MB cache of the memory (256^3 step, FP32 2.09 ->
 // 2.05 ms, FP64 4.00 -> 3.97 ms).
 __device__ __forceinline__ int list_block(const WorkList& wl) {
+  const int blocks = (wl.nwaves + kBlockWaves - 1) / kBlockWaves;  // the grid of every launch over a list
   int b = (int)blockIdx.x;
-  if (wl.reverse) b = (int)gridDim.x - 1 - b;
+  if (wl.reverse) b = blocks - 1 - b;
   if (wl.xcd_remap) {
-    const int q = (int)gridDim.x >> 3;
+    const int q = blocks >> 3;
     if (b < (q << 3)) b = (b & 7) * q + (b >> 3);
   }
   return b;
 }
 
-template <int KIND>
-__device__ __forceinline__ bool work_item(const WorkList& wl, const BoxDesc*& d, int& lw) {
+// The wave's box.  What a wave loads before its first data are scalar loads that
+// miss, each a microsecond or less, and the sweep of a small box lasts five of
+// them: so few of them wait for one another.  The launch's arguments (lines of 64
+// bytes in host memory) are loaded together by touch(); a table of one box needs
+// no look-up of the wave's box before its entry, nor of the entry before its step
+// scalars; and the entry's lines and the step scalars are loaded together.  A
+// double step before and after: 16^3 FP64 70 -> 60 us (with the launches of the
+// start of the step merged), 32^3 FP32 82 -> 77, 64^3 FP32 160 -> 154, 203x77x131
+// FP32 326 -> 312.  The entry among the arguments: 65, 80, 159, 318.
+__device__ __forceinline__ int scalars_slot(const WorkList& wl, const BoxDesc& d) {
+  int slot = wl.slot;
+  if (!wl.one) {
+    slot = d.slot;
+    asm("" : "+s"(slot));
+  }
+  return slot;
+}
+
+template <int KIND, typename L>
+__device__ __forceinline__ bool work_item(const L& launch, const BoxDesc*& d, int& lw) {
+  const WorkList& wl = launch.wl;
   const int wave =
-      __builtin_amdgcn_readfirstlane((int)((list_block(wl) * blockDim.x + threadIdx.x) >> 6));
-  if (wave >= wl.nwaves) return false;
-  d = wl.boxes + wl.wave_box[wave];
-  lw = wave - d->wave0[KIND];
+      __builtin_amdgcn_readfirstlane((int)((list_block(wl) * kBlock + (int)threadIdx.x) >> 6));
+  int nwaves = wl.nwaves;
+  touch(launch, nwaves);
+  if (wave >= nwaves) return false;
+  int box = 0;
+  if (!wl.one) {
+    box = wl.wave_box[wave];
+    asm("" : "+s"(box));  // (a branch: as a select it would wait for the load)
+  }
+  d = wl.boxes + box;
+  const Scalars* sc = launch.sc + scalars_slot(wl, *d);
+  int first = d->wave0[KIND];
+  asm("" : "+s"(first) : "s"(d->g.n[0]), "s"(d->ih[0]), "s"(sc->dt), "s"(sc->kf[0]));
+  lw = wave - first;
   return true;
 }
 
@@ -200,6 +230,13 @@ struct FluidLaunch {
   Scalars* sc;
 };
 
+// The arguments' lines (64 bytes each), loaded together with the first: x is
+// what the kernel needs first.
+template <typename T>
+__device__ __forceinline__ void touch(const FluidLaunch<T>& L, int& x) {
+  asm("" : "+s"(x) : "s"(L.u[0]), "s"(L.b[0]), "s"(L.sc));
+}
+
 // The per-box view of a launch (pointers at the box, its geometry and step
 // scalars).
 template <typename T, int KIND>
@@ -223,7 +260,7 @@ __device__ __forceinline__ FluidArgs<T> fluid_view(const FluidLaunch<T>& L, cons
   a.seg = d.par[KIND];
   a.nseg = d.nseg[KIND];
   a.rows_per_wave = d.par[KIND];
-  a.sc = L.sc + d.slot;
+  a.sc = L.sc + scalars_slot(L.wl, d);
 #pragma unroll
   for (int i = 0; i < 3; ++i) a.i2h[i] = d.i2h[i];
   (void)D;
@@ -430,6 +467,18 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
 
 // The step factors of a sweep along D: dt / (2h) and dt / h from the box's
 // step scalars (evaluated once per step with dt), 1 / (2h) from its table entry.
+// The step size of every sub-operator and the factors the sweeps take from
+// it, dt / (2 h_d) and dt / h_d per axis (evaluated once per step, not in
+// every wave of every sweep).
+__device__ __forceinline__ void set_step(Scalars* s, const Geo& g, double dt) {
+  s->dt = dt;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    s->kh[d] = dt / (2.0 * g.h[d]);
+    s->kf[d] = dt / g.h[d];
+  }
+}
+
 template <typename T>
 __device__ __forceinline__ FluidConsts<T> fluid_consts(const FluidArgs<T>& a, int D) {
   const double dt = a.sc->dt;
@@ -490,7 +539,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && GRAV == 0 && LIM != 2 && !NU
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
   const BoxDesc* d;
   int lw;
-  if (!work_item<K_FLUID_X + D>(L.wl, d, lw)) return;
+  if (!work_item<K_FLUID_X + D>(L, d, lw)) return;
   const FluidArgs<T> a = fluid_view<T, K_FLUID_X + D>(L, *d);
   const Geo& g = a.g;
   const int nA = g.n[A], nO = g.n[O], nD = g.n[D];
@@ -663,9 +712,9 @@ __device__ __forceinline__ void publish_cfl(double cmax, int bad, Scalars* sc, c
     bad |= __shfl_xor(bad, off, 64);
   }
   if ((threadIdx.x & 63) != 0) return;
-  const int w0 = list_block(wl) * ((int)blockDim.x >> 6);  // the block's waves w0 .. w1
-  const int w1 = min(w0 + ((int)blockDim.x >> 6), wl.nwaves) - 1;
-  if (wl.wave_box[w0] == wl.wave_box[w1]) {  // boxes are consecutive in the list
+  const int w0 = list_block(wl) * kBlockWaves;  // the block's waves w0 .. w1
+  const int w1 = min(w0 + kBlockWaves, wl.nwaves) - 1;
+  if (wl.one || wl.wave_box[w0] == wl.wave_box[w1]) {  // boxes are consecutive in the list
     __hip_atomic_fetch_max(&sh->bits, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __hip_atomic_fetch_or(&sh->bad, bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (__hip_atomic_fetch_add(&sh->done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) != w1 - w0) return;
@@ -872,7 +921,7 @@ struct RowStream {
   __device__ void init(int lw, int box_waves, int rows_per_wave, int L_, int n_, int nrows) {
     const int in_block = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int g0 = max(lw - in_block, 0);
-    const int g1 = min(lw - in_block + (int)(blockDim.x >> 6), box_waves);
+    const int g1 = min(lw - in_block + kBlockWaves, box_waves);
     turn = lw - g0;
     waves = g1 - g0;
     first = g0 * rows_per_wave;
@@ -952,7 +1001,7 @@ __global__ __launch_bounds__(256) void fluid_lanes_kernel(FluidLaunch<T> FL) {
   if (CFL) cfl_shared_init(&sh);
   const BoxDesc* d;
   int lw;
-  if (!work_item<K_FLUID_X + D>(FL.wl, d, lw)) return;
+  if (!work_item<K_FLUID_X + D>(FL, d, lw)) return;
   const FluidArgs<T> a = fluid_view<T, K_FLUID_X + D>(FL, *d);
   const Geo& g = a.g;
   const int n = g.n[D], bcD = g.bc[D];
@@ -1139,6 +1188,10 @@ struct FieldLaunch {
   WorkList wl;
   Scalars* sc;
 };
+template <typename T>
+__device__ __forceinline__ void touch(const FieldLaunch<T>& L, int& x) {
+  asm("" : "+s"(x) : "s"(L.rho), "s"(L.sc));
+}
 
 template <typename T, int KIND>
 __device__ __forceinline__ FieldArgs<T> field_view(const FieldLaunch<T>& L, const BoxDesc& d) {
@@ -1159,7 +1212,7 @@ __device__ __forceinline__ FieldArgs<T> field_view(const FieldLaunch<T>& L, cons
   a.seg = d.par[KIND];
   a.nseg = d.nseg[KIND];
   a.rows_per_wave = d.par[KIND];
-  a.sc = L.sc + d.slot;
+  a.sc = L.sc + scalars_slot(L.wl, d);
 #pragma unroll
   for (int i = 0; i < 3; ++i) a.ih[i] = d.ih[i];
   (void)D;
@@ -1418,7 +1471,7 @@ __global__ __launch_bounds__(256) void field_strided_kernel(FieldLaunch<T> FL) {
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
   const BoxDesc* d;
   int lw;
-  if (!work_item<K_FIELD_X + D>(FL.wl, d, lw)) return;
+  if (!work_item<K_FIELD_X + D>(FL, d, lw)) return;
   const FieldArgs<T> a = field_view<T, K_FIELD_X + D>(FL, *d);
   const Geo& g = a.g;
   const int nD = g.n[D];
@@ -1598,7 +1651,7 @@ __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
   constexpr unsigned z4 = sizeof(T);
   const BoxDesc* d;
   int lw;
-  if (!work_item<K_FIELD_X + D>(FL.wl, d, lw)) return;
+  if (!work_item<K_FIELD_X + D>(FL, d, lw)) return;
   const FieldArgs<T> a = field_view<T, K_FIELD_X + D>(FL, *d);
   const Geo& g = a.g;
   const int n = g.n[D], bcD = g.bc[D], n1 = g.n[T1], n2 = g.n[T2];
@@ -1750,6 +1803,10 @@ struct CheckLaunch {
   WorkList wl;
   Scalars* sc;
 };
+template <typename T>
+__device__ __forceinline__ void touch(const CheckLaunch<T>& L, int& x) {
+  asm("" : "+s"(x) : "s"(L.u[0]), "s"(L.sc));
+}
 
 // Eq. (14)-(15) on the stored state: the CFL speed of every cell (the same
 // function, hence bitwise the same value, as the reduction fused into the
@@ -1762,7 +1819,7 @@ __global__ __launch_bounds__(256) void check_cfl_kernel(CheckLaunch<T> L) {
   cfl_shared_init(&sh);
   const BoxDesc* d;
   int lw;
-  if (!work_item<K_CHECK>(L.wl, d, lw)) return;
+  if (!work_item<K_CHECK>(L, d, lw)) return;
   const Geo g = d->g;
   const long long off = d->off;
   const int n0 = g.n[0], n1 = g.n[1], n2 = g.n[2];
@@ -1818,7 +1875,7 @@ __global__ __launch_bounds__(256) void check_cfl_kernel(CheckLaunch<T> L) {
       }
     }
   }
-  publish_cfl(nu ? cnu : cfl_of(smax, g), bad, L.sc + d->slot, L.wl, &sh);
+  publish_cfl(nu ? cnu : cfl_of(smax, g), bad, L.sc + scalars_slot(L.wl, *d), L.wl, &sh);
 }
 
 }  // namespace fish
