@@ -866,10 +866,11 @@ def summarize_trace(tag, outdir):
     lines += ["", f"fluid sweep class: {len(fl)} launches, average {sum(fl) / max(1, len(fl)):.1f} us",
               f"sum of kernel time per double step: {tot / nsteps:.1f} us; first dispatch to last, per double step: "
               f"{span / nsteps:.1f} us", "",
-              "Template arguments: fluid_lanes_kernel<T, GRAV, HSE, LIM, CFL, NU> (x sweep, DPP lane streaming; CFL = "
-              "the last L_x of a step with the fused CFL reduction); fluid_strided_kernel<T, D, GRAV, HSE, LIM, NU> "
-              "(y, z sweeps, and the x sweep on the strided policy); field_lanes_kernel<T, LIM, NU> (B_x); "
-              "field_strided_kernel<T, D, LIM, NU> (B_y, B_z)."]
+              "Template arguments: fluid_lanes_kernel<T, D, GRAV, HSE, LIM, CFL, NU, K> (x sweep, and y and z of small "
+              "boxes; K cells per lane; CFL = the last L_x of a step with the fused CFL reduction); "
+              "fluid_strided_kernel<T, D, GRAV, HSE, LIM, NU, ONCE, AHEAD> (y, z sweeps, and the x sweep on the "
+              "strided policy); field_lanes_kernel<T, D, LIM, NU, K> (B_x, as L_x); "
+              "field_strided_kernel<T, D, LIM, NU, ONCE> (B_y, B_z)."]
     with open(os.path.join(ROOT, "profiles", f"kernels_{tag}.txt"), "w") as f:
         f.write("\n".join(lines) + "\n")
     print("\n".join(lines[7:]))

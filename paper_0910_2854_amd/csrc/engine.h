@@ -91,6 +91,7 @@ class Engine {
   // the identity (every ghost is the cell itself, so every flux difference
   // and every potential difference is zero) and is not launched
   bool flat[3] = {false, false, false};
+  int longest[3] = {0, 0, 0};  // the largest table box's cells, per axis
   bool stream_sweeps = false;  // WorkList::stream of the table's boxes (stream_rule)
   bool reverse = false;        // WorkList::reverse of the next sweep
   bool lanes[K_NUM]{};         // WorkList::lanes of the table's lists

@@ -794,7 +794,7 @@ static long long lane_rows(const HostBox& b, int kind) {
 // Whether a y/z kind takes the lanes policy: for boxes so small that a launch
 // lasts as long as one wave's walk, which lanes along the sweep shorten to a
 // window or two, and their uncoalesced accesses stay in the caches.  Double
-// step, FP32, walks -> lanes: 32^3 113 -> 83 us (16^3 FP64 115 -> 70), 40^3 123
+// step, FP32, walks -> lanes of two cells: 32^3 113 -> 83 us (16^3 FP64 115 -> 70), 40^3 123
 // -> 106, 48^3 128 -> 128, 56^3 147 -> 163, 64^3 161 -> 217.
 static bool planned_lanes(const std::vector<const HostBox*>& boxes, int kind) {
   if (kind == K_FLUID_X || kind == K_FIELD_X || kind == K_CHECK) return false;
@@ -912,7 +912,11 @@ int Engine::build_lists() {
   for (int s : slots) stream_sweeps = stream_sweeps && stream_rule(bytes, boxes[s].st[1] * (long long)esize);
   for (int a = 0; a < 3; ++a) {
     flat[a] = nb > 0;
-    for (int s : slots) flat[a] = flat[a] && boxes[s].n[a] == 1;
+    longest[a] = 0;
+    for (int s : slots) {
+      flat[a] = flat[a] && boxes[s].n[a] == 1;
+      longest[a] = std::max(longest[a], boxes[s].n[a]);
+    }
   }
   // the spare set is written once every launch that read it has completed
   HIP_TRY(hipEventSynchronize(spare.done));

@@ -45,6 +45,7 @@ inline WorkList make_wl(const Engine* e, int kind) {
   w.reverse = e->reverse;
   w.stream = e->stream_sweeps;
   w.lanes = e->lanes[kind];
+  w.narrow = narrow_rule(w.nwaves, e->longest[kind_axis(kind)]);
   return w;
 }
 

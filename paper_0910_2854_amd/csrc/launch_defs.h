@@ -24,13 +24,20 @@ void fluid_kernel(const FluidLaunch<T>& L, bool cfl, bool x_strided, hipStream_t
   if constexpr (D == 0) {
     if (x_strided && !cfl)
       hipLaunchKernelGGL((fluid_strided_kernel<T, 0, GRAV, HSE, LIM, NU, false, !kHeavy>), grid, dim3(kBlock), 0, stream, L);
+    else if (cfl && L.wl.narrow)
+      hipLaunchKernelGGL((fluid_lanes_kernel<T, 0, GRAV, HSE, LIM, true, NU, 1>), grid, dim3(kBlock), 0, stream, L);
     else if (cfl)
-      hipLaunchKernelGGL((fluid_lanes_kernel<T, 0, GRAV, HSE, LIM, true, NU>), grid, dim3(kBlock), 0, stream, L);
+      hipLaunchKernelGGL((fluid_lanes_kernel<T, 0, GRAV, HSE, LIM, true, NU, 2>), grid, dim3(kBlock), 0, stream, L);
+    else if (L.wl.narrow)
+      hipLaunchKernelGGL((fluid_lanes_kernel<T, 0, GRAV, HSE, LIM, false, NU, 1>), grid, dim3(kBlock), 0, stream, L);
     else
-      hipLaunchKernelGGL((fluid_lanes_kernel<T, 0, GRAV, HSE, LIM, false, NU>), grid, dim3(kBlock), 0, stream, L);
+      hipLaunchKernelGGL((fluid_lanes_kernel<T, 0, GRAV, HSE, LIM, false, NU, 2>), grid, dim3(kBlock), 0, stream, L);
   } else {
     if (L.wl.lanes) {
-      hipLaunchKernelGGL((fluid_lanes_kernel<T, D, GRAV, HSE, LIM, false, NU>), grid, dim3(kBlock), 0, stream, L);
+      if (L.wl.narrow)
+        hipLaunchKernelGGL((fluid_lanes_kernel<T, D, GRAV, HSE, LIM, false, NU, 1>), grid, dim3(kBlock), 0, stream, L);
+      else
+        hipLaunchKernelGGL((fluid_lanes_kernel<T, D, GRAV, HSE, LIM, false, NU, 2>), grid, dim3(kBlock), 0, stream, L);
       return;
     }
     // the plain scheme only: the other variants have no registers to spare
@@ -85,10 +92,15 @@ void field_kernel(const SweepSel& s, const FieldLaunch<T>& L) {
   if (L.wl.nwaves == 0) return;
   const dim3 grid(grid_for((long long)L.wl.nwaves * 64));
   if constexpr (D == 0) {
-    hipLaunchKernelGGL((field_lanes_kernel<T, 0, LIM, NU>), grid, dim3(kBlock), 0, s.stream, L);
+    if (L.wl.narrow)
+      hipLaunchKernelGGL((field_lanes_kernel<T, 0, LIM, NU, 1>), grid, dim3(kBlock), 0, s.stream, L);
+    else
+      hipLaunchKernelGGL((field_lanes_kernel<T, 0, LIM, NU, 2>), grid, dim3(kBlock), 0, s.stream, L);
   } else {
-    if (L.wl.lanes)
-      hipLaunchKernelGGL((field_lanes_kernel<T, D, LIM, NU>), grid, dim3(kBlock), 0, s.stream, L);
+    if (L.wl.lanes && L.wl.narrow)
+      hipLaunchKernelGGL((field_lanes_kernel<T, D, LIM, NU, 1>), grid, dim3(kBlock), 0, s.stream, L);
+    else if (L.wl.lanes)
+      hipLaunchKernelGGL((field_lanes_kernel<T, D, LIM, NU, 2>), grid, dim3(kBlock), 0, s.stream, L);
     else if (L.wl.stream)
       hipLaunchKernelGGL((field_strided_kernel<T, D, LIM, NU, true>), grid, dim3(kBlock), 0, s.stream, L);
     else

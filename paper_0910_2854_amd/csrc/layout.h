@@ -60,6 +60,17 @@ inline bool stream_rule(long long bytes, long long row_bytes) {
 constexpr int kBlock = 256;
 constexpr int kBlockWaves = kBlock / 64;
 
+// Whether the lanes policy gives a lane one cell of a row instead of two
+// (WorkList::narrow): with no second wave for a SIMD (1024) a launch lasts as
+// long as one window, which it halves, if a row still fits one (64 lanes with
+// halos of 4).  Double step, two cells -> one: 16^3 FP64 59.5 -> 53.3 us, 24^3 74
+// -> 66, 32^3 FP32 77.7 -> 71.8; but 40^3 (1600 waves) 97 -> 99 in y and z.
+inline bool narrow_rule(long long waves, int longest_row) { return waves <= 1024 && longest_row <= 56; }
+// The axis of a sweep kind's rows (0 for the check).
+inline int kind_axis(int kind) {
+  return kind >= K_FIELD_X && kind <= K_FIELD_Z ? kind - K_FIELD_X : kind <= K_FLUID_Z ? kind - K_FLUID_X : 0;
+}
+
 struct WorkList {
   const BoxDesc* boxes;
   const int* wave_box;  // table index of the box of every wave (not read with one)
@@ -71,6 +82,7 @@ struct WorkList {
   int stream;           // 1: what a sweep reads or writes once passes the caches by (see ld_once)
   int row_groups;       // y/z kinds: 1 = a block's waves on consecutive rows (see strided_map)
   int lanes;            // y/z kinds: 1 = the lanes policy (par: rows per wave)
+  int narrow;           // lanes policy: 1 = one cell per lane (narrow_rule)
 };
 
 }  // namespace fish

@@ -108,6 +108,7 @@ struct Step {
     w.reverse = reverse;
     w.stream = stream;
     w.lanes = lanes[kind];
+    w.narrow = narrow_rule(waves[kind], n[kind_axis(kind)]);
     return w;
   }
 

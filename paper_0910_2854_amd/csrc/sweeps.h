@@ -985,12 +985,11 @@ __device__ __forceinline__ void st2_once(T* p, unsigned off_bytes, T v0, T v1) {
 
 // With CFL the sweep also reduces the CFL speed of the state it writes (the
 // last sub-operator of a double step leaves the next step's time step ready).
-template <typename T, int D, int GRAV, bool HSE, int LIM, bool CFL, bool NU>
+template <typename T, int D, int GRAV, bool HSE, int LIM, bool CFL, bool NU, int K>
 __global__ __launch_bounds__(256) void fluid_lanes_kernel(FluidLaunch<T> FL) {
   static_assert(D == 0 || !CFL, "the last sweep of a step is along x");
   constexpr int A = D == 0 ? 1 : 0, O = D == 0 ? 2 : 3 - D;  // rows: A fast
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-  constexpr int K = 2;
   // an output depends on 3 cells to its left and 3 to its right, the last of
   // which takes its right face from a fourth
   constexpr int HL = (3 + K - 1) / K, HR = (4 + K - 1) / K;
@@ -1046,14 +1045,17 @@ __global__ __launch_bounds__(256) void fluid_lanes_kernel(FluidLaunch<T> FL) {
     }
     const unsigned* o = in.o;
     // along x a pair is split only where the row's ghosts wrap or are copies
-    if (D == 0 && __all(o[1] == o[0] + z4 && f[1] == f[0] + z4)) {
+    bool pairs = false;
+    if constexpr (D == 0 && K == 2) pairs = __all(o[1] == o[0] + z4 && f[1] == f[0] + z4);
+    if (D == 0 && K == 2 && pairs) {
+      constexpr int J = K - 1;
 #pragma unroll
-      for (int i = 0; i < 5; ++i) ld2(a.u[i], o[0], in.u[0][i], in.u[1][i]);
-      ld2(a.b[D], f[0], in.bD[0], in.bD[1]);
-      ld2(a.b[T1], o[0], in.b1[0][0], in.b1[1][0]);
-      ld2(a.b[T1], o[0] + d1, in.b1[0][1], in.b1[1][1]);
-      ld2(a.b[T2], o[0], in.b2[0][0], in.b2[1][0]);
-      ld2(a.b[T2], o[0] + d2, in.b2[0][1], in.b2[1][1]);
+      for (int i = 0; i < 5; ++i) ld2(a.u[i], o[0], in.u[0][i], in.u[J][i]);
+      ld2(a.b[D], f[0], in.bD[0], in.bD[J]);
+      ld2(a.b[T1], o[0], in.b1[0][0], in.b1[J][0]);
+      ld2(a.b[T1], o[0] + d1, in.b1[0][1], in.b1[J][1]);
+      ld2(a.b[T2], o[0], in.b2[0][0], in.b2[J][0]);
+      ld2(a.b[T2], o[0] + d2, in.b2[0][1], in.b2[J][1]);
     } else {
 #pragma unroll
       for (int j = 0; j < K; ++j) {
@@ -1113,17 +1115,19 @@ __global__ __launch_bounds__(256) void fluid_lanes_kernel(FluidLaunch<T> FL) {
     fluid_window<T, D, GRAV, HSE, LIM, NU, K>(in.u, f, in.phi, in.gh, nu, k, un);
     // OFF is a multiple of K, so a row's cell 0 is the first of its lane, and
     // only the last lane of a row can hold a single cell of it
-    const bool out[K] = {(unsigned)in.c0 < (unsigned)n, in.c0 >= 0 && in.c0 + 1 < n};
-    if (out[1]) {
+    bool out[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) out[j] = in.c0 >= 0 && in.c0 + j < n;
+    if (K == 2 && out[K - 1]) {
 #pragma unroll
       for (int i = 0; i < 5; ++i) {
         if (D != 0) {
           st(a.uo[i], in.o[0], un[0][i]);
-          st(a.uo[i], in.o[1], un[1][i]);
+          st(a.uo[i], in.o[K - 1], un[K - 1][i]);
         } else if (FL.wl.stream) {
-          st2_once(a.uo[i], in.o[0], un[0][i], un[1][i]);
+          st2_once(a.uo[i], in.o[0], un[0][i], un[K - 1][i]);
         } else {
-          st2(a.uo[i], in.o[0], un[0][i], un[1][i]);
+          st2(a.uo[i], in.o[0], un[0][i], un[K - 1][i]);
         }
       }
     } else if (out[0]) {
@@ -1639,9 +1643,8 @@ __device__ __forceinline__ void face_row(const T (&w)[K], const T (&b)[K], const
   }
 }
 
-template <typename T, int D, int LIM, bool NU>
+template <typename T, int D, int LIM, bool NU, int K>
 __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
-  constexpr int K = 2;
   constexpr int A = D == 0 ? 1 : 0;  // rows: A fast
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
   // an output depends on 4 cells either side
@@ -1695,17 +1698,20 @@ __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
     const unsigned c[5] = {own, own + c1m, own + c1p, own + c2m, own + c2p};
     T md[5][K], rho[5][K], b[4][K], bd[K];
     // along x a pair is split only where the row's ghosts wrap or are copies
-    if (D == 0 && __all(x[1] == x[0] + z4 && xf[1] == xf[0] + z4)) {
+    constexpr int J = K - 1;
+    bool pairs = false;
+    if constexpr (D == 0 && K == 2) pairs = __all(x[J] == x[0] + z4 && xf[J] == xf[0] + z4);
+    if (D == 0 && K == 2 && pairs) {
 #pragma unroll
       for (int i = 0; i < 5; ++i) {
-        ld2(a.md, c[i] + x[0], md[i][0], md[i][1]);
-        ld2(a.rho, c[i] + x[0], rho[i][0], rho[i][1]);
+        ld2(a.md, c[i] + x[0], md[i][0], md[i][J]);
+        ld2(a.rho, c[i] + x[0], rho[i][0], rho[i][J]);
       }
-      ld2(a.bt[0], row + x[0], b[0][0], b[0][1]);
-      ld2(a.bt[0], row + f1p + x[0], b[1][0], b[1][1]);
-      ld2(a.bt[1], row + x[0], b[2][0], b[2][1]);
-      ld2(a.bt[1], row + f2p + x[0], b[3][0], b[3][1]);
-      ld2(a.bd, row + xf[0], bd[0], bd[1]);
+      ld2(a.bt[0], row + x[0], b[0][0], b[0][J]);
+      ld2(a.bt[0], row + f1p + x[0], b[1][0], b[1][J]);
+      ld2(a.bt[1], row + x[0], b[2][0], b[2][J]);
+      ld2(a.bt[1], row + f2p + x[0], b[3][0], b[3][J]);
+      ld2(a.bd, row + xf[0], bd[0], bd[J]);
     } else {
 #pragma unroll
       for (int j = 0; j < K; ++j) {
@@ -1776,17 +1782,17 @@ __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
         st2(p, o0, v0, v1);
       }
     };
-    if (c0 >= 0 && c0 + 1 < n) {
-      if (own1) put(a.bto[0], row + x[0], row + x[1], bn1[0], bn1[1]);
-      if (own2) put(a.bto[1], row + x[0], row + x[1], bn2[0], bn2[1]);
+    if (K == 2 && c0 >= 0 && c0 + 1 < n) {
+      if (own1) put(a.bto[0], row + x[0], row + x[J], bn1[0], bn1[J]);
+      if (own2) put(a.bto[1], row + x[0], row + x[J], bn2[0], bn2[J]);
     } else if ((unsigned)c0 < (unsigned)n) {
       if (own1) st(a.bto[0], row + x[0], bn1[0]);
       if (own2) st(a.bto[1], row + x[0], bn2[0]);
     }
     if (own1 && own2) {
       const int nf = n + (bcD ? 1 : 0);
-      if (c0 >= 0 && c0 + 1 < nf)
-        put(a.bdo, row + xf[0], row + xf[1], bd[0] + dbd[0], bd[1] + dbd[1]);
+      if (K == 2 && c0 >= 0 && c0 + 1 < nf)
+        put(a.bdo, row + xf[0], row + xf[J], bd[0] + dbd[0], bd[J] + dbd[J]);
       else if ((unsigned)c0 < (unsigned)nf)
         st(a.bdo, row + xf[0], bd[0] + dbd[0]);
     }
