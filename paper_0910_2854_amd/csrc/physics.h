@@ -173,7 +173,8 @@ __device__ __forceinline__ void cell_quantities(const T* u, const FieldQ<T>& f, 
   }
 }
 
-// Limiters, Eqs. (29)-(30).  minmod as the median of a, b and 0.
+// Limiters, Eqs. (29)-(30).  minmod as the median of a, b and 0 (of finite
+// operands; with a NaN the FP32 instruction gives the least of the other two).
 __device__ __forceinline__ float minmod(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
 __device__ __forceinline__ double minmod(double a, double b) {
   return fmax(fmin(a, b), 0.0) + fmin(fmax(a, b), 0.0);
@@ -203,6 +204,17 @@ __device__ constexpr int limit_unit() {
   return LIM == 0 ? 1 : 2;
 }
 
+// The gradient scale of the hydrostatic correction as a finite number.  A
+// negative pressure of a half-step state has no sound speed; its NaN would reach
+// minmod, where the FP32 median gives the lesser of du and 0, not du (as the FP64
+// form does).  With 0 in its place du is the limited value.  An infinite scale
+// (a pressure of zero) becomes the largest number: minmod decides alike, and
+// times a zero xi it is 0.
+__device__ __forceinline__ float finite_scale(float s) {
+  return s == s ? __builtin_amdgcn_fmed3f(s, -3.402823466e38f, 3.402823466e38f) : 0.0f;
+}
+__device__ __forceinline__ double finite_scale(double s) { return s; }
+
 // Dissipation Q_j at the interface between cells L and R, so that the
 // first-order relaxed flux is (F_L + F_R)/2 - Q_j/2:
 //   no HSE: Q = max(d_L, d_R) (u_R - u_L), Eqs. (24)-(25);
@@ -219,7 +231,7 @@ __device__ __forceinline__ void dissipation(const CellQ<T, HSE>& L, const CellQ<
     const T avL = fabs(L.vd), avR = fabs(R.vd);
     const T dadv = speed_max(avL, avR);
     const T dac = speed_max(L.cF, R.cF);
-    const T scale = T(0.5) * ((phiR - phiL) * rcp(L.cS * R.cS));  // (exact: the mean of xi taken here)
+    const T scale = finite_scale(T(0.5) * ((phiR - phiL) * rcp(L.cS * R.cS)));  // (exact: the mean of xi taken here)
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
       const T du = R.u[k] - L.u[k];
