@@ -299,14 +299,14 @@ __device__ __forceinline__ T inv_span(T wm, T w0, T wp) {
 // uniform mesh), and the inverse centre spans of c-1 and c-3 for gravity.
 template <typename T>
 struct FluidNU {
-  T kh1, kf3;  // halved, as FluidConsts::kh2 and kf2
+  T kh1, kf3;
   T wl2, wr2, isp1, isp3;
 };
 template <typename T>
 __device__ __forceinline__ FluidNU<T> fluid_nu(const T* w, T dt) {
   FluidNU<T> n;
-  n.kh1 = T(0.25) * dt * rcp(w[3]);
-  n.kf3 = T(0.5) * dt * rcp(w[1]);
+  n.kh1 = T(0.5) * dt * rcp(w[3]);
+  n.kf3 = dt * rcp(w[1]);
   n.wl2 = w[2] * rcp(w[1] + w[2]);
   n.wr2 = w[2] * rcp(w[2] + w[3]);
   n.isp1 = inv_span(w[2], w[3], w[4]);
@@ -316,7 +316,7 @@ __device__ __forceinline__ FluidNU<T> fluid_nu(const T* w, T dt) {
 
 template <typename T>
 struct FluidConsts {
-  T kh2, kf2;  // half of dt / (2h) and of dt / h: the fluxes they multiply are kept doubled
+  T k_half, k_full;  // dt / (2h) and dt / h
   T half_dt, dt, inv2h, alpha;
   double gamma;
 };
@@ -372,19 +372,16 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   cell_quantities<T, D, HSE>(uc, f0, k.gamma, q0);
   const CellQ<T, HSE> q0m = prev(q0, hi.q0, ho.q0);
   const FieldQ<T> f0m = prev(f0, hi.f, ho.f);
-  // predictor flux at interface c-1/2 (Eq. 24, dissipation scaled by alpha).
-  // All fluxes and flux differences are kept doubled and the step factors
-  // halved: the scalings by 1/2 of Eqs. (24)-(34) are exact, so leaving them
-  // out changes no result and saves 35 products per position.
+  // predictor flux at interface c-1/2 (Eq. 24, dissipation scaled by alpha)
   T Q[5];
   Vec<T, 5> F1;
   dissipation<T, HSE>(q0m, q0, phm1, phc, Q);
 #pragma unroll
-  for (int i = 0; i < 5; ++i) F1.v[i] = (q0m.F[i] + q0.F[i]) - k.alpha * Q[i];
+  for (int i = 0; i < 5; ++i) F1.v[i] = (half_flux<D>(q0m, i) + half_flux<D>(q0, i)) - k.alpha * Q[i];
   const Vec<T, 5> F1m = prev(F1, hi.F1, ho.F1);
   // predictor half step of cell c-1 (Eq. 41; Eq. 69 on an irregular mesh)
   T up[5];
-  const T khalf = NU ? nu.kh1 : k.kh2;
+  const T khalf = NU ? nu.kh1 : k.k_half;
   if (GRAV == 1) {
     T S[5];
     gravity_source<T, D>(q0m.u[RHO], q0m.u[MX + D], phc - phm2, NU ? nu.isp1 : k.inv2h, S);
@@ -404,10 +401,10 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   dissipation<T, HSE>(q1m, q1, phm2, phm1, Qc);
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
-    const T dF = q1.F[i] - q1m.F[i];
+    const T dF = half_flux<D>(q1, i) - half_flux<D>(q1m, i);
     ap.v[i] = dF + Qc[i];
     am.v[i] = dF - Qc[i];
-    bs.v[i] = (q1m.F[i] + q1.F[i]) - Qc[i];
+    bs.v[i] = (half_flux<D>(q1m, i) + half_flux<D>(q1, i)) - Qc[i];
   }
   const Vec<T, 5> apm = prev(ap, hi.ap, ho.ap);
   const Vec<T, 5> amm = prev(am, hi.am, ho.am);
@@ -415,9 +412,8 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   // limited second-order flux at interface c-5/2 (Eq. 34); both limiters
   // taken here belong to cell c-2 (its half-step state decides the switch)
   const T sup2 = LIM == 2 ? prev(q1.sup, hi.sp1, ho.sp1) : T(0);
-  // (the flux is doubled and so are the differences: half their limited value;
-  // irregular mesh: each difference weighted to put cell c-2's slope on its
-  // interfaces, which absorbs that half)
+  // (half their limited value; irregular mesh: each difference weighted to put
+  // cell c-2's slope on its interfaces, which absorbs that half)
   Vec<T, 5> Lp, F2;
   constexpr T unit = T(NU ? 1.0 : 0.5) * limit_unit<LIM>();
   if (!NU) {
@@ -447,7 +443,7 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   const Vec<T, 5> um3 = prev(um2, hi.ub, ho.ub);
   const T* u3 = um3.v;
   // corrector of cell c-3 (Eq. 43)
-  const T kfull = NU ? nu.kf3 : k.kf2;
+  const T kfull = NU ? nu.kf3 : k.k_full;
   if (GRAV == 1) {
     const T rpm2 = prev(up[RHO], hi.rp1, ho.rp1);   // rho' of c-2
     const T rpm3 = prev(rpm2, hi.rp2, ho.rp2);      // rho' of c-3
@@ -483,8 +479,8 @@ template <typename T>
 __device__ __forceinline__ FluidConsts<T> fluid_consts(const FluidArgs<T>& a, int D) {
   const double dt = a.sc->dt;
   FluidConsts<T> k;
-  k.kh2 = T(0.5) * (T)a.sc->kh[D];
-  k.kf2 = T(0.5) * (T)a.sc->kf[D];
+  k.k_half = (T)a.sc->kh[D];
+  k.k_full = (T)a.sc->kf[D];
   k.half_dt = (T)(0.5 * dt);
   k.dt = (T)dt;
   k.inv2h = (T)a.i2h[D];
@@ -780,7 +776,7 @@ __device__ __forceinline__ void cells_from_right(const CellQ<T, HSE> (&x)[K], Ce
     r.u[i] = lane_shl(c.u[i]);
     r.F[i] = i == RHO ? r.F[i] : lane_shl(c.F[i]);
   }
-  r.F[RHO] = r.u[MX + D];  // the mass flux
+  r.F[RHO] = T(0);
   r.d = lane_shl(c.d);
   r.sup = T(0);
   if (HSE) {
@@ -802,8 +798,8 @@ struct CellNU {
 template <typename T>
 __device__ __forceinline__ CellNU<T> cell_nu(T wm, T w0, T wp, T dt) {
   CellNU<T> n;
-  n.kh = T(0.25) * dt * rcp(w0);
-  n.kf = T(0.5) * dt * rcp(w0);
+  n.kh = T(0.5) * dt * rcp(w0);
+  n.kf = dt * rcp(w0);
   n.wl = w0 * rcp(wm + w0);
   n.wr = w0 * rcp(w0 + wp);
   n.isp = inv_span(wm, w0, wp);
@@ -838,13 +834,13 @@ __device__ __forceinline__ void fluid_window(const T (&u_in)[K][5], const FieldQ
     T Q[5];
     dissipation<T, HSE>(q[j], qr[j], phi[j], phr[j], Q);
 #pragma unroll
-    for (int i = 0; i < 5; ++i) F[j].v[i] = (q[j].F[i] + qr[j].F[i]) - k.alpha * Q[i];
+    for (int i = 0; i < 5; ++i) F[j].v[i] = (half_flux<D>(q[j], i) + half_flux<D>(qr[j], i)) - k.alpha * Q[i];
   }
   from_left(F, Fl);
   T up[K][5];
 #pragma unroll
   for (int j = 0; j < K; ++j) {
-    const T khalf = NU ? nu[j].kh : k.kh2;
+    const T khalf = NU ? nu[j].kh : k.k_half;
     if (GRAV == 1) {
       T S[5];
       gravity_source<T, D>(u[j][RHO], u[j][MX + D], phr[j] - phl[j], NU ? nu[j].isp : k.inv2h, S);
@@ -865,10 +861,10 @@ __device__ __forceinline__ void fluid_window(const T (&u_in)[K][5], const FieldQ
     dissipation<T, HSE>(q[j], qr[j], phi[j], phr[j], Q);
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
-      const T dF = qr[j].F[i] - q[j].F[i];
+      const T dF = half_flux<D>(qr[j], i) - half_flux<D>(q[j], i);
       ap[j].v[i] = dF + Q[i];
       am[j].v[i] = dF - Q[i];
-      bs[j].v[i] = (q[j].F[i] + qr[j].F[i]) - Q[i];
+      bs[j].v[i] = (half_flux<D>(q[j], i) + half_flux<D>(qr[j], i)) - Q[i];
     }
   }
   from_left(ap, al);
@@ -897,7 +893,7 @@ __device__ __forceinline__ void fluid_window(const T (&u_in)[K][5], const FieldQ
   from_left(F, Fl);
 #pragma unroll
   for (int j = 0; j < K; ++j) {
-    const T kfull = NU ? nu[j].kf : k.kf2;
+    const T kfull = NU ? nu[j].kf : k.k_full;
     if (GRAV == 1) {
       T S[5];
       gravity_source<T, D>(up[j][RHO], up[j][MX + D], phr[j] - phl[j], NU ? nu[j].isp : k.inv2h, S);
@@ -1739,11 +1735,7 @@ __global__ __launch_bounds__(256) void field_lanes_kernel(FieldLaunch<T> FL) {
       from_left(w, wl);
       from_right(w, wr);
 #pragma unroll
-      for (int j = 0; j < K; ++j) {
-        nu[j] = cell_nu(wl[j], w[j], wr[j], k.dt);
-        nu[j].kh *= T(2);  // the field's fluxes are not kept doubled
-        nu[j].kf *= T(2);
-      }
+      for (int j = 0; j < K; ++j) nu[j] = cell_nu(wl[j], w[j], wr[j], k.dt);
     }
     T w[4][K];  // v_D on the t1-faces c1 and c1+1 and the t2-faces c2 and c2+1
 #pragma unroll
