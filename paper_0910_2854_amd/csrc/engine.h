@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "layout.h"
+#include "plan.h"
 
 namespace fish {
 
@@ -24,17 +25,14 @@ struct DeviceBuf {
 };
 
 // One box of the engine (host side).
-struct HostBox {
+struct HostBox : PlanBox {
   bool used = false;
   bool have_state = false;
   bool cfl_fresh = false;   // its Scalars::cmax_bits holds the CFL speed of its state
-  int n[3]{};
-  int o[3]{};               // extra layer on outflow axes
   int bc[3]{};
   double h[3]{};
   double cfl = 0.5;
   long long st[3]{};        // element strides (1, sy, sz)
-  long long nelem = 0;      // elements per array
   long long off = 0;        // element offset in every pool
   long long reserved = 0;   // elements reserved in the pools (aligned)
   bool parked = false;      // kept (state readable) but out of the launches
@@ -56,18 +54,6 @@ struct EngineConfig {
   void (*free)(void*, size_t, void*, void*) = nullptr;
   void* alloc_user = nullptr;
 };
-
-// Tuning targets per kernel kind: stream positions per wave for the x kinds
-// (whole rows of the box fill it), the segment length along the sweep for
-// the y/z kinds, cells per lane for the CFL check.
-struct Tuning {
-  int target[K_NUM];
-  int remap[K_NUM];   // XCD-aware block order per kind (0/1)
-  int groups[K_NUM];  // y/z kinds: waves of a block on consecutive rows; check kind: the
-                      // step's CFL reduction in the check kernel instead of the last x
-                      // sweep; x fluid kind: the strided layout (0/1)
-};
-Tuning default_tuning();
 
 class Engine {
  public:

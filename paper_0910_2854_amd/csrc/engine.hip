@@ -6,6 +6,7 @@
 
 #include "launch.h"
 #include "launch_api.h"
+#include "plan.h"
 #include "step_kernels.h"
 #include "sweeps.h"
 
@@ -23,21 +24,6 @@ namespace {
 constexpr long long kAlign = 64;  // box offsets in elements (256 B in FP32)
 
 }  // namespace
-
-Tuning default_tuning() {
-  Tuning t;
-  t.target[K_FLUID_X] = 1536;
-  t.target[K_FIELD_X] = 384;
-  t.target[K_FLUID_Y] = t.target[K_FLUID_Z] = 64;
-  t.target[K_FIELD_Y] = t.target[K_FIELD_Z] = 64;
-  t.target[K_CHECK] = 16;
-  for (int k = 0; k < K_NUM; ++k) t.remap[k] = t.groups[k] = 0;
-  // the y/z field sweeps read four neighbouring rows per row: 256^3 FP32
-  // segments of 64, 145 -> 138 us (B_y) and 142 -> 134 us (B_z); 384^3 588 ->
-  // 554 and 554 -> 520 us; the fluid sweeps read two, L_y 195 -> 206 us
-  t.remap[K_FIELD_Y] = t.remap[K_FIELD_Z] = 1;
-  return t;
-}
 
 
 Engine::~Engine() { release(); }
@@ -652,194 +638,6 @@ int Engine::read_scalars(int slot, Scalars* out) {
 }
 
 // ------------------------------------------------------------ work lists
-static long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
-
-// Waves of one box in the list of one kind, and the per-box parameter.
-// Pencil waves of one segment of a y/z kind (strided_map's two orders).
-static long long strided_waves(long long nA, long long nO, int groups) {
-  if (groups && nA >= 64) return ceil_div(nA, 64) * ceil_div(nO, 4) * 4;
-  return ceil_div(nA * nO, 64);
-}
-
-static long long kind_waves(const HostBox& b, int kind, int target, int groups, int* par) {
-  switch (kind) {
-    case K_FLUID_X: {
-      if (groups) {  // the strided policy along x: lanes along y, segments of the rows
-        const int seg = std::max(1, std::min(target, b.n[0]));
-        *par = seg;
-        return strided_waves(b.n[1], b.n[2], groups) * ceil_div(b.n[0], seg);
-      }
-      const int rpw = std::max(1, target / (b.n[0] + 8));
-      *par = rpw;
-      return ceil_div((long long)b.n[1] * b.n[2], rpw);
-    }
-    case K_FIELD_X: {
-      const int rpw = std::max(1, target / (b.n[0] + 8));
-      *par = rpw;
-      return ceil_div((long long)(b.n[1] + b.o[1]) * (b.n[2] + b.o[2]), rpw);
-    }
-    case K_FLUID_Y:
-    case K_FLUID_Z: {
-      const int D = kind - K_FLUID_X;
-      const int seg = std::max(1, std::min(target, b.n[D]));
-      *par = seg;
-      return strided_waves(b.n[0], b.n[3 - D], groups) * ceil_div(b.n[D], seg);
-    }
-    case K_FIELD_Y:
-    case K_FIELD_Z: {
-      const int D = kind - K_FIELD_X;
-      const int seg = std::max(1, std::min(target, b.n[D]));
-      *par = seg;
-      return strided_waves(b.n[0] + b.o[0], b.n[3 - D] + b.o[3 - D], groups) * ceil_div(b.n[D], seg);
-    }
-    default: {
-      const int cpl = std::max(1, target);
-      *par = cpl;
-      return ceil_div((long long)b.n[0] * b.n[1] * b.n[2], 64ll * cpl);
-    }
-  }
-}
-
-// The work shape of a kind at its default, for the boxes of a table.  A launch
-// of many waves takes the default as it is; a launch that leaves SIMDs idle is
-// cut finer.
-//   x kinds: halved while the boxes have fewer than 4096 waves, down to a row
-// per wave (128^3 FP32 L_x: 35.2 us at 5 rows per wave, 32.7 at 2).
-//   y/z kinds: a wave walks its segment and `halo` more positions, and a
-// position takes it as long alone on its SIMD as `alone` waves that share one
-// (latency against issue; more where the boxes come from HBM).  With fewer than
-// 4096 waves at the default, the segment is the one whose rounds of resident
-// waves take the shortest time.  Measured, L_z, at 64 halved to 2048 waves but
-// no shorter than 8, and so: 32^3 FP32 18.0 -> 12.8 us (8 -> 2 cells), 64^3 FP32
-// 20.0 -> 16.7 (8 -> 4), FP64 24.1 -> 21.2.  Boxes of several sizes are taken
-// together, by the longest walk or the sum of the work.
-static int planned_target(const std::vector<const HostBox*>& boxes, int kind, int target, int groups, size_t esize) {
-  if (kind == K_CHECK) {
-    long long w = 0;
-    int par = 1;
-    for (;;) {
-      w = 0;
-      for (const HostBox* b : boxes) w += kind_waves(*b, kind, target, groups, &par);
-      if (w >= 2048 || target < 2) return target;
-      target /= 2;
-    }
-  }
-  if (kind == K_FIELD_X || (kind == K_FLUID_X && !groups)) {
-    int lo = 0, par = 1;
-    for (const HostBox* b : boxes) lo = std::max(lo, b->n[0] + 8);
-    for (;;) {
-      long long w = 0;
-      for (const HostBox* b : boxes) w += kind_waves(*b, kind, target, groups, &par);
-      if (w >= 4096 || target / 2 < lo) return target;
-      target /= 2;
-    }
-  }
-  const int D = kind == K_FLUID_X ? 0 : kind <= K_FLUID_Z ? kind - K_FLUID_X : kind - K_FIELD_X;
-  const int halo = kind <= K_FLUID_Z ? 6 : 8;
-  long long bytes = 0, waves = 0;
-  int par = 1;
-  for (const HostBox* b : boxes) {
-    bytes += 16ll * (long long)esize * b->nelem;
-    waves += kind_waves(*b, kind, target, groups, &par);
-  }
-  if (waves >= 4096) return target;
-  constexpr double kSimds = 1024.0;
-  const double occupancy = esize == 8 ? 2.0 : 4.0;
-  const double alone = (esize == 8 ? 1.15 : 1.75) * (bytes > (256ll << 20) ? 1.45 : 1.0);
-  int best = target;
-  double best_t = 0.0;
-  for (int seg = target; seg >= 1; --seg) {
-    double work = 0.0;
-    long long w = 0;
-    int longest = 0;
-    for (const HostBox* b : boxes) {
-      const long long bw = kind_waves(*b, kind, seg, groups, &par);
-      const int even = (b->n[D] + (b->n[D] + par - 1) / par - 1) / ((b->n[D] + par - 1) / par);
-      w += bw;
-      work += (double)bw * (even + halo);
-      longest = std::max(longest, even);
-    }
-    double t;
-    if (boxes.size() == 1) {
-      const double n = std::ceil((double)w / kSimds), full = std::floor(n / occupancy), rest = n - full * occupancy;
-      t = (longest + halo) * (full * std::max(alone, occupancy) + (rest > 0.0 ? std::max(alone, rest) : 0.0));
-    } else {
-      t = std::max((longest + halo) * alone, work / kSimds);
-    }
-    if (seg == target || t < best_t) {
-      best_t = t;
-      best = seg;
-    }
-  }
-  return best;
-}
-
-// Segments per pencil of a y/z kind, ceil(n_d / segment length); 0 for the
-// other kinds.
-static int kind_segments(const HostBox& b, int kind, int par) {
-  if (kind == K_FLUID_X) return (b.n[0] + par - 1) / par;  // read by the strided layout only
-  if (kind == K_FLUID_Y || kind == K_FIELD_Y) return (b.n[1] + par - 1) / par;
-  if (kind == K_FLUID_Z || kind == K_FIELD_Z) return (b.n[2] + par - 1) / par;
-  return 0;
-}
-
-// Rows along the sweep of a y/z kind, the work of the lanes policy.
-static long long lane_rows(const HostBox& b, int kind) {
-  const bool field = kind >= K_FIELD_X;
-  const int D = field ? kind - K_FIELD_X : kind - K_FLUID_X;
-  const int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
-  return (long long)(b.n[t1] + (field ? b.o[t1] : 0)) * (b.n[t2] + (field ? b.o[t2] : 0));
-}
-
-// Whether a y/z kind takes the lanes policy: for boxes so small that a launch
-// lasts as long as one wave's walk, which lanes along the sweep shorten to a
-// window or two, and their uncoalesced accesses stay in the caches.  Double
-// step, FP32, walks -> lanes of two cells: 32^3 113 -> 83 us (16^3 FP64 115 -> 70), 40^3 123
-// -> 106, 48^3 128 -> 128, 56^3 147 -> 163, 64^3 161 -> 217.
-static bool planned_lanes(const std::vector<const HostBox*>& boxes, int kind) {
-  if (kind == K_FLUID_X || kind == K_FIELD_X || kind == K_CHECK) return false;
-  const int D = kind >= K_FIELD_X ? kind - K_FIELD_X : kind - K_FLUID_X;
-  long long cells = 0;
-  for (const HostBox* b : boxes) {
-    cells += (long long)b->n[0] * b->n[1] * b->n[2];
-    if (b->n[D] < 4) return false;  // rows mostly of ghosts
-  }
-  return cells <= 100000;
-}
-
-// Segments of equal length (to a cell) instead of full ones and a remainder.
-static int even_segments(const HostBox& b, int kind, int par) {
-  const int k = kind_segments(b, kind, par);
-  return k > 0 ? (b.n[kind <= K_FLUID_Z ? kind - K_FLUID_X : kind - K_FIELD_X] + k - 1) / k : par;
-}
-
-void plan_single_box(const int n[3], const int bc[3], size_t esize, long long max_waves, int par[K_NUM],
-                     int nseg[K_NUM], long long waves[K_NUM], bool lanes[K_NUM]) {
-  HostBox b;
-  for (int a = 0; a < 3; ++a) {
-    b.n[a] = n[a];
-    b.bc[a] = bc[a];
-    b.o[a] = bc[a] == 1 ? 1 : 0;
-  }
-  b.nelem = (long long)(n[0] + b.o[0]) * (n[1] + b.o[1]) * (n[2] + b.o[2]);
-  const Tuning t = default_tuning();
-  for (int k = 0; k < K_NUM; ++k) {
-    lanes[k] = planned_lanes({&b}, k);
-    if (lanes[k]) {
-      par[k] = 1;
-      nseg[k] = 0;
-      waves[k] = lane_rows(b, k);
-      continue;
-    }
-    const int target = planned_target({&b}, k, t.target[k], t.groups[k], esize);
-    waves[k] = kind_waves(b, k, target, t.groups[k], &par[k]);
-    // several short rows per wave where single ones are too many for the caller
-    if (k == K_FIELD_X && waves[k] > max_waves) waves[k] = kind_waves(b, k, 2 * target, t.groups[k], &par[k]);
-    if (k != K_FLUID_X) par[k] = even_segments(b, k, par[k]);
-    nseg[k] = kind_segments(b, k, par[k]);
-  }
-}
-
 int Engine::build_lists() {
   std::vector<int> slots;
   for (int s = 0; s < (int)boxes.size(); ++s)
@@ -857,18 +655,13 @@ int Engine::build_lists() {
       boxes[s].woff[a] = anynu ? wtotal[a] : 0;
       if (anynu) wtotal[a] += boxes[s].n[a];
     }
-  // a shape left at its default is planned for the boxes; one set by
-  // fish_set_shape or the autotuner is used as set
-  int target[K_NUM];
-  bool planned[K_NUM];
+  KindPlan plan[K_NUM];
   {
-    const Tuning defaults = default_tuning();
-    std::vector<const HostBox*> all;
+    std::vector<const PlanBox*> all;
     for (int s : slots) all.push_back(&boxes[s]);
     for (int k = 0; k < K_NUM; ++k) {
-      planned[k] = nb > 0 && tuning.target[k] == defaults.target[k];
-      lanes[k] = planned[k] && planned_lanes(all, k);
-      target[k] = planned[k] ? planned_target(all, k, tuning.target[k], tuning.groups[k], esize) : tuning.target[k];
+      plan[k] = plan_kind(all, k, tuning, esize);
+      lanes[k] = plan[k].lanes;
     }
   }
   for (int t = 0; t < nb; ++t) {
@@ -890,15 +683,13 @@ int Engine::build_lists() {
     d.slot = slots[t];
     for (int a = 0; a < 3; ++a) d.woff[a] = b.woff[a];
     for (int k = 0; k < K_NUM; ++k) {
-      int par = 1;
-      const long long w = lanes[k] ? lane_rows(b, k) : kind_waves(b, k, target[k], tuning.groups[k], &par);
-      if (planned[k] && !lanes[k] && k != K_FLUID_X) par = even_segments(b, k, par);
-      if ((long long)list[k].size() + w >= (1ll << 31) / 64)
+      const BoxShape shape = box_shape(b, k, plan[k], tuning.groups[k]);
+      if ((long long)list[k].size() + shape.waves >= (1ll << 31) / 64)
         return fail(5, "work list exceeds the launch size");
       d.wave0[k] = (int)list[k].size();
-      d.par[k] = par;
-      d.nseg[k] = lanes[k] ? 0 : kind_segments(b, k, par);
-      list[k].insert(list[k].end(), (size_t)w, t);
+      d.par[k] = shape.par;
+      d.nseg[k] = shape.nseg;
+      list[k].insert(list[k].end(), (size_t)shape.waves, t);
     }
   }
   int rc = set_device();

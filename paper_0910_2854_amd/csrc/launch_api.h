@@ -40,11 +40,4 @@ void launch_check(const CheckLaunch<T>& L, hipStream_t stream);
 // maximum cleared for the step's last sweep.
 void launch_begin_step(const BoxDesc* boxes, int nb, Scalars* sc, double dt, hipStream_t stream);
 
-// The work shape of a box alone in its table at the default tuning (as the
-// engine plans it): per kind the parameter of BoxDesc::par, the segments per
-// pencil of BoxDesc::nseg, the waves of its work list and WorkList::lanes.
-// With more than max_waves waves the x field sweep is cut coarser.
-void plan_single_box(const int n[3], const int bc[3], size_t esize, long long max_waves, int par[K_NUM],
-                     int nseg[K_NUM], long long waves[K_NUM], bool lanes[K_NUM]);
-
 }  // namespace fish

@@ -255,11 +255,15 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
     return FISH_ERR_UNSUPPORTED;
   }
   BoxDesc d{};
-  long long waves[K_NUM];
+  BoxShape shape[K_NUM];
   bool lanes[K_NUM];
-  plan_single_box(n, bc, esize, FISH_NOALLOC_MAX_WAVES, d.par, d.nseg, waves, lanes);
+  plan_single_box(n, bc, esize, FISH_NOALLOC_MAX_WAVES, shape, lanes);
   long long most = 0;
-  for (int k = 0; k < K_NUM; ++k) most = waves[k] > most ? waves[k] : most;
+  for (int k = 0; k < K_NUM; ++k) {
+    d.par[k] = shape[k].par;
+    d.nseg[k] = shape[k].nseg;
+    most = std::max(most, shape[k].waves);
+  }
   if (most > FISH_NOALLOC_MAX_WAVES) {
     *msg = "the box needs " + std::to_string(most) + " wavefronts in one launch; the most is " +
            std::to_string(FISH_NOALLOC_MAX_WAVES);
@@ -320,7 +324,7 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
       st.table = table;
       st.sc = sc;
       for (int k = 0; k < K_NUM; ++k) {
-        st.waves[k] = waves[k];
+        st.waves[k] = shape[k].waves;
         st.lanes[k] = lanes[k];
       }
       for (int a = 0; a < 3; ++a) st.n[a] = n[a];
@@ -342,7 +346,7 @@ int step_noalloc(const fish_params* p, void* const state[8], void* const work[8]
       st.table = table;
       st.sc = sc;
       for (int k = 0; k < K_NUM; ++k) {
-        st.waves[k] = waves[k];
+        st.waves[k] = shape[k].waves;
         st.lanes[k] = lanes[k];
       }
       for (int a = 0; a < 3; ++a) st.n[a] = n[a];

@@ -1,0 +1,264 @@
+// plan.h -- how the sweeps of a table of boxes are cut into waves: the work shape
+// of every kernel kind and each box's part of it.  Host arithmetic only.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <vector>
+
+#include "layout.h"
+
+namespace fish {
+
+// What a plan takes from a box.
+struct PlanBox {
+  int n[3]{};
+  int o[3]{};           // extra layer on outflow axes
+  long long nelem = 0;  // elements per array
+};
+
+// Tuning targets per kernel kind: stream positions per wave for the x kinds
+// (whole rows of the box fill it), the segment length along the sweep for
+// the y/z kinds, cells per lane for the CFL check.
+struct Tuning {
+  int target[K_NUM];
+  int remap[K_NUM];   // XCD-aware block order per kind (0/1)
+  int groups[K_NUM];  // y/z kinds: waves of a block on consecutive rows; check kind: the
+                      // step's CFL reduction in the check kernel instead of the last x
+                      // sweep; x fluid kind: the strided layout (0/1)
+};
+inline Tuning default_tuning() {
+  Tuning t;
+  t.target[K_FLUID_X] = 1536;
+  t.target[K_FIELD_X] = 384;
+  t.target[K_FLUID_Y] = t.target[K_FLUID_Z] = 64;
+  t.target[K_FIELD_Y] = t.target[K_FIELD_Z] = 64;
+  t.target[K_CHECK] = 16;
+  for (int k = 0; k < K_NUM; ++k) t.remap[k] = t.groups[k] = 0;
+  // the y/z field sweeps read four neighbouring rows per row: 256^3 FP32
+  // segments of 64, 145 -> 138 us (B_y) and 142 -> 134 us (B_z); 384^3 588 ->
+  // 554 and 554 -> 520 us; the fluid sweeps read two, L_y 195 -> 206 us
+  t.remap[K_FIELD_Y] = t.remap[K_FIELD_Z] = 1;
+  return t;
+}
+
+inline long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
+
+// Waves of one box in the list of one kind, and the per-box parameter.
+// Pencil waves of one segment of a y/z kind (strided_map's two orders).
+inline long long strided_waves(long long nA, long long nO, int groups) {
+  if (groups && nA >= 64) return ceil_div(nA, 64) * ceil_div(nO, 4) * 4;
+  return ceil_div(nA * nO, 64);
+}
+
+inline long long kind_waves(const PlanBox& b, int kind, int target, int groups, int* par) {
+  switch (kind) {
+    case K_FLUID_X: {
+      if (groups) {  // the strided policy along x: lanes along y, segments of the rows
+        const int seg = std::max(1, std::min(target, b.n[0]));
+        *par = seg;
+        return strided_waves(b.n[1], b.n[2], groups) * ceil_div(b.n[0], seg);
+      }
+      const int rpw = std::max(1, target / (b.n[0] + 8));
+      *par = rpw;
+      return ceil_div((long long)b.n[1] * b.n[2], rpw);
+    }
+    case K_FIELD_X: {
+      const int rpw = std::max(1, target / (b.n[0] + 8));
+      *par = rpw;
+      return ceil_div((long long)(b.n[1] + b.o[1]) * (b.n[2] + b.o[2]), rpw);
+    }
+    case K_FLUID_Y:
+    case K_FLUID_Z: {
+      const int D = kind - K_FLUID_X;
+      const int seg = std::max(1, std::min(target, b.n[D]));
+      *par = seg;
+      return strided_waves(b.n[0], b.n[3 - D], groups) * ceil_div(b.n[D], seg);
+    }
+    case K_FIELD_Y:
+    case K_FIELD_Z: {
+      const int D = kind - K_FIELD_X;
+      const int seg = std::max(1, std::min(target, b.n[D]));
+      *par = seg;
+      return strided_waves(b.n[0] + b.o[0], b.n[3 - D] + b.o[3 - D], groups) * ceil_div(b.n[D], seg);
+    }
+    default: {
+      const int cpl = std::max(1, target);
+      *par = cpl;
+      return ceil_div((long long)b.n[0] * b.n[1] * b.n[2], 64ll * cpl);
+    }
+  }
+}
+
+// The work shape of a kind at its default, for the boxes of a table.  A launch
+// of many waves takes the default as it is; a launch that leaves SIMDs idle is
+// cut finer.
+//   x kinds: halved while the boxes have fewer than 4096 waves, down to a row
+// per wave (128^3 FP32 L_x: 35.2 us at 5 rows per wave, 32.7 at 2).
+//   y/z kinds: a wave walks its segment and `halo` more positions, and a
+// position takes it as long alone on its SIMD as `alone` waves that share one
+// (latency against issue; more where the boxes come from HBM).  With fewer than
+// 4096 waves at the default, the segment is the one whose rounds of resident
+// waves take the shortest time.  Measured, L_z, at 64 halved to 2048 waves but
+// no shorter than 8, and so: 32^3 FP32 18.0 -> 12.8 us (8 -> 2 cells), 64^3 FP32
+// 20.0 -> 16.7 (8 -> 4), FP64 24.1 -> 21.2.  Boxes of several sizes are taken
+// together, by the longest walk or the sum of the work.
+inline int planned_target(const std::vector<const PlanBox*>& boxes, int kind, int target, int groups, size_t esize) {
+  if (kind == K_CHECK) {
+    long long w = 0;
+    int par = 1;
+    for (;;) {
+      w = 0;
+      for (const PlanBox* b : boxes) w += kind_waves(*b, kind, target, groups, &par);
+      if (w >= 2048 || target < 2) return target;
+      target /= 2;
+    }
+  }
+  if (kind == K_FIELD_X || (kind == K_FLUID_X && !groups)) {
+    int lo = 0, par = 1;
+    for (const PlanBox* b : boxes) lo = std::max(lo, b->n[0] + 8);
+    for (;;) {
+      long long w = 0;
+      for (const PlanBox* b : boxes) w += kind_waves(*b, kind, target, groups, &par);
+      if (w >= 4096 || target / 2 < lo) return target;
+      target /= 2;
+    }
+  }
+  const int D = kind == K_FLUID_X ? 0 : kind <= K_FLUID_Z ? kind - K_FLUID_X : kind - K_FIELD_X;
+  const int halo = kind <= K_FLUID_Z ? 6 : 8;
+  long long bytes = 0, waves = 0;
+  int par = 1;
+  for (const PlanBox* b : boxes) {
+    bytes += 16ll * (long long)esize * b->nelem;
+    waves += kind_waves(*b, kind, target, groups, &par);
+  }
+  if (waves >= 4096) return target;
+  constexpr double kSimds = 1024.0;
+  const double occupancy = esize == 8 ? 2.0 : 4.0;
+  const double alone = (esize == 8 ? 1.15 : 1.75) * (bytes > (256ll << 20) ? 1.45 : 1.0);
+  int best = target;
+  double best_t = 0.0;
+  for (int seg = target; seg >= 1; --seg) {
+    double work = 0.0;
+    long long w = 0;
+    int longest = 0;
+    for (const PlanBox* b : boxes) {
+      const long long bw = kind_waves(*b, kind, seg, groups, &par);
+      const int even = (b->n[D] + (b->n[D] + par - 1) / par - 1) / ((b->n[D] + par - 1) / par);
+      w += bw;
+      work += (double)bw * (even + halo);
+      longest = std::max(longest, even);
+    }
+    double t;
+    if (boxes.size() == 1) {
+      const double n = std::ceil((double)w / kSimds), full = std::floor(n / occupancy), rest = n - full * occupancy;
+      t = (longest + halo) * (full * std::max(alone, occupancy) + (rest > 0.0 ? std::max(alone, rest) : 0.0));
+    } else {
+      t = std::max((longest + halo) * alone, work / kSimds);
+    }
+    if (seg == target || t < best_t) {
+      best_t = t;
+      best = seg;
+    }
+  }
+  return best;
+}
+
+// Segments per pencil of a y/z kind, ceil(n_d / segment length); 0 for the
+// other kinds.
+inline int kind_segments(const PlanBox& b, int kind, int par) {
+  if (kind == K_FLUID_X) return (b.n[0] + par - 1) / par;  // read by the strided layout only
+  if (kind == K_FLUID_Y || kind == K_FIELD_Y) return (b.n[1] + par - 1) / par;
+  if (kind == K_FLUID_Z || kind == K_FIELD_Z) return (b.n[2] + par - 1) / par;
+  return 0;
+}
+
+// Rows along the sweep of a y/z kind, the work of the lanes policy.
+inline long long lane_rows(const PlanBox& b, int kind) {
+  const bool field = kind >= K_FIELD_X;
+  const int D = field ? kind - K_FIELD_X : kind - K_FLUID_X;
+  const int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  return (long long)(b.n[t1] + (field ? b.o[t1] : 0)) * (b.n[t2] + (field ? b.o[t2] : 0));
+}
+
+// Whether a y/z kind takes the lanes policy: for boxes so small that a launch
+// lasts as long as one wave's walk, which lanes along the sweep shorten to a
+// window or two, and their uncoalesced accesses stay in the caches.  Double
+// step, FP32, walks -> lanes of two cells: 32^3 113 -> 83 us (16^3 FP64 115 -> 70), 40^3 123
+// -> 106, 48^3 128 -> 128, 56^3 147 -> 163, 64^3 161 -> 217.
+inline bool planned_lanes(const std::vector<const PlanBox*>& boxes, int kind) {
+  if (kind == K_FLUID_X || kind == K_FIELD_X || kind == K_CHECK) return false;
+  const int D = kind >= K_FIELD_X ? kind - K_FIELD_X : kind - K_FLUID_X;
+  long long cells = 0;
+  for (const PlanBox* b : boxes) {
+    cells += (long long)b->n[0] * b->n[1] * b->n[2];
+    if (b->n[D] < 4) return false;  // rows mostly of ghosts
+  }
+  return cells <= 100000;
+}
+
+// Segments of equal length (to a cell) instead of full ones and a remainder.
+inline int even_segments(const PlanBox& b, int kind, int par) {
+  const int k = kind_segments(b, kind, par);
+  return k > 0 ? (b.n[kind <= K_FLUID_Z ? kind - K_FLUID_X : kind - K_FIELD_X] + k - 1) / k : par;
+}
+
+// How the boxes of a table are cut for a kind.
+struct KindPlan {
+  int target = 1;
+  bool planned = false;  // the shape was left at its default and is planned
+  bool lanes = false;    // y/z kinds: the lanes policy
+};
+
+// A shape left at its default is planned for the boxes; one set by
+// fish_set_shape or the autotuner is used as set.
+inline KindPlan plan_kind(const std::vector<const PlanBox*>& boxes, int kind, const Tuning& tuning, size_t esize) {
+  KindPlan p;
+  p.planned = !boxes.empty() && tuning.target[kind] == default_tuning().target[kind];
+  p.lanes = p.planned && planned_lanes(boxes, kind);
+  p.target = tuning.target[kind];
+  if (p.planned && !p.lanes) p.target = planned_target(boxes, kind, p.target, tuning.groups[kind], esize);
+  return p;
+}
+
+// A box's part of a kind's list: BoxDesc::par and nseg, and its waves.
+struct BoxShape {
+  int par = 1, nseg = 0;
+  long long waves = 0;
+};
+
+inline BoxShape box_shape(const PlanBox& b, int kind, const KindPlan& p, int groups) {
+  BoxShape s;
+  if (p.lanes) {
+    s.waves = lane_rows(b, kind);
+    return s;
+  }
+  s.waves = kind_waves(b, kind, p.target, groups, &s.par);
+  if (p.planned && kind != K_FLUID_X) s.par = even_segments(b, kind, s.par);
+  s.nseg = kind_segments(b, kind, s.par);
+  return s;
+}
+
+// A box alone in its table at the default tuning.  With more than max_waves
+// waves the x field sweep takes several short rows per wave.
+inline void plan_single_box(const int n[3], const int bc[3], size_t esize, long long max_waves, BoxShape shape[K_NUM],
+                            bool lanes[K_NUM]) {
+  PlanBox b;
+  for (int a = 0; a < 3; ++a) {
+    b.n[a] = n[a];
+    b.o[a] = bc[a] == 1 ? 1 : 0;
+  }
+  b.nelem = (long long)(n[0] + b.o[0]) * (n[1] + b.o[1]) * (n[2] + b.o[2]);
+  const Tuning t = default_tuning();
+  for (int k = 0; k < K_NUM; ++k) {
+    KindPlan p = plan_kind({&b}, k, t, esize);
+    shape[k] = box_shape(b, k, p, t.groups[k]);
+    if (k == K_FIELD_X && shape[k].waves > max_waves) {
+      p.target *= 2;
+      shape[k] = box_shape(b, k, p, t.groups[k]);
+    }
+    lanes[k] = p.lanes;
+  }
+}
+
+}  // namespace fish
