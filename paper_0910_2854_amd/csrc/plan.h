@@ -186,15 +186,32 @@ inline long long lane_rows(const PlanBox& b, int kind) {
 // window or two, and their uncoalesced accesses stay in the caches.  Double
 // step, FP32, walks -> lanes of two cells: 32^3 113 -> 83 us (16^3 FP64 115 -> 70), 40^3 123
 // -> 106, 48^3 128 -> 128, 56^3 147 -> 163, 64^3 161 -> 217.
+//   The rows have to be short, since one is the least a wave gets: the four of a
+// block are one window a wave up to 112 cells.  L_z, FP32, lanes and the best
+// segments: 8x8 rows of 120 10.4 and 11.5 us, of 200 13.8 and 11.7, of 2000 (7x7)
+// 131 and 13; FP64 12x12 rows of 130 13.3 and 13.7, of 400 29.6 and 15.4.  In y the
+// lanes are n_x apart and share lines where that is little (and walks, whose lanes
+// are along x, do not): n_x = 1, rows of 300 11.3 and 28.4, of 700 16.8 and 27.1;
+// n_x = 3, rows of 300 11.9 and 16.7; n_x = 6, rows of 200 11.8 and 14.3; n_x = 4,
+// rows of 500 19.6 and 14.2.
+//   And there have to be few, since short ones leave three waves of a block without
+// a window: L_y, FP64, 24000 rows of 4 24.6 us and in segments 16.2, 16000 of 6 18.6
+// and 16.7, 14000 of 7 17.1 and 16.4 (the step of 2000x7x7 273 and 269 us, FP32
+// 211 and 222).
+inline int longest_lane_row(const PlanBox& b, int D) {
+  if (D == 1 && b.n[0] <= 6) return b.n[0] == 1 ? 712 : b.n[0] <= 3 ? 352 : 232;
+  return 128;
+}
 inline bool planned_lanes(const std::vector<const PlanBox*>& boxes, int kind) {
   if (kind == K_FLUID_X || kind == K_FIELD_X || kind == K_CHECK) return false;
   const int D = kind >= K_FIELD_X ? kind - K_FIELD_X : kind - K_FLUID_X;
-  long long cells = 0;
+  long long cells = 0, rows = 0;
   for (const PlanBox* b : boxes) {
     cells += (long long)b->n[0] * b->n[1] * b->n[2];
-    if (b->n[D] < 4) return false;  // rows mostly of ghosts
+    rows += lane_rows(*b, kind);
+    if (b->n[D] < 4 || b->n[D] > longest_lane_row(*b, D)) return false;
   }
-  return cells <= 100000;
+  return cells <= 100000 && rows <= 14400;
 }
 
 // Segments of equal length (to a cell) instead of full ones and a remainder.

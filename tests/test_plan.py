@@ -1,0 +1,81 @@
+"""The planning of the sweeps' work shapes (csrc/plan.h), which is host arithmetic:
+compiled by itself and called on the CPU."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+KINDS = ["fluid_x", "fluid_y", "fluid_z", "field_x", "field_y", "field_z", "check"]
+SOURCE = r"""
+#include "plan.h"
+using namespace fish;
+static std::vector<PlanBox> boxes_of(const int* n, int count, int outflow) {
+  std::vector<PlanBox> v(count);
+  for (int i = 0; i < count; ++i) {
+    v[i].nelem = 1;
+    for (int a = 0; a < 3; ++a) {
+      v[i].n[a] = n[3 * i + a];
+      v[i].o[a] = outflow;
+      v[i].nelem *= v[i].n[a] + outflow;
+    }
+  }
+  return v;
+}
+extern "C" void plan(const int* n, int count, int outflow, int kind, int esize, int* target, int* lanes) {
+  const std::vector<PlanBox> v = boxes_of(n, count, outflow);
+  std::vector<const PlanBox*> p;
+  for (const PlanBox& b : v) p.push_back(&b);
+  const KindPlan k = plan_kind(p, kind, default_tuning(), esize);
+  *target = k.target;
+  *lanes = k.lanes;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    src, out = d / "plan_calls.cpp", d / "plan_calls.so"
+    src.write_text(SOURCE)
+    csrc = os.path.join(ROOT, "paper_0910_2854_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", csrc, str(src), "-o", str(out)], check=True)
+    return ctypes.CDLL(str(out))
+
+
+def plan(lib, boxes, kind, outflow=0, esize=4):
+    n = np.ascontiguousarray(boxes, dtype=np.int32).reshape(-1, 3)
+    target, lanes = ctypes.c_int(), ctypes.c_int()
+    lib.plan(n.ctypes.data_as(ctypes.c_void_p), len(n), outflow, KINDS.index(kind), esize, ctypes.byref(target),
+             ctypes.byref(lanes))
+    return target.value, bool(lanes.value)
+
+
+@pytest.mark.parametrize("op", ["fluid", "field"])
+def test_small_compact_boxes_take_lanes(lib, op):
+    for n in ((16, 16, 16), (32, 32, 32), (46, 46, 46), (20, 128, 30), (20, 30, 128), (4, 4, 4), (12, 12, 80), (700, 11, 11)):
+        for d in "yz":
+            assert plan(lib, n, f"{op}_{d}")[1], (n, d)
+    assert plan(lib, (2000, 7, 7), f"{op}_y")[1]
+    # along y where the lanes, n_x apart, share lines
+    for n in ((1, 700, 140), (3, 300, 100), (6, 200, 80)):
+        assert plan(lib, n, f"{op}_y")[1], n
+
+
+@pytest.mark.parametrize("op", ["fluid", "field"])
+def test_long_rows_and_many_short_ones_take_segments(lib, op):
+    """One row is the least a wave of lanes gets: rows of several windows, or very
+    many rows of a few cells, are slower than segments (fluid_z of 4x4x6000 FP32:
+    297 us on lanes, 16 on segments)."""
+    for n, d in (((4, 4, 6000), "z"), ((7, 7, 2000), "z"), ((10, 10, 900), "z"), ((12, 12, 400), "z"),
+                 ((300, 1, 300), "z"), ((20, 20, 240), "z"), ((4, 6000, 4), "y"), ((7, 2000, 7), "y"),
+                 ((300, 300, 1), "y"), ((100, 300, 3), "y"), ((4, 500, 50), "y"),
+                 ((4, 6000, 4), "z"), ((6000, 4, 4), "y"), ((46, 46, 48), "z")):
+        for outflow in (0, 1):
+            target, lanes = plan(lib, n, f"{op}_{d}", outflow)
+            assert not lanes, (n, d)
+            assert 1 <= target <= 64
+    # one such box in a table of small ones
+    assert not plan(lib, [(16, 16, 16), (4, 4, 500)], f"{op}_z")[1]
