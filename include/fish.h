@@ -205,19 +205,26 @@ enum {
  * blocks of a launch on one XCD, sharing its L2), and with an alternative
  * layout: for the y/z kinds the four waves of a block on four consecutive
  * rows instead of contiguous pencils, for the x field kind none (the value is
- * accepted and has no effect), for the check kind the CFL speed of a step's new state reduced by the check kernel after the last x sweep
- * instead of inside it (the same value either way).  The x fluid kind has
- * an alternative layout too, the strided policy with the lanes along y and
- * the shape as its segment length; the autotuner does not try it (set it
- * with fish_set_shape), and with it the check kernel reduces the CFL speed.  targets_out (may be NULL) receives
- * FISH_NUM_KINDS chosen values: the shape in bits 0-15, the block order
- * (1 = XCD-grouped) in bit 16, the alternative layout in bit 17.
+ * accepted and has no effect), for the check kind the CFL speed of a step's
+ * new state reduced by the check kernel after the last x sweep instead of
+ * inside it (the same value either way).  The x fluid kind has an alternative
+ * layout too, the strided policy with the lanes along y and the shape as its
+ * segment length; the autotuner does not try it (set it with fish_set_shape),
+ * and with it the check kernel reduces the CFL speed.  The shape of a kind at
+ * its default (1536 and 384 positions for the x fluid and field kinds, 64 for
+ * the y/z kinds, 16 cells per lane for the check) is planned for the boxes at
+ * hand and can be another length, or for the y/z kinds of small boxes lanes
+ * along the sweep; the default value stands for that planned shape, here and
+ * in fish_set_shape.  targets_out (may be NULL) receives FISH_NUM_KINDS chosen
+ * values: the shape in bits 0-15, the block order (1 = XCD-grouped) in bit 16,
+ * the alternative layout in bit 17.
  * Results do not depend on the shapes (each cell is computed by the same
  * operations whatever wave computes it).  Synchronises the stream. */
 int fish_autotune(fish_ctx* ctx, int reps, int32_t* targets_out);
 
 /* Set one kind's work shape directly, in the encoding fish_autotune returns
- * (for reproducing a tuned configuration).  FISH_ERR_ARG for an unknown kind
+ * (for reproducing a tuned configuration): used as set, but for a kind's
+ * default, which stands for the planned shape.  FISH_ERR_ARG for an unknown kind
  * or a value outside the encoding. */
 int fish_set_shape(fish_ctx* ctx, int kind, int32_t value);
 

@@ -507,7 +507,8 @@ class Box:
         self._check(self._lib.fish_set_spacing(self._h, int(axis), w.ctypes.data_as(ctypes.POINTER(ctypes.c_double))))
 
     def set_shape(self, kind, target, xcd_remap=0, alt_layout=0):
-        """Set one kind's work shape (kind: a name of KINDS)."""
+        """Set one kind's work shape (kind: a name of KINDS).  A kind's default target (1536 for fluid_x,
+        384 for field_x, 64 for the y/z kinds, 16 for check) stands for the shape planned for the box."""
         self._check(self._lib.fish_set_shape(self._h, KINDS.index(kind), shape_value(target, xcd_remap, alt_layout)))
 
     def autotune(self, reps=3):

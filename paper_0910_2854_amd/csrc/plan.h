@@ -223,16 +223,18 @@ inline int even_segments(const PlanBox& b, int kind, int par) {
 // How the boxes of a table are cut for a kind.
 struct KindPlan {
   int target = 1;
-  bool planned = false;  // the shape was left at its default and is planned
+  bool planned = false;  // the default target: the shape is planned
   bool lanes = false;    // y/z kinds: the lanes policy
 };
 
-// A shape left at its default is planned for the boxes; one set by
-// fish_set_shape or the autotuner is used as set.
+// The default target of a kind stands for the shape planned for the boxes,
+// whether it was left alone, set or found by the autotuner (whose output then
+// sets it again); any other target is used as set.  A layout that is set keeps
+// the kernel that has it: no lanes policy.
 inline KindPlan plan_kind(const std::vector<const PlanBox*>& boxes, int kind, const Tuning& tuning, size_t esize) {
   KindPlan p;
   p.planned = !boxes.empty() && tuning.target[kind] == default_tuning().target[kind];
-  p.lanes = p.planned && planned_lanes(boxes, kind);
+  p.lanes = p.planned && !tuning.groups[kind] && planned_lanes(boxes, kind);
   p.target = tuning.target[kind];
   if (p.planned && !p.lanes) p.target = planned_target(boxes, kind, p.target, tuning.groups[kind], esize);
   return p;

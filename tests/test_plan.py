@@ -24,11 +24,15 @@ static std::vector<PlanBox> boxes_of(const int* n, int count, int outflow) {
   }
   return v;
 }
-extern "C" void plan(const int* n, int count, int outflow, int kind, int esize, int* target, int* lanes) {
+extern "C" void plan(const int* n, int count, int outflow, int kind, int esize, int set, int layout, int* target,
+                     int* lanes) {
   const std::vector<PlanBox> v = boxes_of(n, count, outflow);
   std::vector<const PlanBox*> p;
   for (const PlanBox& b : v) p.push_back(&b);
-  const KindPlan k = plan_kind(p, kind, default_tuning(), esize);
+  Tuning t = default_tuning();
+  if (set) t.target[kind] = set;
+  t.groups[kind] = layout;
+  const KindPlan k = plan_kind(p, kind, t, esize);
   *target = k.target;
   *lanes = k.lanes;
 }
@@ -45,12 +49,12 @@ def lib(tmp_path_factory):
     return ctypes.CDLL(str(out))
 
 
-def plan(lib, boxes, kind, outflow=0, esize=4):
+def plan(lib, boxes, kind, outflow=0, esize=4, target=0, layout=0):
     n = np.ascontiguousarray(boxes, dtype=np.int32).reshape(-1, 3)
-    target, lanes = ctypes.c_int(), ctypes.c_int()
-    lib.plan(n.ctypes.data_as(ctypes.c_void_p), len(n), outflow, KINDS.index(kind), esize, ctypes.byref(target),
-             ctypes.byref(lanes))
-    return target.value, bool(lanes.value)
+    got, lanes = ctypes.c_int(), ctypes.c_int()
+    lib.plan(n.ctypes.data_as(ctypes.c_void_p), len(n), outflow, KINDS.index(kind), esize, target, layout,
+             ctypes.byref(got), ctypes.byref(lanes))
+    return got.value, bool(lanes.value)
 
 
 @pytest.mark.parametrize("op", ["fluid", "field"])
@@ -79,3 +83,18 @@ def test_long_rows_and_many_short_ones_take_segments(lib, op):
             assert 1 <= target <= 64
     # one such box in a table of small ones
     assert not plan(lib, [(16, 16, 16), (4, 4, 500)], f"{op}_z")[1]
+
+
+def test_set_shapes(lib):
+    """Any target but a kind's default is used as set; the default stands for the
+    planned shape, in the layout that is set."""
+    for n in ((32, 32, 32), (100, 90, 60)):
+        for kind, default in zip(KINDS[:6], (1536, 64, 64, 384, 64, 64)):
+            for layout in (0, 1):
+                for target in (63, 400):
+                    assert plan(lib, n, kind, target=target, layout=layout) == (target, False)
+            assert plan(lib, n, kind, target=default) == plan(lib, n, kind)
+    for kind in ("fluid_y", "fluid_z", "field_y", "field_z"):
+        assert plan(lib, (32, 32, 32), kind)[1]
+        target, lanes = plan(lib, (32, 32, 32), kind, target=64, layout=1)
+        assert not lanes and target < 32
