@@ -1134,39 +1134,23 @@ int Engine::autotune(int reps, int* chosen) {
   hipLaunchKernelGGL(finalize_dt_kernel, dim3(grid_for(nb)), dim3(kBlock), 0, cfg.stream, (const BoxDesc*)table.ptr,
                      nb, (Scalars*)scal.ptr);
   if ((rc = launch_check())) return rc;
-  static const int lanes_c[] = {256, 384, 512, 768, 1024, 1536, 2048, 3072, 4096, 6144};
-  static const int seg_c[] = {8, 16, 24, 32, 48, 64, 96, 128, 192, 256};
+  std::vector<const PlanBox*> all;
+  for (int s : table_slots) all.push_back(&boxes[s]);
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
   const int saved_mask = timing_mask;
   timing_mask = 0;
   for (int kind = K_FLUID_X; kind <= K_FIELD_Z; ++kind) {
-    const bool lanes = kind == K_FLUID_X || kind == K_FIELD_X;
-    const int* cand = lanes ? lanes_c : seg_c;
-    const int ncand = lanes ? (int)(sizeof lanes_c / sizeof(int)) : (int)(sizeof seg_c / sizeof(int));
-    // second knob: the pencil order of the y/z kinds
-    const int nord = lanes ? 1 : 2;
     const int op = kind >= K_FIELD_X ? 1 : 0;
     const int d = op ? kind - K_FIELD_X : kind - K_FLUID_X;
     float best = 1e30f;
     int best_t = tuning.target[kind], best_r = tuning.remap[kind], best_g = tuning.groups[kind];
-    std::vector<long long> seen;
-    for (int cj = 0; cj < ncand * 2 * nord && !rc; ++cj) {
-      const int ci = cj / (2 * nord), r = cj % 2, g = (cj / 2) % nord;
-      tuning.target[kind] = cand[ci];
-      tuning.remap[kind] = r;
-      tuning.groups[kind] = g;
-      // skip variants that give every box a shape already timed
-      long long sig = 0;
-      for (int s : table_slots) {
-        int par = 0;
-        const long long w = kind_waves(boxes[s], kind, cand[ci], g, &par);
-        sig = sig * 1000003 + par * 7919 + w;
-      }
-      sig = sig * 4 + r * 2 + g;
-      if (std::find(seen.begin(), seen.end(), sig) != seen.end()) continue;
-      seen.push_back(sig);
+    for (const Variant& v : tuner_variants(all, kind, tuning, esize)) {
+      if (rc) break;
+      tuning.target[kind] = v.target;
+      tuning.remap[kind] = v.remap;
+      tuning.groups[kind] = v.groups;
       if ((rc = build_lists())) break;
       int saved[8];
       std::memcpy(saved, cur, sizeof cur);
@@ -1197,9 +1181,9 @@ int Engine::autotune(int reps, int* chosen) {
       (void)hipEventElapsedTime(&ms, e0, e1);
       if (ms < best) {
         best = ms;
-        best_t = cand[ci];
-        best_r = r;
-        best_g = g;
+        best_t = v.target;
+        best_r = v.remap;
+        best_g = v.groups;
       }
     }
     tuning.target[kind] = best_t;

@@ -258,6 +258,40 @@ inline BoxShape box_shape(const PlanBox& b, int kind, const KindPlan& p, int gro
   return s;
 }
 
+// The variants of a kind that the autotuner times: the default target first, which
+// stands for the planned shape, then set ones; each with both block orders and,
+// for the y/z kinds, both pencil orders.  A variant that cuts every box as an
+// earlier one does is left out.
+struct Variant {
+  int target, remap, groups;
+};
+
+inline std::vector<Variant> tuner_variants(const std::vector<const PlanBox*>& boxes, int kind, Tuning tuning,
+                                           size_t esize) {
+  const bool x = kind == K_FLUID_X || kind == K_FIELD_X;
+  std::vector<int> targets = {default_tuning().target[kind]};
+  for (int t : x ? std::vector<int>{256, 384, 512, 768, 1024, 1536, 2048, 3072, 4096, 6144}
+                 : std::vector<int>{8, 16, 24, 32, 48, 64, 96, 128, 192, 256})
+    if (t != targets[0]) targets.push_back(t);
+  std::vector<Variant> out;
+  std::vector<std::vector<long long>> seen;
+  for (int t : targets)
+    for (int g = 0; g < (x ? 1 : 2); ++g) {
+      tuning.target[kind] = t;
+      tuning.groups[kind] = g;
+      const KindPlan p = plan_kind(boxes, kind, tuning, esize);
+      std::vector<long long> cut = {g, p.lanes};
+      for (const PlanBox* b : boxes) {
+        const BoxShape s = box_shape(*b, kind, p, g);
+        cut.insert(cut.end(), {s.par, s.nseg, s.waves});
+      }
+      if (std::find(seen.begin(), seen.end(), cut) != seen.end()) continue;
+      seen.push_back(cut);
+      for (int r = 0; r < 2; ++r) out.push_back({t, r, g});
+    }
+  return out;
+}
+
 // A box alone in its table at the default tuning.  With more than max_waves
 // waves the x field sweep takes several short rows per wave.
 inline void plan_single_box(const int n[3], const int bc[3], size_t esize, long long max_waves, BoxShape shape[K_NUM],

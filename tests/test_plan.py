@@ -36,6 +36,18 @@ extern "C" void plan(const int* n, int count, int outflow, int kind, int esize, 
   *target = k.target;
   *lanes = k.lanes;
 }
+extern "C" int variants(const int* n, int count, int kind, int esize, int* out) {
+  const std::vector<PlanBox> v = boxes_of(n, count, 0);
+  std::vector<const PlanBox*> p;
+  for (const PlanBox& b : v) p.push_back(&b);
+  int m = 0;
+  for (const Variant& x : tuner_variants(p, kind, default_tuning(), esize)) {
+    out[m++] = x.target;
+    out[m++] = x.remap;
+    out[m++] = x.groups;
+  }
+  return m / 3;
+}
 """
 
 
@@ -98,3 +110,23 @@ def test_set_shapes(lib):
         assert plan(lib, (32, 32, 32), kind)[1]
         target, lanes = plan(lib, (32, 32, 32), kind, target=64, layout=1)
         assert not lanes and target < 32
+
+
+def variants(lib, boxes, kind, esize=4):
+    n = np.ascontiguousarray(boxes, dtype=np.int32).reshape(-1, 3)
+    out = np.zeros(3 * 64, dtype=np.int32)
+    m = lib.variants(n.ctypes.data_as(ctypes.c_void_p), len(n), KINDS.index(kind), esize,
+                     out.ctypes.data_as(ctypes.c_void_p))
+    return [tuple(int(x) for x in v) for v in out[:3 * m].reshape(-1, 3)]
+
+
+@pytest.mark.parametrize("boxes", [(24, 24, 24), (32, 32, 32), (48, 48, 48), (100, 90, 60), (256, 256, 256),
+                                   [(16, 16, 16), (32, 32, 32)]])
+def test_autotuner_times_the_planned_shape(lib, boxes):
+    """The default target stands for the planned shape: it is timed first, in both
+    block orders, whatever the set shapes clip to; and no shape is timed twice."""
+    for kind, default in zip(KINDS[:6], (1536, 64, 64, 384, 64, 64)):
+        v = variants(lib, boxes, kind)
+        assert v[0] == (default, 0, 0) and v[1] == (default, 1, 0), (kind, v)
+        assert len(set(v)) == len(v)
+        assert any(t != default for t, _, _ in v)
