@@ -10,6 +10,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KINDS = ["fluid_x", "fluid_y", "fluid_z", "field_x", "field_y", "field_z", "check"]
 SOURCE = r"""
+#include <chrono>
 #include "plan.h"
 using namespace fish;
 static std::vector<PlanBox> boxes_of(const int* n, int count, int outflow) {
@@ -48,6 +49,21 @@ extern "C" int variants(const int* n, int count, int kind, int esize, int* out) 
   }
   return m / 3;
 }
+extern "C" double plan_us(const int* n, int count, int planned) {
+  const std::vector<PlanBox> v = boxes_of(n, count, 0);
+  std::vector<const PlanBox*> p;
+  for (const PlanBox& b : v) p.push_back(&b);
+  const Tuning t = default_tuning();
+  const auto t0 = std::chrono::steady_clock::now();
+  volatile long long waves = 0;
+  for (int k = 0; k < K_NUM; ++k) {
+    KindPlan plan;
+    plan.target = t.target[k];
+    if (planned) plan = plan_kind(p, k, t, 4);
+    for (const PlanBox& b : v) waves = waves + box_shape(b, k, plan, t.groups[k]).waves;
+  }
+  return std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count();
+}
 """
 
 
@@ -58,7 +74,9 @@ def lib(tmp_path_factory):
     src.write_text(SOURCE)
     csrc = os.path.join(ROOT, "paper_0910_2854_amd", "csrc")
     subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", csrc, str(src), "-o", str(out)], check=True)
-    return ctypes.CDLL(str(out))
+    lib = ctypes.CDLL(str(out))
+    lib.plan_us.restype = ctypes.c_double
+    return lib
 
 
 def plan(lib, boxes, kind, outflow=0, esize=4, target=0, layout=0):
@@ -130,3 +148,12 @@ def test_autotuner_times_the_planned_shape(lib, boxes):
         assert v[0] == (default, 0, 0) and v[1] == (default, 1, 0), (kind, v)
         assert len(set(v)) == len(v)
         assert any(t != default for t, _, _ in v)
+
+
+def test_planning_many_small_boxes_costs_about_what_their_lists_do(lib):
+    """Every change of a table plans it anew: 1000 equal boxes take a few times as
+    long as their wave counts (60 times as long with every segment length tried on
+    every box)."""
+    n = np.full((1000, 3), 12, dtype=np.int32)
+    best = [min(lib.plan_us(n.ctypes.data_as(ctypes.c_void_p), 1000, planned) for _ in range(20)) for planned in (0, 1)]
+    assert best[1] <= 20.0 * best[0], best
