@@ -657,10 +657,11 @@ int Engine::build_lists() {
     }
   KindPlan plan[K_NUM];
   {
-    std::vector<const PlanBox*> all;
-    for (int s : slots) all.push_back(&boxes[s]);
+    Forms forms;
+    for (int s : slots) forms.add(boxes[s]);
+    forms.merge();
     for (int k = 0; k < K_NUM; ++k) {
-      plan[k] = plan_kind(all, k, tuning, esize);
+      plan[k] = plan_kind(forms, k, tuning, esize);
       lanes[k] = plan[k].lanes;
     }
   }
@@ -1134,8 +1135,9 @@ int Engine::autotune(int reps, int* chosen) {
   hipLaunchKernelGGL(finalize_dt_kernel, dim3(grid_for(nb)), dim3(kBlock), 0, cfg.stream, (const BoxDesc*)table.ptr,
                      nb, (Scalars*)scal.ptr);
   if ((rc = launch_check())) return rc;
-  std::vector<const PlanBox*> all;
-  for (int s : table_slots) all.push_back(&boxes[s]);
+  Forms forms;
+  for (int s : table_slots) forms.add(boxes[s]);
+  forms.merge();
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
@@ -1146,7 +1148,7 @@ int Engine::autotune(int reps, int* chosen) {
     const int d = op ? kind - K_FIELD_X : kind - K_FLUID_X;
     float best = 1e30f;
     int best_t = tuning.target[kind], best_r = tuning.remap[kind], best_g = tuning.groups[kind];
-    for (const Variant& v : tuner_variants(all, kind, tuning, esize)) {
+    for (const Variant& v : tuner_variants(forms, kind, tuning, esize)) {
       if (rc) break;
       tuning.target[kind] = v.target;
       tuning.remap[kind] = v.remap;

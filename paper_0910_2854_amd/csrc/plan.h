@@ -17,6 +17,42 @@ struct PlanBox {
   long long nelem = 0;  // elements per array
 };
 
+// The boxes of a table by form: boxes of the same cells and layers are planned
+// together, so that a plan costs what the forms do and not what the boxes do
+// (every change of the table makes one; 1000 boxes of 12^3: 4.1 ms with
+// every segment length tried on every box, 0.02 ms so).
+struct Forms {
+  struct Form : PlanBox {
+    long long count = 0;
+    bool operator<(const Form& f) const {
+      return std::lexicographical_compare(n, n + 3, f.n, f.n + 3) ||
+             (std::equal(n, n + 3, f.n) && std::lexicographical_compare(o, o + 3, f.o, f.o + 3));
+    }
+  };
+  std::vector<Form> forms;
+  long long boxes = 0;
+
+  void add(const PlanBox& b, long long count = 1) {
+    boxes += count;
+    if (!forms.empty() && std::equal(b.n, b.n + 3, forms.back().n) && std::equal(b.o, b.o + 3, forms.back().o)) {
+      forms.back().count += count;
+      return;
+    }
+    forms.emplace_back();
+    static_cast<PlanBox&>(forms.back()) = b;
+    forms.back().count = count;
+  }
+  // after the last box: equal forms that were not added one after another
+  void merge() {
+    if (forms.size() < 3) return;  // (of two, neither is the other)
+    std::sort(forms.begin(), forms.end());
+    std::vector<Form> all;
+    all.swap(forms);
+    boxes = 0;
+    for (const Form& f : all) add(f, f.count);
+  }
+};
+
 // Tuning targets per kernel kind: stream positions per wave for the x kinds
 // (whole rows of the box fill it), the segment length along the sweep for
 // the y/z kinds, cells per lane for the CFL check.
@@ -103,74 +139,51 @@ inline long long kind_waves(const PlanBox& b, int kind, int target, int groups, 
 // no shorter than 8, and so: 32^3 FP32 18.0 -> 12.8 us (8 -> 2 cells), 64^3 FP32
 // 20.0 -> 16.7 (8 -> 4), FP64 24.1 -> 21.2.  Boxes of several sizes are taken
 // together, by the longest walk or the sum of the work.
-inline int planned_target(const std::vector<const PlanBox*>& boxes, int kind, int target, int groups, size_t esize) {
-  if (kind == K_CHECK) {
+inline int planned_target(const Forms& table, int kind, int target, int groups, size_t esize) {
+  int par = 1;
+  auto waves_at = [&](int t) {
     long long w = 0;
-    int par = 1;
-    for (;;) {
-      w = 0;
-      for (const PlanBox* b : boxes) w += kind_waves(*b, kind, target, groups, &par);
-      if (w >= 2048 || target < 2) return target;
-      target /= 2;
-    }
+    for (const Forms::Form& f : table.forms) w += f.count * kind_waves(f, kind, t, groups, &par);
+    return w;
+  };
+  if (kind == K_CHECK) {
+    while (target > 1 && waves_at(target) < 2048) target /= 2;
+    return target;
   }
   if (kind == K_FIELD_X || (kind == K_FLUID_X && !groups)) {
-    int lo = 0, par = 1;
-    for (const PlanBox* b : boxes) lo = std::max(lo, b->n[0] + 8);
-    for (;;) {
-      long long w = 0;
-      for (const PlanBox* b : boxes) w += kind_waves(*b, kind, target, groups, &par);
-      if (w >= 4096 || target / 2 < lo) return target;
-      target /= 2;
-    }
+    int lo = 0;
+    for (const Forms::Form& f : table.forms) lo = std::max(lo, f.n[0] + 8);
+    while (target / 2 >= lo && waves_at(target) < 4096) target /= 2;
+    return target;
   }
+  if (waves_at(target) >= 4096) return target;
   const int D = kind == K_FLUID_X ? 0 : kind <= K_FLUID_Z ? kind - K_FLUID_X : kind - K_FIELD_X;
   const int halo = kind <= K_FLUID_Z ? 6 : 8;
-  // boxes alike in waves per segment and cells along the sweep count together:
-  // the scan below is over forms, not boxes (1000 boxes of 12^3: 4.1 ms of every
-  // change of the table, 0.25 so)
-  struct Form {
-    long long waves, count;
-    int n;
-    bool operator<(const Form& f) const { return waves != f.waves ? waves < f.waves : n < f.n; }
-  };
-  std::vector<Form> forms;
-  auto count = [&forms](const Form& f) {
-    if (!forms.empty() && forms.back().waves == f.waves && forms.back().n == f.n)
-      forms.back().count += f.count;
-    else
-      forms.push_back(f);
-  };
-  long long bytes = 0, waves = 0;
-  int par = 1, longest_n = 1;
-  for (const PlanBox* b : boxes) {
-    bytes += 16ll * (long long)esize * b->nelem;
-    waves += kind_waves(*b, kind, target, groups, &par);
-    longest_n = std::max(longest_n, b->n[D]);
-    count({kind_waves(*b, kind, b->n[D], groups, &par), 1, b->n[D]});
+  long long bytes = 0;
+  int longest_n = 1;
+  std::vector<long long> segment_waves;
+  for (const Forms::Form& f : table.forms) {
+    bytes += 16ll * (long long)esize * f.nelem * f.count;
+    longest_n = std::max(longest_n, f.n[D]);
+    segment_waves.push_back(f.count * kind_waves(f, kind, f.n[D], groups, &par));
   }
-  if (waves >= 4096) return target;
-  std::vector<Form> all;
-  all.swap(forms);
-  std::sort(all.begin(), all.end());
-  for (const Form& f : all) count(f);
   constexpr double kSimds = 1024.0;
   const double occupancy = esize == 8 ? 2.0 : 4.0;
   const double alone = (esize == 8 ? 1.15 : 1.75) * (bytes > (256ll << 20) ? 1.45 : 1.0);
   int best = target;
   double best_t = 0.0;
-  for (int seg = target; seg >= 1; seg = std::min(seg, longest_n) - 1) {
+  for (int seg = target; seg >= 1; seg = std::min(seg, longest_n) - 1) {  // past the longest box all are alike
     double work = 0.0;
     long long w = 0;
     int longest = 0;
-    for (const Form& f : forms) {
-      const int k = (f.n + seg - 1) / seg, even = (f.n + k - 1) / k;
-      w += f.count * f.waves * k;
-      work += (double)(f.count * f.waves * k) * (even + halo);
+    for (size_t i = 0; i < segment_waves.size(); ++i) {
+      const int n = table.forms[i].n[D], k = (n + seg - 1) / seg, even = (n + k - 1) / k;
+      w += segment_waves[i] * k;
+      work += (double)(segment_waves[i] * k) * (even + halo);
       longest = std::max(longest, even);
     }
     double t;
-    if (boxes.size() == 1) {
+    if (table.boxes == 1) {
       const double n = std::ceil((double)w / kSimds), full = std::floor(n / occupancy), rest = n - full * occupancy;
       t = (longest + halo) * (full * std::max(alone, occupancy) + (rest > 0.0 ? std::max(alone, rest) : 0.0));
     } else {
@@ -222,14 +235,14 @@ inline int longest_lane_row(const PlanBox& b, int D) {
   if (D == 1 && b.n[0] <= 6) return b.n[0] == 1 ? 712 : b.n[0] <= 3 ? 352 : 232;
   return 128;
 }
-inline bool planned_lanes(const std::vector<const PlanBox*>& boxes, int kind) {
+inline bool planned_lanes(const Forms& table, int kind) {
   if (kind == K_FLUID_X || kind == K_FIELD_X || kind == K_CHECK) return false;
   const int D = kind >= K_FIELD_X ? kind - K_FIELD_X : kind - K_FLUID_X;
   long long cells = 0, rows = 0;
-  for (const PlanBox* b : boxes) {
-    cells += (long long)b->n[0] * b->n[1] * b->n[2];
-    rows += lane_rows(*b, kind);
-    if (b->n[D] < 4 || b->n[D] > longest_lane_row(*b, D)) return false;
+  for (const Forms::Form& f : table.forms) {
+    cells += f.count * f.n[0] * f.n[1] * f.n[2];
+    rows += f.count * lane_rows(f, kind);
+    if (f.n[D] < 4 || f.n[D] > longest_lane_row(f, D)) return false;
   }
   return cells <= 100000 && rows <= 14400;
 }
@@ -251,12 +264,12 @@ struct KindPlan {
 // whether it was left alone, set or found by the autotuner (whose output then
 // sets it again); any other target is used as set.  A layout that is set keeps
 // the kernel that has it: no lanes policy.
-inline KindPlan plan_kind(const std::vector<const PlanBox*>& boxes, int kind, const Tuning& tuning, size_t esize) {
+inline KindPlan plan_kind(const Forms& table, int kind, const Tuning& tuning, size_t esize) {
   KindPlan p;
-  p.planned = !boxes.empty() && tuning.target[kind] == default_tuning().target[kind];
-  p.lanes = p.planned && !tuning.groups[kind] && planned_lanes(boxes, kind);
+  p.planned = table.boxes > 0 && tuning.target[kind] == default_tuning().target[kind];
+  p.lanes = p.planned && !tuning.groups[kind] && planned_lanes(table, kind);
   p.target = tuning.target[kind];
-  if (p.planned && !p.lanes) p.target = planned_target(boxes, kind, p.target, tuning.groups[kind], esize);
+  if (p.planned && !p.lanes) p.target = planned_target(table, kind, p.target, tuning.groups[kind], esize);
   return p;
 }
 
@@ -286,8 +299,7 @@ struct Variant {
   int target, remap, groups;
 };
 
-inline std::vector<Variant> tuner_variants(const std::vector<const PlanBox*>& boxes, int kind, Tuning tuning,
-                                           size_t esize) {
+inline std::vector<Variant> tuner_variants(const Forms& table, int kind, Tuning tuning, size_t esize) {
   const bool x = kind == K_FLUID_X || kind == K_FIELD_X;
   std::vector<int> targets = {default_tuning().target[kind]};
   for (int t : x ? std::vector<int>{256, 384, 512, 768, 1024, 1536, 2048, 3072, 4096, 6144}
@@ -299,10 +311,10 @@ inline std::vector<Variant> tuner_variants(const std::vector<const PlanBox*>& bo
     for (int g = 0; g < (x ? 1 : 2); ++g) {
       tuning.target[kind] = t;
       tuning.groups[kind] = g;
-      const KindPlan p = plan_kind(boxes, kind, tuning, esize);
+      const KindPlan p = plan_kind(table, kind, tuning, esize);
       std::vector<long long> cut = {g, p.lanes};
-      for (const PlanBox* b : boxes) {
-        const BoxShape s = box_shape(*b, kind, p, g);
+      for (const Forms::Form& f : table.forms) {
+        const BoxShape s = box_shape(f, kind, p, g);
         cut.insert(cut.end(), {s.par, s.nseg, s.waves});
       }
       if (std::find(seen.begin(), seen.end(), cut) != seen.end()) continue;
@@ -322,9 +334,11 @@ inline void plan_single_box(const int n[3], const int bc[3], size_t esize, long 
     b.o[a] = bc[a] == 1 ? 1 : 0;
   }
   b.nelem = (long long)(n[0] + b.o[0]) * (n[1] + b.o[1]) * (n[2] + b.o[2]);
+  Forms table;
+  table.add(b);
   const Tuning t = default_tuning();
   for (int k = 0; k < K_NUM; ++k) {
-    KindPlan p = plan_kind({&b}, k, t, esize);
+    KindPlan p = plan_kind(table, k, t, esize);
     shape[k] = box_shape(b, k, p, t.groups[k]);
     if (k == K_FIELD_X && shape[k].waves > max_waves) {
       p.target *= 2;

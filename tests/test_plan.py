@@ -13,6 +13,12 @@ SOURCE = r"""
 #include <chrono>
 #include "plan.h"
 using namespace fish;
+static Forms forms_of(const std::vector<PlanBox>& v) {
+  Forms f;
+  for (const PlanBox& b : v) f.add(b);
+  f.merge();
+  return f;
+}
 static std::vector<PlanBox> boxes_of(const int* n, int count, int outflow) {
   std::vector<PlanBox> v(count);
   for (int i = 0; i < count; ++i) {
@@ -28,21 +34,17 @@ static std::vector<PlanBox> boxes_of(const int* n, int count, int outflow) {
 extern "C" void plan(const int* n, int count, int outflow, int kind, int esize, int set, int layout, int* target,
                      int* lanes) {
   const std::vector<PlanBox> v = boxes_of(n, count, outflow);
-  std::vector<const PlanBox*> p;
-  for (const PlanBox& b : v) p.push_back(&b);
   Tuning t = default_tuning();
   if (set) t.target[kind] = set;
   t.groups[kind] = layout;
-  const KindPlan k = plan_kind(p, kind, t, esize);
+  const KindPlan k = plan_kind(forms_of(v), kind, t, esize);
   *target = k.target;
   *lanes = k.lanes;
 }
 extern "C" int variants(const int* n, int count, int kind, int esize, int* out) {
   const std::vector<PlanBox> v = boxes_of(n, count, 0);
-  std::vector<const PlanBox*> p;
-  for (const PlanBox& b : v) p.push_back(&b);
   int m = 0;
-  for (const Variant& x : tuner_variants(p, kind, default_tuning(), esize)) {
+  for (const Variant& x : tuner_variants(forms_of(v), kind, default_tuning(), esize)) {
     out[m++] = x.target;
     out[m++] = x.remap;
     out[m++] = x.groups;
@@ -51,11 +53,10 @@ extern "C" int variants(const int* n, int count, int kind, int esize, int* out) 
 }
 extern "C" double plan_us(const int* n, int count, int planned) {
   const std::vector<PlanBox> v = boxes_of(n, count, 0);
-  std::vector<const PlanBox*> p;
-  for (const PlanBox& b : v) p.push_back(&b);
   const Tuning t = default_tuning();
   const auto t0 = std::chrono::steady_clock::now();
   volatile long long waves = 0;
+  const Forms p = planned ? forms_of(v) : Forms();
   for (int k = 0; k < K_NUM; ++k) {
     KindPlan plan;
     plan.target = t.target[k];
@@ -151,9 +152,9 @@ def test_autotuner_times_the_planned_shape(lib, boxes):
 
 
 def test_planning_many_small_boxes_costs_about_what_their_lists_do(lib):
-    """Every change of a table plans it anew: 1000 equal boxes take a few times as
-    long as their wave counts (60 times as long with every segment length tried on
+    """Every change of a table plans it anew: 1000 equal boxes take little more
+    than their wave counts (60 times as long with every segment length tried on
     every box)."""
     n = np.full((1000, 3), 12, dtype=np.int32)
     best = [min(lib.plan_us(n.ctypes.data_as(ctypes.c_void_p), 1000, planned) for _ in range(20)) for planned in (0, 1)]
-    assert best[1] <= 20.0 * best[0], best
+    assert best[1] <= 4.0 * best[0], best
