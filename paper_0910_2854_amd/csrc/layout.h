@@ -37,8 +37,8 @@ struct BoxDesc {
   double cfl;         // Courant number of Eq. (14)
   int slot;           // index of the box's Scalars
   int wave0[K_NUM];   // first wave of the box in each kind's list
-  int par[K_NUM];     // rows per wave (x kinds), segment length (y/z kinds), cells per lane (check)
-  int nseg[K_NUM];    // y/z kinds: segments per pencil, ceil(n_d / par)
+  int par[K_NUM];     // lanes policy (x kinds, y/z kinds of small boxes): rows per wave; strided: segment length; check: cells per lane
+  int nseg[K_NUM];    // strided policy: segments per pencil, ceil(n_d / par)
   long long woff[3];  // irregular meshes: element offset of the box's cell widths in each axis's width array
   double ih[3], i2h[3];  // 1 / h_d and 1 / (2 h_d)
 };

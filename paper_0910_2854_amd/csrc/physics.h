@@ -192,6 +192,7 @@ __device__ __forceinline__ void cell_quantities(const T* u, const FieldQ<T>& f, 
 
 // Limiters, Eqs. (29)-(30).  minmod as the median of a, b and 0 (of finite
 // operands; with a NaN the FP32 instruction gives the least of the other two).
+// No product that could underflow decides the sign.
 __device__ __forceinline__ float minmod(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
 __device__ __forceinline__ double minmod(double a, double b) {
   return fmax(fmin(a, b), 0.0) + fmin(fmax(a, b), 0.0);

@@ -138,7 +138,11 @@ inline long long kind_waves(const PlanBox& b, int kind, int target, int groups, 
 // waves take the shortest time.  Measured, L_z, at 64 halved to 2048 waves but
 // no shorter than 8, and so: 32^3 FP32 18.0 -> 12.8 us (8 -> 2 cells), 64^3 FP32
 // 20.0 -> 16.7 (8 -> 4), FP64 24.1 -> 21.2.  Boxes of several sizes are taken
-// together, by the longest walk or the sum of the work.
+// together, by the longest walk or the sum of the work.  The resident waves and
+// `alone` are those of the plain scheme; FP64 with HSE, or with the
+// loads ahead of the limiter switch and the irregular mesh, has one wave per SIMD
+// and would take longer segments (L_y of 120^3 with HSE: 79 us at 32 cells, 91 at
+// 16).
 inline int planned_target(const Forms& table, int kind, int target, int groups, size_t esize) {
   int par = 1;
   auto waves_at = [&](int t) {

@@ -7,20 +7,21 @@
 // 0 and is never stored.  Ghost cells are never stored either: every load
 // maps its index (periodic wrap, or clamp for zeroth-order extrapolation).
 //
-// Both sweeps are written once as a streaming pipeline over the positions of
-// a pencil: when cell c is loaded, the predictor of cell c-1 and the
-// corrector of cell c-3 are produced (the 7-cell stencil of Sect. 3), so each
-// cell is read from HBM once per pass.  "The value one position back" comes
-// from one of two policies:
-//   Strided (y and z sweeps): a lane owns a pencil segment and walks it; the
-//     previous position is the lane's own register from the last iteration.
-//     Adjacent lanes are adjacent along x, so every access is coalesced.
-//   Lanes (x sweep): the 64 lanes of a wave hold 64 consecutive positions of
-//     a stream of whole x rows (each row padded by its 3-cell halos); the
-//     previous position is the neighbour lane (DPP wave shift).  The first
-//     lanes of each iteration recompute the positions the previous one ended
-//     on, so no value crosses iterations.  Again every access is coalesced
-//     and no row is transposed.
+// Both sweeps evaluate the 7-cell stencil of Sect. 3 in one pass, each cell read
+// from HBM once but for halos, by one of two policies:
+//   Strided (y and z sweeps): a lane owns a pencil segment and walks it as a
+//     streaming pipeline: when cell c is loaded, the predictor of cell c-1 and
+//     the corrector of cell c-3 are produced, and the value one position back is
+//     the lane's own register from the last iteration.  Adjacent lanes are
+//     adjacent along x, so every access is coalesced.
+//   Lanes (x sweeps, and y and z of small boxes): a lane holds K consecutive cells
+//     of a row along the sweep, a wave a window of 64 K of a stream of whole
+//     rows, each padded by its ghosts; the scheme runs stage by stage with every
+//     value in the lane of its cell, and a neighbour's value is the lane's own or
+//     one DPP wave shift away.  The outer lanes of a window are a halo that the
+//     neighbouring windows output, so no value crosses windows; the waves of a
+//     block that work on one box take the windows of their rows in turn.  Along
+//     x every access is coalesced and no row is transposed.
 #pragma once
 
 #include "layout.h"
@@ -28,9 +29,8 @@
 
 // Multiply-adds are fused only within one source expression (never across
 // statements), so the rounding of every value is fixed by the source alone:
-// the kernels that stream the same arithmetic in different layouts (lanes,
-// pairs of positions, strided pencils, any work shape) give bitwise the same
-// result.
+// the kernels that run the same arithmetic in different layouts (lanes of one
+// cell or two, strided pencils, any work shape) give bitwise the same result.
 #pragma clang fp contract(on)
 
 namespace fish {
@@ -342,8 +342,7 @@ struct FluidHist {
 };
 
 // One stream position: loads of cell c in (uc, bc, phc); returns the
-// corrected state of cell c-3 in un.  u3 is the state of cell c-3 when the
-// caller reloads it (lanes policy); otherwise the history chain supplies it.
+// corrected state of cell c-3 in un.
 // GRAV: 0 none, 1 unsplit source in the predictor and corrector (Eqs. 41-43),
 // 2 split kicks G(dt/2) L G(dt/2) (Eqs. 38-40): the entering cell is kicked
 // by gh_c = (dt/2)(phi_c+1 - phi_c-1)/(2h), which the caller computes from
@@ -461,8 +460,6 @@ __device__ __forceinline__ void fluid_position(const T* uc_in, const Vec<T, 3>& 
   (void)phm3;
 }
 
-// The step factors of a sweep along D: dt / (2h) and dt / h from the box's
-// step scalars (evaluated once per step with dt), 1 / (2h) from its table entry.
 // The step size of every sub-operator and the factors the sweeps take from
 // it, dt / (2 h_d) and dt / h_d per axis (evaluated once per step, not in
 // every wave of every sweep).
@@ -475,6 +472,8 @@ __device__ __forceinline__ void set_step(Scalars* s, const Geo& g, double dt) {
   }
 }
 
+// The step factors of a sweep along D: dt / (2h) and dt / h from the box's
+// step scalars (evaluated once per step with dt), 1 / (2h) from its table entry.
 template <typename T>
 __device__ __forceinline__ FluidConsts<T> fluid_consts(const FluidArgs<T>& a, int D) {
   const double dt = a.sc->dt;
